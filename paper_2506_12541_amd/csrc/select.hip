@@ -6,17 +6,32 @@
 // k* best blocks (higher score first, lower block index on equal scores), stored in
 // ascending block order with -1 in unused slots.
 //
-// The score matrix (N/g x N/l per head) is never stored. One workgroup owns 16 groups of
-// one head: the pooled queries sit in registers as the B operand of f32 MFMA tiles, the
-// four waves stream disjoint 16-token slices of the compressed keys from L2, and every
-// lane keeps a running top-k of (ordered score, ~index) 64-bit keys for its group. The
-// four lists of each group are merged in registers at the end.
-// Scores keep f32 accuracy so that rankings match the float64 definition except where two
-// scores are closer than f32 rounding: each f32 operand is split into three bf16 parts
-// (x = hi + mid + lo up to 2^-27 |x|) and a score is the f32 sum of the six products
-// whose weight reaches 2^-16 (hi hi, hi mid, mid hi, hi lo, lo hi, mid mid), each exact in
-// the bf16 matrix cores: about the error of an f32 product, at 6 bf16 MFMAs per 32-wide
-// slice instead of 8 f32 ones per 4-wide slice.
+// The mean of a block's scores is the score of its keys' sum (over r): the keys are summed
+// over each block first. The score matrix (N/g x N/l' per head) is never stored, and only
+// the few blocks that can be among the k* best are scored in f32. A workgroup owns 64
+// groups of one head, 16 per wave; the block keys are streamed twice in tiles shared
+// by its waves:
+//   1. Scores from unit vectors in f16 (one MFMA per 32 dimensions), times the key's norm,
+//      less a bound on their error: a lower bound of each block's score. Every lane keeps
+//      the largest of each of a few disjoint sets of blocks; the k*-th largest of a
+//      group's set maxima bounds its k*-th best score from below.
+//   2. The same scores plus the bound: blocks that reach the group's threshold (about
+//      1.15 k* of them; every block of the k* best is one) go to the wave's list.
+//   3. The listed blocks are scored with f32 products and sums and ranked within their
+//      group; the selected ones are ordered by block index.
+// Error bound of a unit-vector score: f16 rounds each of the two operands by at most 2^-11
+// of its magnitude, so by Cauchy-Schwarz the score errs by at most 2^-10 (+ 2^-22); the
+// vectors are scaled by 2^7, which keeps what f16 cannot hold (below 2^-24, or below 2^-14
+// if subnormal numbers were flushed) under 2^-17; f32 sums and norms add under 2^-17.
+// kUnitErr is 1.1 * 2^-10. A group whose list overflows (e.g. all scores equal) is scanned
+// in f32 by its wave.
+// What bounds it: VALU issue (75 instructions per 64 blocks and 16 groups in both streams,
+// about 3000 per 16 groups for the ranking), and with few waves per SIMD the latency of each
+// tile. Measured with d = 64, r = 2, k* = 16 (in brackets: one stream of all compressed keys
+// with f32-accurate scores from six MFMAs per 32 dimensions and a 16-deep list in every lane):
+// 65536 queries x 8 heads in groups of 16 0.074 ms (0.250), one by one 0.82 ms (2.96);
+// 2^20 queries x 16 heads in groups of 32 4.0 ms (15.4). Two sets of 16 groups per wave, which
+// halve the LDS reads per group, were slower (0.109 and 0.86 ms: fewer waves).
 #include <type_traits>
 
 #include "common.hpp"
@@ -27,6 +42,14 @@ namespace bsa {
 namespace {
 
 constexpr int kWaves = 4;
+constexpr int kFlat = 512;                // listed blocks of a wave (about 18 per group for k* = 16)
+constexpr int kRing = 4, kAhead = 3;     // key tiles in LDS; of these, loads in flight
+constexpr int kPerGroup = 64;             // listed blocks of a group
+constexpr int kNoBlock = 0x7FFFFFFF;
+constexpr float kUnit = 128.0f;           // scale of the f16 unit vectors
+constexpr float kUnitErr = 1.1f / 1024 * kUnit * kUnit;
+
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 __device__ __forceinline__ uint32_t ordered_bits(float x) {
   x = x + 0.0f;
@@ -38,55 +61,6 @@ __device__ __forceinline__ uint64_t make_key(float score, int blk) {
   return ((uint64_t)ordered_bits(score) << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)blk);
 }
 
-// Inverse of ordered_bits (the score of a key's upper word).
-__device__ __forceinline__ float key_score(uint64_t key) {
-  const uint32_t b = (uint32_t)(key >> 32);
-  return __uint_as_float((b & 0x80000000u) ? (b & 0x7FFFFFFFu) : ~b);
-}
-
-// Insert x into the descending list (keys are unique, x > lst[K - 1]): every entry compares
-// with x independently, then each slot keeps its entry, takes x, or takes its upper
-// neighbour (slots are rewritten from the bottom, so the neighbour is still the old one).
-template <int K>
-__device__ __forceinline__ void topk_insert(uint64_t (&lst)[K], uint64_t x) {
-  bool gt[K];
-#pragma unroll
-  for (int t = 0; t < K; ++t) gt[t] = lst[t] > x;
-#pragma unroll
-  for (int t = K - 1; t >= 1; --t) lst[t] = gt[t] ? lst[t] : (gt[t - 1] ? x : lst[t - 1]);
-  lst[0] = gt[0] ? lst[0] : x;
-}
-
-// The group's four lanes L, L^16, L^32, L^48 exchange through gfx950's VALU lane swaps
-// (no LDS traffic). With both operands holding x, v_permlane16_swap returns the values of
-// the even and the odd 16-lane row of the lane's row pair, v_permlane32_swap those of the
-// lower and the upper half; min and max are symmetric, so either order serves.
-__device__ __forceinline__ void swap16_u64(uint64_t x, uint64_t& a, uint64_t& b) {
-  const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)x, false, false);
-  const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(x >> 32), (uint32_t)(x >> 32), false, false);
-  a = ((uint64_t)hi[0] << 32) | lo[0];
-  b = ((uint64_t)hi[1] << 32) | lo[1];
-}
-__device__ __forceinline__ void swap32_u64(uint64_t x, uint64_t& a, uint64_t& b) {
-  const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)x, false, false);
-  const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(x >> 32), (uint32_t)(x >> 32), false, false);
-  a = ((uint64_t)hi[0] << 32) | lo[0];
-  b = ((uint64_t)hi[1] << 32) | lo[1];
-}
-__device__ __forceinline__ uint64_t group_min_u64(uint64_t x) {
-  uint64_t a, b;
-  swap16_u64(x, a, b);
-  x = a < b ? a : b;
-  swap32_u64(x, a, b);
-  return a < b ? a : b;
-}
-__device__ __forceinline__ uint64_t group_max_u64(uint64_t x) {
-  uint64_t a, b;
-  swap16_u64(x, a, b);
-  x = a > b ? a : b;
-  swap32_u64(x, a, b);
-  return a > b ? a : b;
-}
 // x of the lanes r, r + 16, r + 32, r + 48 (r = L mod 16), in that order
 __device__ __forceinline__ void group_gather(int x, int (&out)[4]) {
   const auto p = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)x, false, false);
@@ -98,305 +72,605 @@ __device__ __forceinline__ void group_gather(int x, int (&out)[4]) {
   out[3] = (int)o[1];
 }
 
-// Pooled queries (Eq. 11): q_p = (1/g) * sum of the group's real queries, one thread per
-// (group, channel); consecutive threads read consecutive channels of each query row.
-template <typename T, int HD>
-__global__ void pool_q_kernel(const T* q, const uint8_t* valid, int H, int N, int g, long long total, float* qpool) {
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= total) return;
-  const int c = (int)(i % HD);
-  const long long gp = i / HD;             // (b*H + h) * (N/g) + p
-  const int ngroups = N / g;
-  const long long bh = gp / ngroups;
-  const int p = (int)(gp % ngroups);
-  const int b = (int)(bh / H);
-  const T* qr = q + ((size_t)bh * N + (size_t)p * g) * HD + c;
-  const uint8_t* vb = valid ? valid + (size_t)b * N + (size_t)p * g : nullptr;
-  float s = 0.f;
-#pragma unroll 8
-  for (int t = 0; t < g; ++t)
-    if (vb == nullptr || vb[t]) s += to_f32<T>(qr[(size_t)t * HD]);
-  qpool[i] = s / (float)g;
+// Sum of an int over the group's four lanes.
+__device__ __forceinline__ int group_sum(int x) {
+  int v[4];
+  group_gather(x, v);
+  return (v[0] + v[1]) + (v[2] + v[3]);
 }
 
-// hi = bf16(x), mid = bf16(x - hi), lo = bf16(x - hi - mid) (the differences are exact in
-// f32); eight elements per thread.
-__device__ __forceinline__ void split3(const float* x, bf16x8& hi, bf16x8& mid, bf16x8& lo) {
-  float h[8], md[8], lw[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const float a = x[e];
-    const float ah = bf2f(f2bf(a));
-    const float r1 = a - ah;
-    const float am = bf2f(f2bf(r1));
-    h[e] = ah;
-    md[e] = am;
-    lw[e] = r1 - am;
+// Rows of HD values, one 8-value chunk per lane of HD / 8 lanes, to f16 unit vectors times
+// 2^7, and the row's norm (0 for a zero row, whose vector is zero; a row that is not
+// finite gives NaN products). Scaling by a power of two first keeps the sum of squares in
+// range for any magnitude.
+template <typename MaxF, typename SumF>
+__device__ __forceinline__ float unit_scale(const float* x, int n, int& e, MaxF rmax, SumF rsum) {
+  float mx = 0.f;
+  for (int i = 0; i < n; ++i) mx = fmaxf(mx, fabsf(x[i]));
+  mx = rmax(mx);
+  e = mx > 0.f ? __builtin_amdgcn_frexp_expf(mx) : 0;
+  float ss = 0.f;
+  for (int i = 0; i < n; ++i) {
+    const float y = ldexpf(x[i], -e);
+    ss += y * y;
   }
-  hi = make_chunk<bf16_t>(h);
-  mid = make_chunk<bf16_t>(md);
-  lo = make_chunk<bf16_t>(lw);
+  ss = rsum(ss);
+  return ss;
 }
 
-__global__ void __launch_bounds__(256) split3_kernel(const float* __restrict__ x, long long n8,
-                                                     bf16_t* __restrict__ hi, bf16_t* __restrict__ mid,
-                                                     bf16_t* __restrict__ lo) {
-  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n8) return;
-  const f32x8 v = load_chunk(x + 8 * i);
+// Preparation of the selection in one launch. Workgroups below `pool_blocks`: pooled
+// queries (Eq. 11), q_p = (1/g) * sum of the group's real queries in slot order, eight
+// channels per thread (HBM: one read of Q in 16-byte loads; a thread per channel took 33
+// instead of 14 us at 65536 queries x 8 heads of 64). The others: every selection block's
+// compressed keys summed (ksum, not written for r = 1: kcmp holds them), as f16 unit vectors
+// and negated norms, HD / 8 threads per block; blocks without a real token get the norm NaN,
+// which no comparison passes, and (for r > 1) a sum of NaN. A head's norms are padded with
+// NaN to a whole tile of the selection kernel.
+template <typename T, int HD>
+__global__ void __launch_bounds__(256) select_prep_kernel(const T* __restrict__ q, const uint8_t* __restrict__ valid,
+                                                          int H, int lgn, int lgg, long long pool_n8, int pool_blocks,
+                                                          float* __restrict__ qpool, const float* __restrict__ kcmp,
+                                                          const uint8_t* __restrict__ cvalid, int lgb, int lgr,
+                                                          long long blocks, float* __restrict__ ksum,
+                                                          uint16_t* __restrict__ kunit, float* __restrict__ knorm) {
+  constexpr int CPR = HD / 8;
+  if ((int)blockIdx.x < pool_blocks) {
+    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (i >= pool_n8) return;
+    const int c = (int)(i % CPR) * 8, g = 1 << lgg;
+    const long long tok = (i / CPR) << lgg;   // (b*H + h) * N + the group's first slot
+    const T* qr = q + tok * HD + c;
+    const uint8_t* vb =
+        valid ? valid + ((long long)((uint32_t)(tok >> lgn) / (uint32_t)H) << lgn) + (tok & ((1LL << lgn) - 1))
+              : nullptr;
+    float s[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) s[e] = 0.f;
+#pragma unroll 8
+    for (int t = 0; t < g; ++t) {
+      const typename Chunk<T>::type v = load_chunk(qr + (size_t)t * HD);
+      const bool ok = vb == nullptr || vb[t];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) s[e] = ok ? s[e] + (float)v[e] : s[e];
+    }
+    f32x8 o;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] = s[e] / (float)g;
+    *reinterpret_cast<f32x8*>(qpool + 8 * i) = o;
+    return;
+  }
+  const long long i = (long long)(blockIdx.x - pool_blocks) * 256 + threadIdx.x;
+  if (i >= blocks * CPR) return;   // whole rows: 256 is a multiple of CPR
+  const long long blk = i / CPR;   // (b*H + h) * nblk + block, nblk = 2^lgb
+  const int r = 1 << lgr;
   float a[8];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) a[e] = v[e];
-  bf16x8 h, m, l;
-  split3(a, h, m, l);
-  *reinterpret_cast<bf16x8*>(hi + 8 * i) = h;
-  *reinterpret_cast<bf16x8*>(mid + 8 * i) = m;
-  *reinterpret_cast<bf16x8*>(lo + 8 * i) = l;
+  for (int e = 0; e < 8; ++e) a[e] = 0.f;
+  for (int k = 0; k < r; ++k) {
+    const f32x8 v = load_chunk(kcmp + ((blk << lgr) + k) * HD + 8 * (i % CPR));
+#pragma unroll
+    for (int e = 0; e < 8; ++e) a[e] += v[e];
+  }
+  const uint8_t* cv = cvalid + ((long long)((uint32_t)(blk >> lgb) / (uint32_t)H) << (lgb + lgr)) +
+                      ((blk & ((1LL << lgb) - 1)) << lgr);
+  uint32_t any = 0;
+  for (int k = 0; k < r; ++k) any |= cv[k];
+  int ex;
+  const float ss = unit_scale(
+      a, 8, ex,
+      [](float x) {
+#pragma unroll
+        for (int o = 1; o < CPR; o <<= 1) x = fmaxf(x, __shfl_xor(x, o, 64));
+        return x;
+      },
+      [](float x) {
+#pragma unroll
+        for (int o = 1; o < CPR; o <<= 1) x += __shfl_xor(x, o, 64);
+        return x;
+      });
+  const float nrm = sqrtf(ss);
+  const float rn = ss == 0.f ? 0.f : kUnit / nrm;
+  f16x8 u;
+  f32x8 o;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    u[e] = (_Float16)(ldexpf(a[e], -ex) * rn);
+    o[e] = any ? a[e] : __builtin_nanf("");
+  }
+  *reinterpret_cast<f16x8*>(kunit + 8 * i) = u;
+  if (r > 1) *reinterpret_cast<f32x8*>(ksum + 8 * i) = o;
+  if (i % CPR == 0) {
+    float* kn = knorm + (blk >> lgb) * (long long)max(1 << lgb, 4096 / HD);
+    const int t = (int)(blk & ((1LL << lgb) - 1));
+    kn[t] = any ? -ldexpf(nrm, ex) : __builtin_nanf("");
+    for (int p = t + (1 << lgb); p < 4096 / HD; p += 1 << lgb) kn[p] = __builtin_nanf("");
+  }
 }
 
-template <typename T, int HD, int K, int R>
-__global__ void __launch_bounds__(kWaves * 64) select_kernel(const float* qpool, const bf16_t* kplanes,
-                                                             const uint8_t* cvalid, int H, int N, int l, int ls,
-                                                             int m, int g, int mask_own, int kk, int* sel) {
-  constexpr int NCH = HD / 32;
-  constexpr int KT = 64;        // compressed tokens per staged tile
-  constexpr int GW = 16 * kWaves;   // groups per workgroup
-  // the three bf16 parts of a tile of compressed keys, double-buffered (distinct objects)
-  __shared__ __attribute__((aligned(16))) bf16_t kh0[KT * HD], km0[KT * HD], kl0[KT * HD];
-  __shared__ __attribute__((aligned(16))) bf16_t kh1[KT * HD], km1[KT * HD], kl1[KT * HD];
-  __shared__ uint8_t cv0[KT], cv1[KT];
-  __shared__ uint32_t av0, av1;   // 1: every compressed token of the staged tile is real
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  const int r = lane & 15, j = lane >> 4;
-  const int ngroups = N / g;
-  const int bh = blockIdx.y;
-  const int b = bh / H;
-  const int p0 = blockIdx.x * GW;
-  const int ntok = N / l;
-  const size_t plane = (size_t)gridDim.y * ntok * HD;   // elements of one part
-  const bf16_t* ph = kplanes + (size_t)bh * ntok * HD;
-  const uint8_t* cv = cvalid + (size_t)b * (N / l);
-
-  // compressed-token tiles: the three parts moved by direct global->LDS loads; token
-  // validity bytes are read before the tile loads (by wave 0: KT == 64), and a flag marks
-  // tiles whose tokens are all real
-  static_assert(KT == 64, "wave 0 reads the validity of one tile");
-  auto issue = [&](int t0, bf16_t* dh, bf16_t* dm, bf16_t* dl, uint8_t* cd, uint32_t* ad) {
-    uint8_t c = 0;
-    if (threadIdx.x < KT) c = t0 + (int)threadIdx.x < ntok ? cv[t0 + threadIdx.x] : 0;
-    dma_tile<HD, KT, kWaves>(dh, ph, t0, ntok, wid, lane);
-    dma_tile<HD, KT, kWaves>(dm, ph + plane, t0, ntok, wid, lane);
-    dma_tile<HD, KT, kWaves>(dl, ph + 2 * plane, t0, ntok, wid, lane);
-    if (threadIdx.x < KT) cd[threadIdx.x] = c;
-    if (wid == 0) {
-      const uint64_t real = __builtin_amdgcn_ballot_w64(c != 0);
-      if (lane == 0) *ad = real == ~0ull ? 1u : 0u;
-    }
+// Sum over aligned runs of eight lanes, in every lane of the run.
+__device__ __forceinline__ float sum8(float x) {
+  auto dpp = [](float v, auto ctrl) {
+    return __int_as_float(
+        __builtin_amdgcn_update_dpp(0, __float_as_int(v), decltype(ctrl)::value, 0xF, 0xF, true));
   };
-  issue(0, kh0, km0, kl0, cv0, &av0);
+  x += dpp(x, std::integral_constant<int, 0xB1>{});    // lane ^ 1
+  x += dpp(x, std::integral_constant<int, 0x4E>{});    // lane ^ 2
+  x += dpp(x, std::integral_constant<int, 0x141>{});   // mirrored within eight lanes
+  return x;
+}
 
-  // pooled queries of this lane's group (B operand), in three bf16 parts
-  const int pg = p0 + 16 * wid + r;
-  const float* qpr = qpool + ((size_t)bh * ngroups + (pg < ngroups ? pg : 0)) * HD;
-  bf16x8 qh[NCH], qm[NCH], ql[NCH];
+// Score of a selection block in f32 (r times it: <q, sum of its compressed keys>), by eight
+// lanes (sub = lane % 8, four dimensions of each 32 per lane, so a row is read as whole
+// 128-byte lines).
+template <int NCH>
+__device__ __forceinline__ float dot8(const f32x4 (&x)[NCH], const f32x4 (&y)[NCH]) {
+  float s = 0.f;
 #pragma unroll
-  for (int c = 0; c < NCH; ++c) {
-    const f32x8 v = load_chunk(qpr + 32 * c + 8 * j);
-    float a[8];
+  for (int c = 0; c < NCH; ++c)
 #pragma unroll
-    for (int e = 0; e < 8; ++e) a[e] = v[e];
-    split3(a, qh[c], qm[c], ql[c]);
+    for (int e = 0; e < 4; ++e) s = fmaf(x[c][e], y[c][e], s);
+  return sum8(s);
+}
+
+// a[0 .. n) sorted descending from a bitonic sequence (n a power of two).
+template <int N>
+__device__ __forceinline__ void bitonic_merge(float (&a)[N]) {
+#pragma unroll
+  for (int h = N / 2; h >= 1; h >>= 1)
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+      if ((i & h) == 0) {
+        const float x = a[i], y = a[i + h];
+        a[i] = fmaxf(x, y);
+        a[i + h] = fminf(x, y);
+      }
+}
+template <int N>
+__device__ __forceinline__ void sort_desc(float (&a)[N]) {
+#pragma unroll
+  for (int w = 2; w <= N; w <<= 1)
+#pragma unroll
+    for (int h = w / 2; h >= 1; h >>= 1)
+#pragma unroll
+      for (int i = 0; i < N; ++i)
+        if ((i & h) == 0) {
+          const bool desc = w == N || (i & w) == 0;
+          const float x = a[i], y = a[i + h];
+          a[i] = desc ? fmaxf(x, y) : fminf(x, y);
+          a[i + h] = desc ? fminf(x, y) : fmaxf(x, y);
+        }
+}
+
+// The K-th largest of the group's 4 NB values, NB per lane (K = NB or 2 NB).
+template <int K, int NB>
+__device__ __forceinline__ float group_kth(float (&a)[NB]) {
+  static_assert(NB == K || 2 * NB == K, "values per lane");
+  sort_desc(a);
+  float t[K];
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    float lo, hi;   // the lane pair's lists: values of the even and of the odd 16-lane row
+    lo = xor16_pair(a[i], hi);
+    float lo2, hi2;
+    lo2 = xor16_pair(a[NB - 1 - i], hi2);
+    if (NB == K) {
+      t[i] = fmaxf(lo, hi2);   // the best K of both lists, bitonic
+    } else {
+      t[i] = lo;               // both lists: descending, then ascending
+      t[NB + i] = hi2;
+    }
   }
-
-  const int my_group = p0 + 16 * wid + r;
-  const int my_ball = (my_group * g) / m;
-  // selection blocks of the group's own ball (excluded when mask_own)
-  const int own_lo = mask_own ? my_ball * (m / ls) : -1;
-  const int own_hi = mask_own ? own_lo + m / ls : -1;
-  uint64_t lst[K];
+  bitonic_merge(t);
+  float best = __builtin_huge_valf();
 #pragma unroll
-  for (int t = 0; t < K; ++t) lst[t] = 0;
-  // The group's four lanes each keep a list; the group needs only its k* best (k* <= K).
-  // Each lane's K/4 best are all at least the smallest of the four lanes' (K/4)-th keys,
-  // so the group already holds K >= k* keys at or above that value and no candidate below
-  // it can enter the final k*: the lanes filter on it as well as on their own K-th key.
+  for (int i = 0; i < K; ++i) {
+    float lo, hi, lo2, hi2;
+    lo = xor32_pair(t[i], hi);
+    lo2 = xor32_pair(t[K - 1 - i], hi2);
+    (void)hi;
+    (void)lo2;
+    best = fminf(best, fmaxf(lo, hi2));
+  }
+  return best;
+}
 
-  auto step = [&](int t0, const bf16_t* th, const bf16_t* tm, const bf16_t* tl_, const uint8_t* ct,
-                  const uint32_t* at, bf16_t* nh, bf16_t* nm, bf16_t* nl, uint8_t* cn, uint32_t* an) {
-    vm_drain();
-    __syncthreads();
-    const bool all_real = *at != 0u;
-    if (t0 + KT < ntok) issue(t0 + KT, nh, nm, nl, cn, an);
-    const uint64_t gthr = group_min_u64(lst[K / 4 - 1]);
-    const uint64_t thr = gthr > lst[K - 1] ? gthr : lst[K - 1];
-    // candidates pass on their score first (a key above thr has a score >= thr's); the
-    // exact key comparison is made for the candidate that is inserted
-    const float thr_f = thr == 0 ? kNegInf : key_score(thr);
-    // the tile's candidates of this lane (4 / R per 16-token sub-tile, ascending blocks),
-    // as scores; -inf = none
-    constexpr int NPS = 4 / R;
-    constexpr int NCAND = (KT / 16) * NPS;
-    const int blk0 = (t0 + 4 * j) / R;
-    float cand[NCAND];
-    // scores of the tile's 4 sub-tiles: independent MFMA chains, interleaved
-    f32x4 accs[KT / 16];
+// Eight row fragments of a key tile: at a0 plus 16 rows each (128-byte rows: four at a0, the
+// same four rows' second half at a1). One statement that also waits: the compiler would
+// otherwise wait for the tile loads in flight, whose stages it cannot tell apart.
+template <int HD>
+__device__ __forceinline__ void lds_frags8(uint32_t a0, uint32_t a1, f16x8 (&f)[8]) {
+  if (HD == 64)
+    asm volatile(
+        "ds_read_b128 %0, %8\n\tds_read_b128 %1, %8 offset:2048\n\tds_read_b128 %2, %8 offset:4096\n\t"
+        "ds_read_b128 %3, %8 offset:6144\n\tds_read_b128 %4, %9\n\tds_read_b128 %5, %9 offset:2048\n\t"
+        "ds_read_b128 %6, %9 offset:4096\n\tds_read_b128 %7, %9 offset:6144\n\ts_waitcnt lgkmcnt(0)"
+        : "=&v"(f[0]), "=&v"(f[1]), "=&v"(f[2]), "=&v"(f[3]), "=&v"(f[4]), "=&v"(f[5]), "=&v"(f[6]), "=&v"(f[7])
+        : "v"(a0), "v"(a1)
+        : "memory");
+  else
+    asm volatile(
+        "ds_read_b128 %0, %8\n\tds_read_b128 %1, %8 offset:1024\n\tds_read_b128 %2, %8 offset:2048\n\t"
+        "ds_read_b128 %3, %8 offset:3072\n\tds_read_b128 %4, %8 offset:4096\n\tds_read_b128 %5, %8 offset:5120\n\t"
+        "ds_read_b128 %6, %8 offset:6144\n\tds_read_b128 %7, %8 offset:7168\n\ts_waitcnt lgkmcnt(0)"
+        : "=&v"(f[0]), "=&v"(f[1]), "=&v"(f[2]), "=&v"(f[3]), "=&v"(f[4]), "=&v"(f[5]), "=&v"(f[6]), "=&v"(f[7])
+        : "v"(a0)
+        : "memory");
+}
+// Norms of a tile: lane j's four blocks of every sub-tile (64 bytes apart).
+template <int NST>
+__device__ __forceinline__ void lds_norms(uint32_t a, f32x4 (&n)[NST]) {
+  static_assert(NST == 4 || NST == 8, "sub-tiles");
+  if constexpr (NST == 4)
+    asm volatile(
+        "ds_read_b128 %0, %4\n\tds_read_b128 %1, %4 offset:64\n\tds_read_b128 %2, %4 offset:128\n\t"
+        "ds_read_b128 %3, %4 offset:192\n\ts_waitcnt lgkmcnt(0)"
+        : "=&v"(n[0]), "=&v"(n[1]), "=&v"(n[2]), "=&v"(n[3])
+        : "v"(a)
+        : "memory");
+  else
+    asm volatile(
+        "ds_read_b128 %0, %8\n\tds_read_b128 %1, %8 offset:64\n\tds_read_b128 %2, %8 offset:128\n\t"
+        "ds_read_b128 %3, %8 offset:192\n\tds_read_b128 %4, %8 offset:256\n\tds_read_b128 %5, %8 offset:320\n\t"
+        "ds_read_b128 %6, %8 offset:384\n\tds_read_b128 %7, %8 offset:448\n\ts_waitcnt lgkmcnt(0)"
+        : "=&v"(n[0]), "=&v"(n[1]), "=&v"(n[2]), "=&v"(n[3]), "=&v"(n[4]), "=&v"(n[5]), "=&v"(n[6]), "=&v"(n[7])
+        : "v"(a)
+        : "memory");
+}
+
+// s_waitcnt with vmcnt = V (expcnt and lgkmcnt left at their maxima)
+template <int V>
+__device__ __forceinline__ void vm_wait() {
+  static_assert(V >= 0 && V < 64, "vmcnt");
+  __builtin_amdgcn_s_waitcnt((V & 15) | ((V >> 4) << 14) | (7 << 4) | (15 << 8));
+}
+
+// lgls, lgm, lgg: log2 of l', m and g; check: ksum holds keys of blocks without a real token.
+template <int HD, int K>
+__global__ void __launch_bounds__(kWaves * 64)
+    select_kernel(const float* __restrict__ qpool, const float* __restrict__ ksum, const uint16_t* __restrict__ kunit,
+                  const float* __restrict__ knorm, int N, int lgls, int lgm, int lgg, int mask_own, int check, int kk,
+                  int* __restrict__ sel) {
+  constexpr int NCH = HD / 32;
+  constexpr int KT = 4096 / HD;     // blocks per staged tile (8 KB)
+  constexpr int GW = 16 * kWaves;   // groups per workgroup
+  constexpr int NST = KT / 16;      // 16-block sub-tiles of a tile
+  constexpr int NC = 4 * NST;       // blocks per lane and tile
+  constexpr int NB = K;             // sets per lane: a block's set is its place in the tile
+  static_assert(NC % NB == 0, "sets");
+  // a ring of key tiles (8 KB each) and their norms, kAhead of them in flight
+  __shared__ __attribute__((aligned(1024))) bf16_t ring[kRing][KT * HD];
+  __shared__ __attribute__((aligned(256))) float nring[kRing][KT];
+  __shared__ uint32_t flat_s[kWaves][kFlat];   // block | group << 20
+  __shared__ int cnt_s[kWaves][16];
+  __shared__ __attribute__((aligned(16))) int best_s[kWaves][16 * 16];
+  static_assert(sizeof(ring) >= kWaves * 16 * kPerGroup * 8, "reused tiles");
+  const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r = lane & 15, j = lane >> 4;
+  const int ngroups = N >> lgg;
+  const int bh = blockIdx.y;
+  const int p0 = blockIdx.x * GW + 16 * wid;   // the wave's first group
+  const int nblk = N >> lgls;
+  const bf16_t* ku = kunit + (size_t)bh * nblk * HD;
+  const float* kn = knorm + (size_t)bh * max(nblk, KT);   // negated; padded with NaN to a tile
+  const float* kc = ksum + (size_t)bh * nblk * HD;
+  const float* qb = qpool + (size_t)bh * ngroups * HD;
+
+  // tiles u = 0 .. 2 nt - 1: the keys once per pass. Every wave loads its share of a tile
+  // and all of the tile's norms, so that its loads in flight count alike.
+  const int nt = (nblk + KT - 1) / KT;
+  constexpr int PER = 8 / kWaves + KT / 64;
+  auto issue = [&](int u) {
+    if (u >= 2 * nt) return;
+    const int t0 = (u >= nt ? u - nt : u) * KT;
+    dma_tile<HD, KT, kWaves>(ring[u % kRing], ku, t0, nblk, wid, lane);
 #pragma unroll
-    for (int st = 0; st < KT / 16; ++st) accs[st] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < KT / 64; ++i)
+      __builtin_amdgcn_global_load_lds(kn + t0 + 64 * i + lane, &nring[u % kRing][64 * i], 4, 0, 0);
+  };
+  // tile u is in LDS for every wave, and the stage of tile u - 1 is free for tile u + kAhead
+  auto advance = [&](int u) {
+    if (u + kAhead <= 2 * nt)
+      vm_wait<(kAhead - 1) * PER>();
+    else
+      vm_drain();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    issue(u + kAhead);
+  };
+
+#pragma unroll
+  for (int u = 0; u < kAhead; ++u) issue(u);
+
+  // this lane's group: unit query (B operand)
+  const int pg = p0 + r;
+  const bool live = pg < ngroups;
+  f16x8 qf[NCH];
+  bool over;   // the group is scanned whole instead (a zero query: all blocks tie)
+  {
+    const float* qr = qb + (size_t)(live ? pg : 0) * HD;
+    float a[8 * NCH];
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
-      bf16x8 ah[KT / 16], am[KT / 16], al[KT / 16];
+      const f32x8 v = load_chunk(qr + 32 * c + 8 * j);
 #pragma unroll
-      for (int st = 0; st < KT / 16; ++st) {   // row 16 st + r, dims 32 c + 8 j ..
-        ah[st] = lds_row_chunk<HD>(th, 16 * st + r, 4 * c + j);
-        am[st] = lds_row_chunk<HD>(tm, 16 * st + r, 4 * c + j);
-        al[st] = lds_row_chunk<HD>(tl_, 16 * st + r, 4 * c + j);
-      }
-      // smaller terms first
-#pragma unroll
-      for (int st = 0; st < KT / 16; ++st) accs[st] = mma(al[st], qh[c], accs[st]);
-#pragma unroll
-      for (int st = 0; st < KT / 16; ++st) accs[st] = mma(ah[st], ql[c], accs[st]);
-#pragma unroll
-      for (int st = 0; st < KT / 16; ++st) accs[st] = mma(am[st], qm[c], accs[st]);
-#pragma unroll
-      for (int st = 0; st < KT / 16; ++st) accs[st] = mma(am[st], qh[c], accs[st]);
-#pragma unroll
-      for (int st = 0; st < KT / 16; ++st) accs[st] = mma(ah[st], qm[c], accs[st]);
-#pragma unroll
-      for (int st = 0; st < KT / 16; ++st) accs[st] = mma(ah[st], qh[c], accs[st]);
+      for (int e = 0; e < 8; ++e) a[8 * c + e] = v[e];
     }
-    // branch-free per candidate; the validity bytes are read only for tiles with padding
-    // (a wave-uniform choice)
-    auto build = [&](auto with_valid) {
+    int ex;
+    const float ss = unit_scale(a, 8 * NCH, ex, [](float x) { return col_max(x); }, [](float x) { return col_sum(x); });
+    over = live && ss == 0.f;
+    const float rn = ss == 0.f ? 0.f : kUnit / sqrtf(ss);
 #pragma unroll
-      for (int st = 0; st < KT / 16; ++st) {
-        const f32x4 acc = accs[st];
-        // lane holds scores of compressed tokens t0 + 16 st + 4j + i for group my_group
-        const int tl = 16 * st + 4 * j;
-        const bool in_range = t0 + 16 * st < ntok;
+    for (int c = 0; c < NCH; ++c)
 #pragma unroll
-        for (int u = 0; u < NPS; ++u) {
-          float sc = 0.f;
+      for (int e = 0; e < 8; ++e) qf[c][e] = (_Float16)(ldexpf(a[8 * c + e], -ex) * rn);
+  }
+
+  // blocks of the group's own ball (excluded when mask_own); a wave compares only in tiles
+  // that touch a ball of one of its groups
+  const int lgb = lgm - lgls;   // blocks per ball
+  const int own_lo = (pg >> (lgm - lgg)) << lgb;
+  const int wave_lo = mask_own ? (p0 >> (lgm - lgg)) << lgb : 0;
+  const int wave_hi = mask_own ? (((p0 + 15) >> (lgm - lgg)) + 1) << lgb : 0;
+  auto own = [&](int blk) { return (uint32_t)(blk - own_lo) < (1u << lgb); };
+
+  // the unit scores of tile u (plus `start`) and the blocks' negated norms: fn(index of the
+  // block, norm, score); their product is minus the block's score over the query's norm.
+  // Row fragments of sub-tile st lie 16 rows apart (one swizzle), so two addresses serve all.
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)&ring[0][0];
+  const uint32_t ldsn = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)&nring[0][0] + 16 * j;
+  auto scores = [&](int u, float start, auto&& fn) {
+    const f32x4 st4 = {start, start, start, start};
+    const uint32_t base = lds0 + (u % kRing) * (KT * HD * 2) + r * HD * 2;
+    f16x8 kf[8];
+    lds_frags8<HD>(base + 16 * (j ^ swz<HD>(r)), base + 16 * ((4 + j) ^ swz<HD>(r)), kf);
+    f32x4 acc[NST], nn[NST];
 #pragma unroll
-          for (int i = 0; i < R; ++i) sc += acc[u * R + i];
-          sc *= 1.0f / (float)R;
-          bool ok = in_range;
-          if (decltype(with_valid)::value) {
-            uint32_t any = 0;
+    for (int c = 0; c < NCH; ++c)
 #pragma unroll
-            for (int i = 0; i < R; ++i) any |= ct[tl + u * R + i];
-            ok = ok & (any != 0);
-          }
-          const int blk = blk0 + st * (16 / R) + u;
-          ok = ok & !((blk >= own_lo) & (blk < own_hi)) & (sc >= thr_f);
-          cand[st * NPS + u] = ok ? sc : kNegInf;
-        }
-      }
-    };
-    if (all_real)
-      build(std::false_type{});
+      for (int st = 0; st < NST; ++st)
+        acc[st] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kf[c * NST + st], qf[c], c ? acc[st] : st4, 0, 0, 0);
+    lds_norms<NST>(ldsn + (u % kRing) * (KT * 4), nn);
+#pragma unroll
+    for (int st = 0; st < NST; ++st)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) fn(4 * st + t, nn[st][t], acc[st][t]);
+  };
+  // the block of index t in a tile that starts at block t0
+  auto block_of = [&](int t0, int t) { return t0 + 16 * (t / 4) + 4 * j + t % 4; };
+
+  float top[NB];   // minus each set's largest lower bound
+#pragma unroll
+  for (int t = 0; t < NB; ++t) top[t] = __builtin_huge_valf();
+#pragma unroll 1
+  for (int u = 0; u < nt; ++u) {
+    advance(u);
+    const int t0 = u * KT;
+    if (t0 < wave_hi && t0 + KT > wave_lo)
+      scores(u, -kUnitErr, [&](int t, float n, float sc) {
+        float& x = top[t % NB];
+        x = fminf(x, own(block_of(t0, t)) ? __builtin_huge_valf() : n * sc);
+      });
     else
-      build(std::true_type{});
-    // insert the qualifying candidates best first; the wave repeats only as many times as
-    // its busiest lane needs (most candidates fall below the lane's current k-th key)
+      scores(u, -kUnitErr, [&](int t, float n, float sc) {
+        float& x = top[t % NB];
+        x = fminf(x, n * sc);
+      });
+  }
+  // just below the k*-th largest lower bound (-inf: fewer than K sets hold a block), so that
+  // blocks that reach it lie above; NaN passes no block
+#pragma unroll
+  for (int t = 0; t < NB; ++t) top[t] = -top[t];
+  float thr = group_kth<K, NB>(top);
+  thr = thr == 0.f ? __int_as_float((int)0x80000001)
+                   : thr > kNegInf ? __int_as_float(__float_as_int(thr) + (thr > 0.f ? -1 : 1)) : thr;
+  thr = live && !over ? thr : __builtin_nanf("");
+
+  // Hits (threshold minus upper bound below zero) are collected as sign bits, a tile's NC
+  // candidates at a time, and moved to the wave's list every 32 candidates: a few rounds, each
+  // taking one hit of every lane that has one. (A branch per candidate took 57 instead of 45 us
+  // at 65536 queries in groups of 16.)
+  uint32_t* flat = flat_s[wid];
+  int total = 0;   // wave-uniform; entries past kFlat are counted, not kept
+  const uint32_t tag = ((uint32_t)r << 20) + (uint32_t)(4 * j);
+  uint32_t bits = 0;
+  constexpr int TF = 32 / NC;   // tiles per move
+  auto move = [&](int tile, int pushed) {   // `pushed` candidates since tile `tile`
     for (;;) {
-      float bs = kNegInf;
-      int bi = 0;
-#pragma unroll
-      for (int t = 0; t < NCAND; ++t) {   // first maximum: the lowest block among equal scores
-        const bool better = cand[t] > bs;
-        bs = better ? cand[t] : bs;
-        bi = better ? t : bi;
-      }
-      const uint64_t key = bs > kNegInf ? make_key(bs, blk0 + (bi / NPS) * (16 / R) + bi % NPS) : 0;
-      const uint64_t lim = thr > lst[K - 1] ? thr : lst[K - 1];
-      const bool take = key > lim;
-      if (!__builtin_amdgcn_ballot_w64(take)) break;
-      if (take) {
-        topk_insert<K>(lst, key);
-#pragma unroll
-        for (int t = 0; t < NCAND; ++t) cand[t] = t == bi ? kNegInf : cand[t];
-      } else {
-#pragma unroll
-        for (int t = 0; t < NCAND; ++t) cand[t] = kNegInf;
-      }
+      const uint64_t has = __builtin_amdgcn_ballot_w64(bits != 0);
+      if (!has) break;
+      const int at = total + __builtin_amdgcn_mbcnt_hi((uint32_t)(has >> 32),
+                                                       __builtin_amdgcn_mbcnt_lo((uint32_t)has, 0));
+      const int top1 = 31 - __builtin_clz(bits | 1);
+      const int ord = pushed - 1 - top1, t = ord % NC;
+      if (bits != 0 && at < kFlat) flat[at] = tag + (uint32_t)((tile + ord / NC) * KT + 16 * (t / 4) + t % 4);
+      bits &= ~(1u << top1);
+      total += __popcll(has);
     }
   };
-  for (int t0 = 0; t0 < ntok; t0 += 2 * KT) {
-    step(t0, kh0, km0, kl0, cv0, &av0, kh1, km1, kl1, cv1, &av1);
-    if (t0 + KT < ntok) step(t0 + KT, kh1, km1, kl1, cv1, &av1, kh0, km0, kl0, cv0, &av0);
+#pragma unroll 1
+  for (int u = nt; u < 2 * nt; ++u) {
+    advance(u);
+    const int t0 = (u - nt) * KT;
+    if (t0 < wave_hi && t0 + KT > wave_lo)
+      scores(u, kUnitErr, [&](int t, float n, float sc) {
+        const float x = own(block_of(t0, t)) ? 0.f : fmaf(n, sc, thr);
+        bits = __builtin_amdgcn_alignbit(bits, __float_as_uint(x), 31);
+      });
+    else
+      scores(u, kUnitErr, [&](int, float n, float sc) {
+        bits = __builtin_amdgcn_alignbit(bits, __float_as_uint(fmaf(n, sc, thr)), 31);
+      });
+    const int done = (u - nt) % TF + 1;
+    if (done == TF || u == 2 * nt - 1) move(u - nt - done + 1, done * NC);
   }
-  // merge: the 4 sorted lists of group r sit in lanes r, r + 16, r + 32, r + 48 (the wave's
-  // 16 groups side by side). k* rounds of a 4-way merge: the group's best head (two
-  // exchanges) is chosen and its owner drops it; lane j keeps the blocks of rounds
-  // j, j + 4, ... (-1 once the lists run dry).
-  int mine[4] = {-1, -1, -1, -1};
-#pragma unroll
-  for (int t = 0; t < K; ++t) {
-    if (t >= kk) break;
-    const uint64_t head = lst[0];
-    const uint64_t w = group_max_u64(head);
-    const bool pop = w != 0 && head == w;   // keys are unique: one lane of the group holds w
-#pragma unroll
-    for (int i = 0; i < K - 1; ++i) lst[i] = pop ? lst[i + 1] : lst[i];
-    lst[K - 1] = pop ? 0 : lst[K - 1];
-    const int blk = w == 0 ? -1 : (int)(0xFFFFFFFFu - (uint32_t)(w & 0xFFFFFFFFu));
-    mine[t >> 2] = (t & 3) == j ? blk : mine[t >> 2];
+  __syncthreads();   // the tiles are free: they hold the groups' lists from here
+
+  // f32 scores, each to its group's list as a key (in no particular order)
+  uint64_t* keys = reinterpret_cast<uint64_t*>(ring) + wid * 16 * kPerGroup;   // [group][kPerGroup]
+  int* cnt = cnt_s[wid];
+  int* best16 = best_s[wid];   // [group][16] the k* best blocks
+  if (lane < 16) cnt[lane] = 0;
+  *reinterpret_cast<int4*>(best16 + 4 * lane) = make_int4(kNoBlock, kNoBlock, kNoBlock, kNoBlock);
+  wave_sync();
+  if (total > kFlat) {
+    over = live;
+    total = 0;
   }
-  // stored ascending with -1 in unused slots: each chosen block goes to its rank among the
-  // group's (at most 16) chosen blocks, which every lane of the group gathers
-  int all[16];
+  const int sub = lane & 7;
+  // four rounds of eight entries at a time, all their rows in flight together
+  constexpr int PF = 4;
+#pragma unroll 1
+  for (int e0 = 0; e0 < total; e0 += 8 * PF) {
+    uint32_t x[PF];
+    f32x4 qv[PF][NCH], kv[PF][NCH];
+    float n[PF];
 #pragma unroll
-  for (int s4 = 0; s4 < 4; ++s4) {
-    int g4[4];
-    group_gather(mine[s4], g4);
+    for (int i = 0; i < PF; ++i) x[i] = flat[min(e0 + 8 * i + (lane >> 3), total - 1)];
 #pragma unroll
-    for (int q4 = 0; q4 < 4; ++q4) all[4 * q4 + s4] = g4[q4];
-  }
-  int nsel = 0;
+    for (int i = 0; i < PF; ++i) {
+      const int grp = (int)((x[i] >> 20) & 15), blk = (int)(x[i] & 0xFFFFF);
 #pragma unroll
-  for (int e = 0; e < 16; ++e) nsel += all[e] >= 0;
-  const int p = p0 + 16 * wid + r;
-  if (p < ngroups) {
-    int* out = sel + ((size_t)bh * ngroups + p) * kk;
-#pragma unroll
-    for (int s4 = 0; s4 < 4; ++s4) {
-      const int v = mine[s4];
-      if (v >= 0) {
-        int rank = 0;
-#pragma unroll
-        for (int e = 0; e < 16; ++e) rank += (all[e] >= 0) & (all[e] < v);
-        out[rank] = v;
+      for (int c = 0; c < NCH; ++c) {
+        qv[i][c] = *reinterpret_cast<const f32x4*>(qb + (size_t)(p0 + grp) * HD + 32 * c + 4 * sub);
+        kv[i][c] = *reinterpret_cast<const f32x4*>(kc + (size_t)blk * HD + 32 * c + 4 * sub);
       }
-      const int slot = j + 4 * s4;
-      if (slot < kk && slot >= nsel) out[slot] = -1;
+      n[i] = check ? kn[blk] : 0.f;
     }
+#pragma unroll
+    for (int i = 0; i < PF; ++i) {
+      const float s = dot8<NCH>(qv[i], kv[i]);
+      if (sub == 0 && e0 + 8 * i + (lane >> 3) < total && s > kNegInf && n[i] <= 0.f) {
+        const int grp = (int)((x[i] >> 20) & 15), blk = (int)(x[i] & 0xFFFFF);
+        const int at = atomicAdd(&cnt[grp], 1);
+        if (at < kPerGroup) keys[grp * kPerGroup + at] = make_key(s, blk);
+      }
+    }
+  }
+  wave_sync();
+  // each key's rank within its group: lane j takes the group's keys j, j + 4, ..., eight at
+  // a time, and compares them with all of the group's keys
+  const int n = cnt[r];
+  over = over || (live && n > kPerGroup);
+  const int nr = over ? 0 : n;
+  const uint64_t* list = keys + r * kPerGroup;
+  for (int b0 = 0; __builtin_amdgcn_ballot_w64(b0 < nr); b0 += 32) {
+    uint64_t own8[8];
+    int rank[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int y = b0 + 4 * i + j;
+      own8[i] = y < nr ? list[y] : 0;
+      rank[i] = 0;
+    }
+#pragma unroll 4
+    for (int y = 0; y < nr; ++y) {
+      const uint64_t k2 = list[y];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) rank[i] += k2 > own8[i];
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if (own8[i] != 0 && rank[i] < kk) best16[16 * r + rank[i]] = (int)(0xFFFFFFFFu - (uint32_t)own8[i]);
+  }
+  wave_sync();
+  // stored ascending with -1 in unused slots: lane j places the blocks of ranks 4j .. 4j + 3
+  int* out = sel + ((size_t)bh * ngroups + p0) * kk;
+  {
+    int4 v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = reinterpret_cast<const int4*>(best16 + 16 * r)[i];
+    const int all[16] = {v[0].x, v[0].y, v[0].z, v[0].w, v[1].x, v[1].y, v[1].z, v[1].w,
+                         v[2].x, v[2].y, v[2].z, v[2].w, v[3].x, v[3].y, v[3].z, v[3].w};
+    const int4 m4 = reinterpret_cast<const int4*>(best16 + 16 * r)[j];
+    const int mine[4] = {m4.x, m4.y, m4.z, m4.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      int pos = 0;
+#pragma unroll
+      for (int t = 0; t < 16; ++t) pos += all[t] < mine[i];
+      const bool used = mine[i] != kNoBlock;
+      if (!used) pos = 4 * j + i;   // ranks are filled from 0: the slots past them stay unused
+      if (live && !over && pos < kk) out[r * kk + pos] = used ? mine[i] : -1;
+    }
+  }
+
+  // groups left over: every block scored in f32, eight at a time; the k* best keys sit in
+  // lanes 0 .. kk - 1 in descending order
+  uint64_t todo = __builtin_amdgcn_ballot_w64(over) & 0xFFFFull;
+  while (todo) {
+    const int rr = __builtin_ctzll(todo);
+    todo &= todo - 1;
+    const float* qr = qb + (size_t)(p0 + rr) * HD;
+    const int lo = ((p0 + rr) >> (lgm - lgg)) << lgb;
+    const bool zero = __builtin_amdgcn_ballot_w64(lane < HD && qr[lane < HD ? lane : 0] != 0.f) == 0;
+    f32x4 qv[NCH];
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) qv[c] = *reinterpret_cast<const f32x4*>(qr + 32 * c + 4 * sub);
+    uint64_t best = 0;
+    for (int b0 = 0; b0 < nblk; b0 += 64) {
+      // lane's key of block b0 + lane
+      uint64_t key = 0;
+      for (int i = 0; i < 8; ++i) {
+        const int blk = b0 + 8 * i + (lane >> 3), bc = min(blk, nblk - 1);
+        f32x4 kv[NCH];
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) kv[c] = *reinterpret_cast<const f32x4*>(kc + (size_t)bc * HD + 32 * c + 4 * sub);
+        const float s = dot8<NCH>(qv, kv);
+        const float n0 = kn[bc];
+        const bool ok = blk < nblk && !(mask_own && (uint32_t)(blk - lo) < (1u << lgb)) && n0 == n0 && s > kNegInf;
+        const uint64_t k8 = ok ? make_key(s, blk) : 0;
+        const uint64_t got = __shfl(k8, 8 * sub);   // of block b0 + 8 i + sub
+        key = (lane >> 3) == i ? got : key;
+      }
+      for (;;) {
+        const uint64_t kth = __shfl(best, kk - 1);
+        const uint64_t hits = __builtin_amdgcn_ballot_w64(key > kth);
+        if (!hits) break;
+        const int src = __builtin_ctzll(hits);
+        const uint64_t x = __shfl(key, src);
+        const int pos = __popcll(__builtin_amdgcn_ballot_w64(lane < kk && best > x));
+        const uint64_t up = __shfl_up(best, 1);
+        best = lane < pos ? best : lane == pos ? x : up;
+        if (lane == src) key = 0;
+      }
+      // a zero query scores every block 0: the first k* eligible blocks are the result
+      if (zero && __shfl(best, kk - 1) != 0) break;
+    }
+    const bool has = lane < kk && best != 0;
+    const int blk = (int)(0xFFFFFFFFu - (uint32_t)best);
+    int rank = 0, n = 0;
+    for (int t = 0; t < kk; ++t) {
+      const uint64_t o = __shfl(best, t);
+      rank += o != 0 && (int)(0xFFFFFFFFu - (uint32_t)o) < blk;
+      n += o != 0;
+    }
+    if (has) out[rr * kk + rank] = blk;
+    if (lane >= n && lane < kk) out[rr * kk + lane] = -1;
   }
 }
 
 template <typename T, int HD, int K>
 hipError_t select_k(const Dims& D, const void* q, const uint8_t* valid, const float* kcmp, const uint8_t* cvalid,
                     int* sel, float* qpool, bool given, uint16_t* kplanes, hipStream_t st) {
-  const long long total = (long long)D.B * D.H * (D.N / D.g) * HD;
-  if (!given)
-    hipLaunchKernelGGL((pool_q_kernel<T, HD>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, (const T*)q,
-                       valid, D.H, D.N, D.g, total, qpool);
-  const long long n8 = D.cmp_rows() * HD / 8;
-  bf16_t* kp = reinterpret_cast<bf16_t*>(kplanes);
-  hipLaunchKernelGGL(split3_kernel, dim3((unsigned)((n8 + 255) / 256)), dim3(256), 0, st, kcmp, n8, kp,
-                     kp + D.cmp_rows() * HD, kp + 2 * D.cmp_rows() * HD);
-  const int ngroups = D.N / D.g;
-  dim3 grid((ngroups + 16 * kWaves - 1) / (16 * kWaves), D.B * D.H);
-  const int R = D.ls / D.l;
-  if (R == 1)
-    hipLaunchKernelGGL((select_kernel<T, HD, K, 1>), grid, dim3(kWaves * 64), 0, st, (const float*)qpool, (const bf16_t*)kp,
-                       cvalid, D.H, D.N, D.l, D.ls, D.m, D.g, D.mask_own, D.k, sel);
-  else if (R == 2)
-    hipLaunchKernelGGL((select_kernel<T, HD, K, 2>), grid, dim3(kWaves * 64), 0, st, (const float*)qpool, (const bf16_t*)kp,
-                       cvalid, D.H, D.N, D.l, D.ls, D.m, D.g, D.mask_own, D.k, sel);
-  else
-    hipLaunchKernelGGL((select_kernel<T, HD, K, 4>), grid, dim3(kWaves * 64), 0, st, (const float*)qpool, (const bf16_t*)kp,
-                       cvalid, D.H, D.N, D.l, D.ls, D.m, D.g, D.mask_own, D.k, sel);
+  auto lg = [](int x) { return __builtin_ctz((unsigned)x); };
+  const int ngroups = D.N / D.g, nblk = D.N / D.ls, R = D.ls / D.l;
+  const long long blocks = (long long)D.B * D.H * nblk;
+  const long long pool_n8 = given ? 0 : (long long)D.B * D.H * ngroups * (HD / 8);
+  const long long pool_blocks = (pool_n8 + 255) / 256, key_blocks = (blocks * (HD / 8) + 255) / 256;
+  // workspace of 6 bytes per compressed key and channel: unit vectors (2), norms, and for
+  // R > 1 the summed keys (4, 256-byte aligned)
+  uint16_t* kunit = kplanes;
+  float* knorm = reinterpret_cast<float*>(kplanes + blocks * HD);
+  const size_t norm_end = (2 * (size_t)blocks * HD + 4 * (size_t)D.B * D.H * (nblk > 4096 / HD ? nblk : 4096 / HD) + 255) & ~(size_t)255;
+  float* ksum = R > 1 ? reinterpret_cast<float*>(reinterpret_cast<char*>(kplanes) + norm_end) : nullptr;
+  hipLaunchKernelGGL((select_prep_kernel<T, HD>), dim3((unsigned)(pool_blocks + key_blocks)), dim3(256), 0, st,
+                     (const T*)q, valid, D.H, lg(D.N), lg(D.g), pool_n8, (int)pool_blocks, qpool, kcmp, cvalid,
+                     lg(nblk), lg(R), blocks, ksum, kunit, knorm);
+  const dim3 grid((ngroups + 16 * kWaves - 1) / (16 * kWaves), D.B * D.H);
+  hipLaunchKernelGGL((select_kernel<HD, K>), grid, dim3(kWaves * 64), 0, st, (const float*)qpool, R > 1 ? ksum : kcmp,
+                     (const uint16_t*)kunit, (const float*)knorm, D.N, lg(D.ls), lg(D.m), lg(D.g), D.mask_own,
+                     (int)(R == 1), D.k, sel);
   return hipGetLastError();
 }
 
