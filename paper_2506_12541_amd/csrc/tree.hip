@@ -8,13 +8,14 @@
 // is free to use any partition that preserves them.
 //
 // GPU plan. The three per-axis orderings of every cloud are produced once by a stable
-// LSD radix sort (8-bit digits). Each node then keeps, for every axis, its points
-// sorted on that axis, stored at the node's own slot range. A split reads the extremes
-// of each axis at the ends of the lists and the median at position ceil(n/2)-1 of the
-// split axis; every list is then stably partitioned by "key <= median key", which keeps
-// all three lists sorted in both children. Levels with nodes larger than 1024 slots run
-// as three small kernels per level over all nodes; the last ten levels run inside one
-// workgroup per 1024-slot node, entirely in LDS.
+// LSD radix sort (8-bit digits): clouds of up to 16384 points by one workgroup per cloud and
+// axis in LDS, larger ones by two kernels per digit over all clouds. Each node then keeps,
+// for every axis, its points sorted on that axis, stored at the node's own slot range. A
+// split reads the extremes of each axis at the ends of the lists and the median at position
+// ceil(n/2)-1 of the split axis; every list is then stably partitioned by "key <= median
+// key", which keeps all three lists sorted in both children. Levels with nodes larger than
+// 16384 slots run as two kernels per level, levels down to 2048 as one (a workgroup per node
+// and axis); the last ten levels run inside one workgroup per 1024-slot node, in LDS.
 #include <map>
 #include <mutex>
 
@@ -32,6 +33,8 @@ constexpr int kScanChunk = 8192;                      // counts scanned per work
 constexpr int kLocalScanTiles = 64;   // up to this many tiles, each scatter workgroup scans itself
 constexpr int kPartTile = 2048;                       // slots per partition workgroup
 constexpr int kBottom = 1024;                         // node size finished in LDS
+constexpr int kCloudSort = 16384;                     // points of a cloud sorted in LDS
+constexpr int kLevelNode = 16384;                     // node size partitioned by one workgroup per axis
 
 __device__ __forceinline__ uint32_t ordered_key(float x) {
   x = x + 0.0f;  // -0.0 -> +0.0
@@ -63,16 +66,16 @@ __device__ int block_exclusive_scan(int v, int* lds_tmp, int* total) {
   }
   if (lane == 63) lds_tmp[wid] = x;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    int run = 0;
-    for (int w = 0; w < nw; ++w) { int t = lds_tmp[w]; lds_tmp[w] = run; run += t; }
-    lds_tmp[nw] = run;
+  int before = 0, all = 0;   // every thread adds the waves' totals (independent reads)
+#pragma unroll
+  for (int w = 0; w < 16; ++w) {
+    const int t = w < nw ? lds_tmp[w] : 0;
+    before += w < wid ? t : 0;
+    all += t;
   }
+  if (total) *total = all;
   __syncthreads();
-  int res = x - v + lds_tmp[wid];
-  if (total) *total = lds_tmp[nw];
-  __syncthreads();
-  return res;
+  return x - v + before;
 }
 
 // ---- radix sort of (key, point) per axis; grid.y = axis ----
@@ -127,14 +130,26 @@ __global__ void __launch_bounds__(1024) sort_scan_kernel(uint32_t* hist, int tot
   const int n = min(kScanChunk, total - chunk * kScanChunk);
   constexpr int per = kScanChunk / 1024;
   const int s = threadIdx.x * per;
+  static_assert(per == 8, "two 16-byte loads per thread");
+  int c[per] = {};   // n is a multiple of 256: a thread's entries all exist or none does
+  if (s < n) {
+    *reinterpret_cast<int4*>(&c[0]) = reinterpret_cast<const int4*>(H + s)[0];
+    *reinterpret_cast<int4*>(&c[4]) = reinterpret_cast<const int4*>(H + s)[1];
+  }
   int sum = 0;
-  for (int i = s; i < s + per && i < n; ++i) sum += (int)H[i];
+#pragma unroll
+  for (int i = 0; i < per; ++i) sum += c[i];
   int all = 0;
   int run = block_exclusive_scan(sum, tmp, &all);
-  for (int i = s; i < s + per && i < n; ++i) {
-    int t = (int)H[i];
-    H[i] = (uint32_t)run;
+#pragma unroll
+  for (int i = 0; i < per; ++i) {
+    const int t = c[i];
+    c[i] = run;
     run += t;
+  }
+  if (s < n) {
+    reinterpret_cast<int4*>(H + s)[0] = *reinterpret_cast<const int4*>(&c[0]);
+    reinterpret_cast<int4*>(H + s)[1] = *reinterpret_cast<const int4*>(&c[4]);
   }
   // a single chunk is already the whole scan: its offset is 0 (no chunk-total pass runs)
   if (threadIdx.x == 0) sums[(size_t)blockIdx.y * nchunks + chunk] = nchunks == 1 ? 0u : (uint32_t)all;
@@ -156,81 +171,210 @@ __global__ void __launch_bounds__(1024) sort_scan_sums_kernel(uint32_t* sums, in
   }
 }
 
-// Stable scatter of one tile. Items are taken in index order, 256 per round: within a
-// round, an item's rank among equal digits comes from eight ballots (lanes of its wave
-// with the same digit and a lower lane id) plus the counts of the lower waves and of the
-// earlier rounds, all kept per digit in LDS. sums == nullptr (few tiles): the tile's output
-// starts come from the unscanned counts, each thread summing its digit's row of tiles and
-// the workgroup scanning those totals over the digits (no scan launches).
+// Ranks of a wave's items among its items of the same digit, in index order (rounds of 64):
+// eight ballots per round find the lanes with the same digit, cnt holds the digit's items of
+// the earlier rounds (this wave's counts, cleared by the caller). Returns the rank; lanes
+// that are not ok take no part.
+__device__ __forceinline__ uint32_t wave_digit_rank(uint32_t d, bool ok, uint32_t* cnt) {
+  const uint64_t all = __builtin_amdgcn_ballot_w64(ok);
+  uint32_t lo = (uint32_t)all, hi = (uint32_t)(all >> 32);   // lanes with the same digit
+#pragma unroll
+  for (int bit = 0; bit < 8; ++bit) {
+    const uint32_t on = 0u - ((d >> bit) & 1u);
+    const uint64_t bb = __builtin_amdgcn_ballot_w64(on != 0u);
+    lo &= ~((uint32_t)bb ^ on);
+    hi &= ~((uint32_t)(bb >> 32) ^ on);
+  }
+  const uint32_t rank = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0));
+  const uint32_t before = cnt[d];
+  wave_sync();   // every lane has read its digit's count
+  if (ok && rank == 0) cnt[d] = before + (uint32_t)(__popc(lo) + __popc(hi));
+  wave_sync();
+  return before + rank;
+}
+
+// Sum of the first `upto` of 16 consecutive counts (read together, no dependent loads).
+__device__ __forceinline__ int prefix16(const int* c, int from, int upto) {
+  int v[16], s = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) *reinterpret_cast<int4*>(&v[4 * i]) = reinterpret_cast<const int4*>(c)[i];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) s += i >= from && i < upto ? v[i] : 0;
+  return s;
+}
+
+// ---- clouds of up to 1024 ITEMS points: one workgroup sorts one axis of one cloud in LDS ----
+// Bound by the latency of its barriers and LDS round trips (about 3 us per digit at 4096
+// points). Wave w owns items [64 ITEMS w, 64 ITEMS (w + 1)) in rounds of 64 in index order:
+// an item's rank among its wave's items of the same digit comes from eight ballots per round
+// and a per-wave digit count in LDS; the counts are then scanned over digits and waves. It
+// replaces a launch that forms keys, two per digit (and one more digit for the cloud index)
+// and one that lays out the lists: 16 clouds of 3586 points 87 -> 16 us.
+constexpr int kCloudThreads = 1024;
+template <int ITEMS>
+__global__ void __launch_bounds__(kCloudThreads) cloud_sort_kernel(const float* __restrict__ pts, int dim, int n_real,
+                                                                   int n_pad, size_t slots, int* __restrict__ lists) {
+  constexpr int NW = kCloudThreads / 64;
+  __shared__ uint32_t key_s[kCloudThreads * ITEMS];
+  __shared__ uint16_t val_s[kCloudThreads * ITEMS];
+  __shared__ uint32_t cnt[NW][kRadix];
+  __shared__ uint32_t wave_tot[kRadix / 64];
+  const int b = blockIdx.x, a = blockIdx.y, t = threadIdx.x, lane = t & 63, wid = t >> 6;
+  const int first = wid * 64 * ITEMS + lane;
+  uint32_t k[ITEMS];
+  uint32_t v[ITEMS];   // item, and from the ranking on its rank << 16
+#pragma unroll
+  for (int it = 0; it < ITEMS; ++it) {
+    const int i = first + 64 * it;   // items past n_real sort last (and, equal keys, in index order)
+    k[it] = i < n_real ? ordered_key(coord(pts, dim, b * n_real + i, a)) : 0xFFFFFFFFu;
+    v[it] = (uint32_t)i;
+  }
+  for (int pass = 0; pass < 4; ++pass) {
+#pragma unroll
+    for (int i = 0; i < NW * kRadix / kCloudThreads; ++i) (&cnt[0][0])[t + kCloudThreads * i] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
+      const uint32_t d = (k[it] >> (8 * pass)) & 255u;
+      v[it] |= wave_digit_rank(d, true, cnt[wid]) << 16;
+    }
+    __syncthreads();
+    // counts -> output starts: over the digits, then over the waves of each digit
+    uint32_t tot = 0;
+    if (t < kRadix) {
+#pragma unroll
+      for (int w = 0; w < NW; ++w) tot += cnt[w][t];
+    }
+    uint32_t inc = tot;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t y = __shfl_up(inc, o, 64);
+      inc += lane >= o ? y : 0u;
+    }
+    if (t < kRadix && lane == 63) wave_tot[wid] = inc;
+    __syncthreads();
+    if (t < kRadix) {
+      uint32_t run = inc - tot;
+#pragma unroll
+      for (int w = 0; w < kRadix / 64; ++w) run += w < wid ? wave_tot[w] : 0u;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        const uint32_t c = cnt[w][t];
+        cnt[w][t] = run;
+        run += c;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
+      const uint32_t dst = cnt[wid][(k[it] >> (8 * pass)) & 255u] + (v[it] >> 16);
+      key_s[dst] = k[it];
+      val_s[dst] = (uint16_t)(v[it] & 0xFFFFu);
+    }
+    __syncthreads();
+    if (pass < 3) {
+#pragma unroll
+      for (int it = 0; it < ITEMS; ++it) {
+        k[it] = key_s[first + 64 * it];
+        v[it] = val_s[first + 64 * it];
+      }
+    }
+  }
+  int* out = lists + a * slots + (size_t)b * n_pad;
+  for (int i = t; i < n_pad; i += kCloudThreads) out[i] = i < n_real ? b * n_real + (int)val_s[i] : -1;
+}
+
+// Stable scatter of one tile: each wave ranks its contiguous quarter of the tile by itself (no
+// barrier between rounds), the counts are scanned over digits and waves, the tile is sorted
+// in LDS and then written, so that a digit's items leave as one run. sums == nullptr (few
+// tiles): the tile's output starts come from the unscanned counts, each thread summing its
+// digit's row of tiles and the workgroup scanning those totals over the digits (no scan
+// launches). Bound by latency at 65536 keys x 3 axes (rounds of 256 with three barriers and
+// stores straight from the ranks took 15.6 instead of 12 us) and by its scattered
+// writes at 8.4 M pairs (99 instead of 64 us).
 __global__ void __launch_bounds__(kSortThreads) sort_scatter_kernel(const uint32_t* keys, const uint32_t* vals,
                                                                     uint32_t* keys_out, uint32_t* vals_out,
                                                                     int m, int pass, int n_real, int ntiles,
                                                                     const uint32_t* hist, const uint32_t* sums,
                                                                     int nchunks) {
-  __shared__ uint32_t run[kRadix];            // items of each digit in earlier rounds
-  __shared__ uint32_t base[kRadix];           // output start of each digit for this tile
-  __shared__ uint32_t wc[kSortThreads / 64][kRadix];   // this round's count per wave and digit
+  constexpr int NW = kSortThreads / 64;
+  static_assert(kSortThreads == kRadix, "one thread per digit");
+  __shared__ uint32_t cnt[NW][kRadix];        // a wave's items per digit, then its first place in the tile
+  __shared__ uint32_t to_out[kRadix];         // output position less place in the sorted tile
+  __shared__ uint32_t key_s[kSortTile], val_s[kSortTile];
+  __shared__ int tmp[NW];
   const int a = blockIdx.y, tile = blockIdx.x, t = threadIdx.x;
   const int lane = t & 63, wid = t >> 6;
-  const uint32_t* K = keys + (size_t)a * m;
-  const uint32_t* V = vals + (size_t)a * m;
+  const int i0 = tile * kSortTile, n = min(kSortTile, m - i0);
+  const int first = wid * 64 * kSortItems + lane;
+  const uint32_t* K = keys + (size_t)a * m + i0;
+  const uint32_t* V = vals + (size_t)a * m + i0;
+  uint32_t k[kSortItems], v[kSortItems], pos[kSortItems];
+#pragma unroll
+  for (int it = 0; it < kSortItems; ++it) {
+    const int i = first + 64 * it;
+    k[it] = i < n ? K[i] : 0u;
+    v[it] = i < n ? V[i] : 0u;
+  }
+  uint32_t base;   // output start of digit t for this tile
   if (sums == nullptr) {
-    __shared__ int tmp[kSortThreads / 64 + 1];
     const uint32_t* hd = hist + ((size_t)a * kRadix + t) * ntiles;   // digit t's counts over tiles
     uint32_t tot = 0, part = 0;
+#pragma unroll 8
     for (int tl = 0; tl < ntiles; ++tl) {
       const uint32_t c = hd[tl];
       tot += c;
       part += tl < tile ? c : 0u;
     }
-    base[t] = (uint32_t)block_exclusive_scan((int)tot, tmp, nullptr) + part;
-    run[t] = 0;
+    base = (uint32_t)block_exclusive_scan((int)tot, tmp, nullptr) + part;
   } else {
     const size_t e = (size_t)t * ntiles + tile;   // digit-major entry of (digit t, this tile)
-    base[t] = hist[(size_t)a * kRadix * ntiles + e] + sums[(size_t)a * nchunks + e / kScanChunk];
-    run[t] = 0;
+    base = hist[(size_t)a * kRadix * ntiles + e] + sums[(size_t)a * nchunks + e / kScanChunk];
   }
-  const uint64_t below = (1ull << lane) - 1ull;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) cnt[w][t] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int it = 0; it < kSortItems; ++it) {
+    const bool ok = first + 64 * it < n;
+    const uint32_t d = ok ? sort_digit(k[it], v[it], pass, n_real) : 0u;
+    pos[it] = wave_digit_rank(d, ok, cnt[wid]);
+  }
+  __syncthreads();
+  uint32_t c[NW], tot = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    c[w] = cnt[w][t];
+    tot += c[w];
+  }
+  uint32_t run = (uint32_t)block_exclusive_scan((int)tot, tmp, nullptr);
+  to_out[t] = base - run;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    cnt[w][t] = run;
+    run += c[w];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int it = 0; it < kSortItems; ++it) {
+    if (first + 64 * it < n) {
+      const uint32_t p = cnt[wid][sort_digit(k[it], v[it], pass, n_real)] + pos[it];
+      key_s[p] = k[it];
+      val_s[p] = v[it];
+    }
+  }
+  __syncthreads();
   uint32_t* KO = keys_out + (size_t)a * m;
   uint32_t* VO = vals_out + (size_t)a * m;
-  // the tile's items are loaded before the rounds (one round trip instead of one per round)
-  uint32_t kk[kSortItems], vv[kSortItems];
 #pragma unroll
   for (int it = 0; it < kSortItems; ++it) {
-    const int i = tile * kSortTile + it * kSortThreads + t;
-    kk[it] = i < m ? K[i] : 0u;
-    vv[it] = i < m ? V[i] : 0u;
-  }
-#pragma unroll
-  for (int it = 0; it < kSortItems; ++it) {
-    const int i = tile * kSortTile + it * kSortThreads + t;
-    const bool ok = i < m;
-    const uint32_t k = kk[it], v = vv[it];
-    const uint32_t d = ok ? sort_digit(k, v, pass, n_real) : 0u;
-#pragma unroll
-    for (int w = 0; w < kSortThreads / 64; ++w) wc[w][t] = 0;
-    uint64_t peers = __builtin_amdgcn_ballot_w64(ok);
-#pragma unroll
-    for (int bit = 0; bit < 8; ++bit) {
-      const bool on = (d >> bit) & 1u;
-      const uint64_t bb = __builtin_amdgcn_ballot_w64(on);
-      peers &= on ? bb : ~bb;
+    const int p = it * kSortThreads + t;
+    if (p < n) {
+      const uint32_t kk = key_s[p], vv = val_s[p];
+      const uint32_t o = to_out[sort_digit(kk, vv, pass, n_real)] + (uint32_t)p;
+      KO[o] = kk;
+      VO[o] = vv;
     }
-    const uint32_t rank = (uint32_t)__builtin_popcountll(peers & below);
-    __syncthreads();   // wc cleared; run and base written
-    if (ok && rank == 0) wc[wid][d] = (uint32_t)__builtin_popcountll(peers);
-    __syncthreads();
-    if (ok) {
-      uint32_t off = base[d] + run[d] + rank;
-      for (int w = 0; w < wid; ++w) off += wc[w][d];
-      KO[off] = k;
-      VO[off] = v;
-    }
-    __syncthreads();   // every item of the round has read run
-    uint32_t add = 0;
-#pragma unroll
-    for (int w = 0; w < kSortThreads / 64; ++w) add += wc[w][t];
-    run[t] += add;
   }
 }
 
@@ -381,123 +525,133 @@ __global__ void __launch_bounds__(256) part_scatter_kernel(const float* pts, int
   }
 }
 
+// One level for nodes of capacity 1024 ITEMS: one workgroup forms a node's split and
+// partitions one of its axis lists (16 waves, each a contiguous run of the list in rounds of
+// 64; ranks from ballots, then the waves' totals). Latency-bound: three dependent global
+// round trips; as two launches (counts, then scatter, in tiles of 2048 slots) a level took
+// 12 us instead of 5 at 65536 slots with 2048-slot nodes, and as much with 16384-slot nodes.
+template <int ITEMS>
+__global__ void __launch_bounds__(1024) level_kernel(const float* __restrict__ pts, int dim, int n_real, int n_pad,
+                                                     int log2_npad, int log2c, size_t slots,
+                                                     const int* __restrict__ lists, int* __restrict__ lists_out) {
+  __shared__ __attribute__((aligned(16))) int wcnt[16];
+  const int nd = blockIdx.x, a = blockIdx.y, lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const size_t start = a * slots + ((size_t)nd << log2c);
+  const int first = wid * 64 * ITEMS + lane;
+  int g[ITEMS];
+#pragma unroll
+  for (int it = 0; it < ITEMS; ++it) g[it] = lists[start + first + 64 * it];
+  const NodeSplit sp = node_split_block(pts, dim, n_real, n_pad, log2_npad, log2c, slots, lists, nd);
+  const uint64_t below = (1ull << lane) - 1ull;
+  bool left[ITEMS];
+#pragma unroll
+  for (int it = 0; it < ITEMS; ++it)
+    left[it] = first + 64 * it < sp.cnt && goes_left(pts, dim, g[it], sp);
+  int rank[ITEMS], n = 0;
+#pragma unroll
+  for (int it = 0; it < ITEMS; ++it) {
+    const uint64_t m = __builtin_amdgcn_ballot_w64(left[it]);
+    rank[it] = n + __builtin_popcountll(m & below);
+    n += __builtin_popcountll(m);
+  }
+  if (lane == 0) wcnt[wid] = n;
+  __syncthreads();
+  const int before = prefix16(wcnt, 0, wid);
+#pragma unroll
+  for (int it = 0; it < ITEMS; ++it) {
+    const int pos = first + 64 * it, lr = before + rank[it];
+    if (pos < sp.cnt) lists_out[start + (left[it] ? lr : (1 << (log2c - 1)) + pos - lr)] = g[it];
+  }
+}
+
 // ---- the last levels of one node of capacity T <= 1024, in LDS ----
-// kBottomThreads threads per node, each owning a contiguous run of kBottomItems list slots
-constexpr int kBottomThreads = 1024;
-constexpr int kBottomItems = 3 * kBottom / kBottomThreads;
-__global__ void __launch_bounds__(kBottomThreads) bottom_kernel(const float* pts, int dim, int n_real, int n_pad,
-                                                     int log2_npad, int log2t, int nodes, const int* lists,
-                                                     int* perm) {
-  __shared__ float4 el[3 * kBottom];   // (x, y, z, point as int bits) per list slot
-  __shared__ int sub_axis[kBottom / 2];
-  __shared__ int sub_idx[kBottom / 2];
-  __shared__ float sub_med[kBottom / 2];
-  __shared__ int tmp[kBottomThreads / 64 + 1];
+// Thread r owns slot r of the three axis lists and forms the split of its slot's node by
+// itself (six list ends and the median from LDS, one address per node). Ranks of the
+// left-going points are ballots within the wave; nodes of more than 64 slots add the counts
+// of the node's earlier waves (two barriers per level), smaller ones stay inside a wave (no
+// barrier). Bound by the latency of about five LDS round trips per level. (Three list slots
+// per thread of one concatenated list, splits formed by a thread per node and a workgroup
+// scan took 37 instead of 18 us.)
+__global__ void __launch_bounds__(kBottom) bottom_kernel(const float* __restrict__ pts, int dim, int n_real, int n_pad,
+                                                         int log2_npad, int log2t, int nodes,
+                                                         const int* __restrict__ lists, int* __restrict__ perm) {
+  __shared__ float4 el[3][kBottom];   // (x, y, z, point as int bits) per list slot
+  __shared__ __attribute__((aligned(16))) int wcnt[3][16];
   const int T = 1 << log2t;
   const int nd = blockIdx.x;
   const size_t slots = (size_t)nodes << log2t;
   const size_t start = (size_t)nd << log2t;
   const int per_cloud = n_pad >> log2t;
-  const int node_in_cloud = nd % per_cloud;
   const int cloud = nd / per_cloud;
-  const int cnt0 = node_count(n_real, log2_npad, log2t, node_in_cloud);
-  for (int i = threadIdx.x; i < 3 * T; i += kBottomThreads) {
-    int a = i / T, r = i % T;
-    float4 e = make_float4(0.f, 0.f, 0.f, __int_as_float(-1));
-    if (r < cnt0) {
-      int g = lists[a * slots + start + r];
-      e = make_float4(coord(pts, dim, g, 0), coord(pts, dim, g, 1), coord(pts, dim, g, 2), __int_as_float(g));
-    }
-    el[i] = e;
+  const int r = threadIdx.x, lane = r & 63, wid = r >> 6;
+  const uint64_t below = (1ull << lane) - 1ull;
+  int cnt = r < T ? node_count(n_real, log2_npad, log2t, nd % per_cloud) : 0;   // points of the slot's node
+  if (r < cnt) {
+    int g[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) g[a] = lists[a * slots + start + r];
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+      el[a][r] = make_float4(coord(pts, dim, g[a], 0), coord(pts, dim, g[a], 1), coord(pts, dim, g[a], 2),
+                             __int_as_float(g[a]));
   }
   __syncthreads();
-  const int items = (3 * T + kBottomThreads - 1) / kBottomThreads;  // <= kBottomItems
   for (int log2c = log2t; log2c >= 1; --log2c) {
-    const int C = 1 << log2c;
-    const int nsub = T >> log2c;
-    // split of every sub-node
-    for (int s = threadIdx.x; s < nsub; s += kBottomThreads) {
-      int cnt = node_count(n_real, log2_npad, log2c, node_in_cloud * nsub + s);
-      int axis = 0, midx = -1;
-      float med = 0.f;
-      if (cnt > 0) {
-        double best = -1.0;
-        for (int a = 0; a < 3; ++a) {
-          float4 lo = el[a * T + s * C], hi = el[a * T + s * C + cnt - 1];
-          float l = a == 0 ? lo.x : (a == 1 ? lo.y : lo.z);
-          float h = a == 0 ? hi.x : (a == 1 ? hi.y : hi.z);
-          double sp = (double)h - (double)l;
-          if (sp > best) { best = sp; axis = a; }
-        }
-        float4 me = el[axis * T + s * C + (cnt + 1) / 2 - 1];
-        med = axis == 0 ? me.x : (axis == 1 ? me.y : me.z);
-        midx = __float_as_int(me.w);
-      }
-      sub_axis[s] = axis;
-      sub_idx[s] = midx;
-      sub_med[s] = med;
-    }
-    __syncthreads();
-    float4 e[kBottomItems];
-    int f[kBottomItems];
-    int mine = 0;
+    const int C = 1 << log2c, s0 = r & ~(C - 1), pos = r & (C - 1);
+    const bool here = pos < cnt;
+    float4 e[3];
+    int lr[3];
+    bool left[3] = {false, false, false};
+    if (here) {
+      const int hi = s0 + cnt - 1, mid = s0 + (cnt + 1) / 2 - 1;
+      const float sx0 = el[0][s0].x, sx1 = el[0][hi].x, sy0 = el[1][s0].y, sy1 = el[1][hi].y, sz0 = el[2][s0].z,
+                  sz1 = el[2][hi].z;
 #pragma unroll
-    for (int it = 0; it < kBottomItems; ++it) {
-      f[it] = -1;
-      int i = threadIdx.x * items + it;
-      if (it < items && i < 3 * T) {
-        e[it] = el[i];
-        int g = __float_as_int(e[it].w);
-        if (g >= 0) {
-          int s = (i % T) >> log2c;
-          int ax = sub_axis[s];
-          float c = ax == 0 ? e[it].x : (ax == 1 ? e[it].y : e[it].z);
-          f[it] = (c < sub_med[s] || (c == sub_med[s] && g <= sub_idx[s])) ? 1 : 0;
-          mine += f[it];
-        }
-      }
-    }
-    // exclusive prefix of left flags over the concatenated lists; sub-node starts are
-    // aligned to C, so the prefix at a sub-node start is subtracted below
-    int pre = block_exclusive_scan(mine, tmp, nullptr);
-    __shared__ int start_pref[3 * kBottom / 2];
-    // record prefix at each sub-node start: the thread owning index (s*C) writes it
-    {
-      int run = pre;
+      for (int a = 0; a < 3; ++a) e[a] = el[a][r];
+      const double d0 = (double)sx1 - (double)sx0, d1 = (double)sy1 - (double)sy0, d2 = (double)sz1 - (double)sz0;
+      double best = -1.0;
+      int axis = 0;
+      if (d0 > best) best = d0;
+      if (d1 > best) { best = d1; axis = 1; }
+      if (d2 > best) axis = 2;
+      const float4 me = el[axis][mid];
+      const float med = axis == 0 ? me.x : (axis == 1 ? me.y : me.z);
+      const int midx = __float_as_int(me.w);
 #pragma unroll
-      for (int it = 0; it < kBottomItems; ++it) {
-        int i = threadIdx.x * items + it;
-        if (it < items && i < 3 * T) {
-          if ((i & (C - 1)) == 0) start_pref[i >> log2c] = run;
-          run += f[it] > 0 ? 1 : 0;
-        }
+      for (int a = 0; a < 3; ++a) {
+        const float c = axis == 0 ? e[a].x : (axis == 1 ? e[a].y : e[a].z);
+        left[a] = c < med || (c == med && __float_as_int(e[a].w) <= midx);
       }
     }
-    __syncthreads();
-    // all old values are in registers: rewrite the lists in place
-    for (int i = threadIdx.x; i < 3 * T; i += kBottomThreads) el[i] = make_float4(0.f, 0.f, 0.f, __int_as_float(-1));
-    __syncthreads();
-    {
-      int run = pre;
+    uint64_t m[3];
 #pragma unroll
-      for (int it = 0; it < kBottomItems; ++it) {
-        int i = threadIdx.x * items + it;
-        if (it < items && i < 3 * T && f[it] >= 0) {
-          int sub_start = i & ~(C - 1);
-          int lr = run - start_pref[i >> log2c];   // left flags before i in this sub-node
-          int pos = i - sub_start;
-          int dst = f[it] ? sub_start + lr : sub_start + C / 2 + (pos - lr);
-          el[dst] = e[it];
-        }
-        if (it < items && i < 3 * T) run += f[it] > 0 ? 1 : 0;
+    for (int a = 0; a < 3; ++a) m[a] = __builtin_amdgcn_ballot_w64(left[a]);
+    if (C > 64) {
+      if (lane == 0) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) wcnt[a][wid] = __builtin_popcountll(m[a]);
       }
+      __syncthreads();   // every wave has read its slots and its node's split
+#pragma unroll
+      for (int a = 0; a < 3; ++a)
+        lr[a] = prefix16(wcnt[a], s0 >> 6, wid) + __builtin_popcountll(m[a] & below);
+    } else {
+      const uint64_t seg = (C == 64 ? ~0ull : ((1ull << C) - 1ull) << (lane & ~(C - 1))) & below;
+#pragma unroll
+      for (int a = 0; a < 3; ++a) lr[a] = __builtin_popcountll(m[a] & seg);
+      wave_sync();
     }
-    __syncthreads();
+    if (here) {
+#pragma unroll
+      for (int a = 0; a < 3; ++a) el[a][left[a] ? s0 + lr[a] : s0 + C / 2 + pos - lr[a]] = e[a];
+    }
+    if (C > 64)
+      __syncthreads();
+    else
+      wave_sync();
+    cnt = pos < C / 2 ? (cnt + 1) >> 1 : cnt >> 1;
   }
-  for (int r = threadIdx.x; r < T; r += kBottomThreads) {
-    int g = __float_as_int(el[r].w);
-    perm[start + r] = g >= 0 ? g - cloud * n_real : -1;
-  }
+  if (r < T) perm[start + r] = cnt > 0 ? __float_as_int(el[0][r].w) - cloud * n_real : -1;
 }
 
 // ---- row gather / scatter between point order and ball order ----
@@ -647,37 +801,62 @@ hipError_t launch_build_tree(const float* pts, int64_t n_real, int dim, int64_t 
   NodeSplit* splits = (NodeSplit*)take(sizeof(NodeSplit) * (slots / 2 + 1));
   int* tilecnt = (int*)take(4 * 3 * (slots / kPartTile + 1));
 
-  hipLaunchKernelGGL(sort_init_kernel, dim3((unsigned)((m + 255) / 256), 3), dim3(256), 0, st, pts, dim,
-                     (int)m, ka, va);
-  int passes = 4;
-  for (int bits = 0; (1 << bits) < batch; bits += 8) ++passes;
-  const bool local_scan = ntiles <= kLocalScanTiles;
-  for (int pass = 0; pass < passes; ++pass) {
-    hipLaunchKernelGGL(sort_hist_kernel, dim3(ntiles, 3), dim3(kSortThreads), 0, st, ka, va, (int)m, pass,
-                       (int)n_real, ntiles, hist);
-    if (!local_scan) {
-      hipLaunchKernelGGL(sort_scan_kernel, dim3(nchunks, 3), dim3(1024), 0, st, hist, kRadix * ntiles, sums);
-      if (nchunks > 1) hipLaunchKernelGGL(sort_scan_sums_kernel, dim3(1, 3), dim3(1024), 0, st, sums, nchunks);
-    }
-    hipLaunchKernelGGL(sort_scatter_kernel, dim3(ntiles, 3), dim3(kSortThreads), 0, st, ka, va, kb, vb,
-                       (int)m, pass, (int)n_real, ntiles, hist, local_scan ? nullptr : sums, nchunks);
-    std::swap(ka, kb);
-    std::swap(va, vb);
-  }
-  hipLaunchKernelGGL(lists_init_kernel, dim3((unsigned)((slots + 255) / 256), 3), dim3(256), 0, st, va,
-                     (int)m, (int)n_real, (int)n_pad, batch, la);
   const int log2_npad = ilog2(n_pad);
   const int log2t = log2_npad < 10 ? log2_npad : 10;
+  // small clouds: one workgroup per cloud and axis (its padding slots are written by the same
+  // workgroup, hence the bound on n_pad)
+  if (n_real <= kCloudSort && n_pad <= 2 * kCloudSort) {
+    const dim3 grid((unsigned)batch, 3);
+    const int np = (int)n_pad, nr = (int)n_real;
+    if (n_real <= 1024)
+      hipLaunchKernelGGL(cloud_sort_kernel<1>, grid, dim3(kCloudThreads), 0, st, pts, dim, nr, np, slots, la);
+    else if (n_real <= 2048)
+      hipLaunchKernelGGL(cloud_sort_kernel<2>, grid, dim3(kCloudThreads), 0, st, pts, dim, nr, np, slots, la);
+    else if (n_real <= 4096)
+      hipLaunchKernelGGL(cloud_sort_kernel<4>, grid, dim3(kCloudThreads), 0, st, pts, dim, nr, np, slots, la);
+    else if (n_real <= 8192)
+      hipLaunchKernelGGL(cloud_sort_kernel<8>, grid, dim3(kCloudThreads), 0, st, pts, dim, nr, np, slots, la);
+    else
+      hipLaunchKernelGGL(cloud_sort_kernel<16>, grid, dim3(kCloudThreads), 0, st, pts, dim, nr, np, slots, la);
+  } else {
+    hipLaunchKernelGGL(sort_init_kernel, dim3((unsigned)((m + 255) / 256), 3), dim3(256), 0, st, pts, dim,
+                       (int)m, ka, va);
+    int passes = 4;
+    for (int bits = 0; (1 << bits) < batch; bits += 8) ++passes;
+    const bool local_scan = ntiles <= kLocalScanTiles;
+    for (int pass = 0; pass < passes; ++pass) {
+      hipLaunchKernelGGL(sort_hist_kernel, dim3(ntiles, 3), dim3(kSortThreads), 0, st, ka, va, (int)m, pass,
+                         (int)n_real, ntiles, hist);
+      if (!local_scan) {
+        hipLaunchKernelGGL(sort_scan_kernel, dim3(nchunks, 3), dim3(1024), 0, st, hist, kRadix * ntiles, sums);
+        if (nchunks > 1) hipLaunchKernelGGL(sort_scan_sums_kernel, dim3(1, 3), dim3(1024), 0, st, sums, nchunks);
+      }
+      hipLaunchKernelGGL(sort_scatter_kernel, dim3(ntiles, 3), dim3(kSortThreads), 0, st, ka, va, kb, vb,
+                         (int)m, pass, (int)n_real, ntiles, hist, local_scan ? nullptr : sums, nchunks);
+      std::swap(ka, kb);
+      std::swap(va, vb);
+    }
+    hipLaunchKernelGGL(lists_init_kernel, dim3((unsigned)((slots + 255) / 256), 3), dim3(256), 0, st, va,
+                       (int)m, (int)n_real, (int)n_pad, batch, la);
+  }
   for (int log2c = log2_npad; log2c > log2t; --log2c) {
-    const int tiles = (int)(slots / kPartTile);
-    hipLaunchKernelGGL(part_count_kernel, dim3(tiles, 3), dim3(256), 0, st, pts, dim, (int)n_real, (int)n_pad,
-                       log2_npad, log2c, la, splits, tiles, tilecnt);
-    hipLaunchKernelGGL(part_scatter_kernel, dim3(tiles, 3), dim3(256), 0, st, pts, dim, log2c, la, lb,
-                       splits, tiles, tilecnt);
+    if ((1 << log2c) > kLevelNode) {
+      const int tiles = (int)(slots / kPartTile);
+      hipLaunchKernelGGL(part_count_kernel, dim3(tiles, 3), dim3(256), 0, st, pts, dim, (int)n_real, (int)n_pad,
+                         log2_npad, log2c, la, splits, tiles, tilecnt);
+      hipLaunchKernelGGL(part_scatter_kernel, dim3(tiles, 3), dim3(256), 0, st, pts, dim, log2c, la, lb,
+                         splits, tiles, tilecnt);
+    } else {
+      const dim3 grid((unsigned)(slots >> log2c), 3);
+      auto kern = log2c == 11 ? level_kernel<2> : log2c == 12 ? level_kernel<4> : log2c == 13 ? level_kernel<8>
+                                                                                             : level_kernel<16>;
+      hipLaunchKernelGGL(kern, grid, dim3(1024), 0, st, pts, dim, (int)n_real, (int)n_pad, log2_npad, log2c, slots, la,
+                         lb);
+    }
     std::swap(la, lb);
   }
   const int nodes = (int)(slots >> log2t);
-  hipLaunchKernelGGL(bottom_kernel, dim3(nodes), dim3(kBottomThreads), 0, st, pts, dim, (int)n_real, (int)n_pad,
+  hipLaunchKernelGGL(bottom_kernel, dim3(nodes), dim3(kBottom), 0, st, pts, dim, (int)n_real, (int)n_pad,
                      log2_npad, log2t, nodes, la, perm);
   return hipGetLastError();
 }

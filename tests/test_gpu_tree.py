@@ -44,6 +44,22 @@ def test_tree_edge_cases(batch, n_real, n_pad, dim):
         assert np.array_equal(got[b], build_ball_tree(pts[b], n_pad))
 
 
+@pytest.mark.parametrize("batch,n_real,n_pad", [
+    (2, 1024, 1024), (2, 1025, 2048), (1, 2049, 8192), (2, 4096, 4096), (1, 4097, 32768), (2, 8192, 8192),
+    (1, 16384, 16384), (1, 9000, 65536), (1, 16385, 32768), (1, 20000, 32768),
+])
+def test_tree_sort_and_level_edges(batch, n_real, n_pad):
+    """Each size of the in-LDS sort, the largest cloud of each and one point more, and node
+    sizes on both sides of the one-workgroup partition; a third of the points share coordinates."""
+    rng = np.random.default_rng(n_real)
+    pts = rng.standard_normal((batch, n_real, 3)).astype(np.float32)
+    pts[:, ::3] = np.round(pts[:, ::3] * 2) / 2
+    print(f"tree sort edge B={batch} n_real={n_real} n_pad={n_pad}", flush=True)
+    got = _gpu_perm(pts, n_pad)
+    for b in range(batch):
+        assert np.array_equal(got[b], build_ball_tree(pts[b], n_pad))
+
+
 def test_permute_and_unpermute():
     cfg = CONFIGS[2]
     pts = make_points(cfg)
