@@ -844,7 +844,7 @@ bsa::GemmOut out_heads(const BlockDims& X, void* p0, void* p1, void* p2) {
 // and out2 (the remaining rows, when out2 is given).
 hipError_t wgrad(const BlockDims& X, const bsa::GemmMat& a, const bsa::GemmMat& b, int Mo, int No, float* part,
                  float* out, float* out2, int split_row, hipStream_t st) {
-  const int S = bsa::gemm_splits(Mo, No, X.M);
+  const int S = bsa::wgrad_splits(Mo, No, X.M, wgrad_part_bytes(X));
   bsa::GemmOut o{};
   o.epi = bsa::kEpiPart;
   o.out = part;

@@ -22,14 +22,14 @@ constexpr float kNormEps = 1e-6f;
 //     rows (the weight gradients dW = dY^T X over tokens); tiles are staged as 64 rows x 128
 //     and read with transposing LDS reads (ds_read_b64_tr_b16).
 // Accumulator lane L holds C[m0 + L % 16][n0 + 4 (L / 16) + e], e = 0..3 (the B fragment
-// is the first MFMA operand), so each lane stores 4 consecutive columns.
+// is the first MFMA operand).
 
 // 16-byte chunk swizzle of a staged tile row: 4 or 8 chunks per row (row-fragment reads
 // of 16 consecutive rows on distinct banks) or 16 and more chunks per row (transposing
 // reads of 8 consecutive rows, chunk pairs on distinct banks).
 template <int COLS>
 __device__ __forceinline__ int tile_swz(int x) {
-  return COLS == 32 ? ((x >> 2) & 3) : COLS == 64 ? (x & 7) : 2 * (x & 7);
+  return COLS == 32 ? ((x >> 1) & 3) : COLS == 64 ? (x & 7) : 2 * (x & 7);
 }
 
 // Staging of ROWS x COLS tiles of a logical row-major operand into LDS by the NW waves of
@@ -110,6 +110,9 @@ __device__ __forceinline__ void vm_wait() {
   __builtin_amdgcn_s_waitcnt((V & 15) | ((V >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
+// Wait for this wave's LDS reads; no LDS access moves across it.
+__device__ __forceinline__ void lgkm_drain() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
 // LDS byte addresses of the two transposing reads that give lane (p = L % 16, j = L / 16)
 // the operand X[k0 + 4j + i][m0 + p] (i = 0..3) and X[k0 + 16 + 4j + i][m0 + p] of a
 // [64][COLS] tile X: within each 16-lane group, ds_read_b64_tr_b16 hands lane l element
@@ -150,13 +153,30 @@ __device__ __forceinline__ void tr_frags4(const bf16_t* t, int k0, int m0, int l
     f[i] = __builtin_bit_cast(bf16x8, make_uint4(r[2 * i].x, r[2 * i].y, r[2 * i + 1].x, r[2 * i + 1].y));
 }
 
+// 1 / (1 + exp(-x)): the hardware reciprocal and one Newton step (within an ulp of the divided
+// value, at a third of the division's instructions); exp is kept finite.
+__device__ __forceinline__ float sigmoid(float x) {
+  const float y = 1.0f + __expf(fminf(-x, 80.0f));
+  const float r = __builtin_amdgcn_rcpf(y);
+  return fmaf(fmaf(-y, r, 1.0f), r, r);
+}
+
 struct GemmArgs {
   GemmMat a, b;
   int ntn;        // column tiles
   int kt_per;     // contraction tiles per split
   GemmOut o;
   long long split_stride;   // elements between the partial products of two splits
+  bool stream_out;          // SwiGLU forward: stores that bypass the caches
 };
+
+// Rows of a wave's tile that pass through LDS at a time in the epilogue: as many as fit the
+// four arrays of the first two stages.
+constexpr int epi_rows(int array_bytes, int tmw, int tnw, int nw) {
+  int rp = tmw;
+  while (rp > 16 && 4 * (array_bytes / (rp * tnw * 4)) < nw) rp /= 2;
+  return rp;
+}
 
 // Workgroup tile BM x BN of WM x WN waves (wave tile BM / WM x BN / WN in 16 x 16
 // accumulator tiles); contraction tiles of BK in a ring of NS LDS stages, NS - 1 of them in
@@ -166,7 +186,7 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_kernel(GemmArgs g) {
   constexpr int NW = WM * WN;
   constexpr int TMW = BM / WM, TNW = BN / WN;
   constexpr int FI = TMW / 16, FJ = TNW / 16;
-  static_assert(FI % 4 == 0 && FJ % 4 == 0, "wave tile");
+  static_assert(!TR || (FI % 4 == 0 && FJ % 4 == 0), "wave tile");
   static_assert(NS >= 2 && NS <= 4 && (BK == 32 || BK == 64), "pipeline");
   constexpr int AE = BM * BK, BE = BN * BK;
   __shared__ __attribute__((aligned(1024))) bf16_t as0[AE], bs0[BE], as1[AE], bs1[BE];
@@ -205,130 +225,228 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_kernel(GemmArgs g) {
 #pragma unroll
     for (int j = 0; j < FJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  auto compute = [&](const bf16_t* as, const bf16_t* bs) {
+  bf16x8 af[FI], bfr[FJ];
+  auto read = [&](const bf16_t* as, const bf16_t* bs, int ks) {
+    if (!TR) {
 #pragma unroll
-    for (int ks = 0; ks < BK / 32; ++ks) {
-      bf16x8 af[FI], bfr[FJ];
-      if (!TR) {
+      for (int i = 0; i < FI; ++i) af[i] = frag_row<BK>(as, wm * TMW + 16 * i + (lane & 15), 4 * ks + (lane >> 4));
 #pragma unroll
-        for (int i = 0; i < FI; ++i) af[i] = frag_row<BK>(as, wm * TMW + 16 * i + (lane & 15), 4 * ks + (lane >> 4));
+      for (int j = 0; j < FJ; ++j) bfr[j] = frag_row<BK>(bs, wn * TNW + 16 * j + (lane & 15), 4 * ks + (lane >> 4));
+    } else {
 #pragma unroll
-        for (int j = 0; j < FJ; ++j) bfr[j] = frag_row<BK>(bs, wn * TNW + 16 * j + (lane & 15), 4 * ks + (lane >> 4));
-      } else {
+      for (int i = 0; i < FI; i += 4)
+        tr_frags4<BM>(as, 32 * ks, wm * TMW + 16 * i, lane, *reinterpret_cast<bf16x8(*)[4]>(&af[i]));
 #pragma unroll
-        for (int i = 0; i < FI; i += 4)
-          tr_frags4<BM>(as, 32 * ks, wm * TMW + 16 * i, lane, *reinterpret_cast<bf16x8(*)[4]>(&af[i]));
-#pragma unroll
-        for (int j = 0; j < FJ; j += 4)
-          tr_frags4<BN>(bs, 32 * ks, wn * TNW + 16 * j, lane, *reinterpret_cast<bf16x8(*)[4]>(&bfr[j]));
-      }
-#pragma unroll
-      for (int i = 0; i < FI; ++i)
-#pragma unroll
-        for (int j = 0; j < FJ; ++j) acc[i][j] = mma(bfr[j], af[i], acc[i][j]);
+      for (int j = 0; j < FJ; j += 4)
+        tr_frags4<BN>(bs, 32 * ks, wn * TNW + 16 * j, lane, *reinterpret_cast<bf16x8(*)[4]>(&bfr[j]));
     }
+  };
+  auto multiply = [&]() {
+#pragma unroll
+    for (int i = 0; i < FI; ++i)
+#pragma unroll
+      for (int j = 0; j < FJ; ++j) acc[i][j] = mma(bfr[j], af[i], acc[i][j]);
   };
 
 #pragma unroll
   for (int s = 0; s < NS - 1; ++s)
     if (kt0 + s < kt1) issue(kt0 + s, s);
-  for (int kt = kt0; kt < kt1; kt += NS) {
+  if constexpr (NW == 8) {
+    // Two waves share a SIMD; the second four waves run one phase behind the first four, so
+    // that one wave of each SIMD multiplies while the other reads its fragments from LDS
+    // (reads of both, then products of both, left each pipe idle half of the time). Phases
+    // end with a barrier; wave group 0 reads tile t in phase 2t and multiplies in 2t + 1,
+    // group 1 one phase later. Stage (t - 1) % NS is last read in phase 2t - 1, so tile
+    // t + NS - 1 may be loaded into it from phase 2t on (both groups: as they read tile t);
+    // tile t + 1 is first read in phase 2t + 2, so every wave waits for its part of it before
+    // the barrier that ends phase 2t + 1.
+    static_assert(BK == 32 && NS == 4, "one fragment depth per phase");
+    const int n = kt1 - kt0, grp = wid >> 2;
+    auto landed = [&](int t) {   // tile t + 1, with at most tiles t + 2 and t + 3 in flight
+      if (t + 3 < n)
+        vm_wait<2 * PER>();
+      else if (t + 2 < n)
+        vm_wait<PER>();
+      else
+        vm_drain();
+    };
+    landed(-1);
+    lds_barrier();
+    if (grp == 1) lds_barrier();
+    for (int t0 = 0; t0 < n; t0 += NS) {
 #pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      const int t = kt + s;
-      if (t < kt1) {
-        // tile t has landed once at most the NS - 2 tiles issued after it are in flight
-        if (t + NS - 2 < kt1)
-          vm_wait<(NS - 2) * PER>();
-        else
-          vm_drain();
-        lds_barrier();     // every wave's loads of tile t are visible; stage s - 1 is free
-        if (t + NS - 1 < kt1) issue(t + NS - 1, (s + NS - 1) % NS);
-        compute(AS[s], BS[s]);
+      for (int s = 0; s < NS; ++s) {
+        const int t = t0 + s;
+        if (t < n) {
+          if (t + NS - 1 < n) issue(kt0 + t + NS - 1, (s + NS - 1) % NS);
+          read(AS[s], BS[s], 0);
+          lgkm_drain();
+          if (grp == 1) landed(t);
+          lds_barrier();
+          __builtin_amdgcn_s_setprio(1);
+          multiply();
+          __builtin_amdgcn_s_setprio(0);
+          if (grp == 0) landed(t);
+          lds_barrier();
+        }
+      }
+    }
+    if (grp == 0) lds_barrier();
+  } else {
+    for (int kt = kt0; kt < kt1; kt += NS) {
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        const int t = kt + s;
+        if (t < kt1) {
+          // tile t has landed once at most the NS - 2 tiles issued after it are in flight
+          if (t + NS - 2 < kt1)
+            vm_wait<(NS - 2) * PER>();
+          else
+            vm_drain();
+          lds_barrier();     // every wave's loads of tile t are visible; stage s - 1 is free
+          if (t + NS - 1 < kt1) issue(t + NS - 1, (s + NS - 1) % NS);
+#pragma unroll
+          for (int ks = 0; ks < BK / 32; ++ks) {
+            read(AS[s], BS[s], ks);
+            multiply();
+          }
+        }
       }
     }
   }
 
+  // Epilogue. The accumulators go through LDS (the stages are free by then), RP rows of the
+  // wave's tile at a time in f32, so that every global access is a run of whole 128-byte
+  // lines: a lane stores 8 consecutive columns (4 of f32 outputs). Storing 4 columns of 16
+  // rows straight from the accumulators left 32-byte pieces: at 65536 rows, C = 512, F = 2048
+  // the SwiGLU forward took 477 instead of 402 us, its backward 497 instead of 340, the Q/K/V
+  // product 174 instead of 140. (Without any epilogue the same products take 209, 122 and 90 us:
+  // the writes are HBM-bound and the workgroups of a round write together.) 16-byte chunk c of row x sits at c ^ (x mod 16) (mod 8 for
+  // 32-column tiles): rows written and rows read spread over the banks.
+  constexpr int AB = 2 * (AE < BE ? AE : BE);                          // bytes used of a stage array
+  constexpr int RP = epi_rows(AB, TMW, TNW, NW);
+  constexpr int WPA = AB / (RP * TNW * 4);                             // waves per stage array
+  static_assert(WPA >= 1 && 4 * WPA >= NW && RP % 16 == 0, "epilogue regions");
   const GemmOut& o = g.o;
   const int r = lane & 15, jq = lane >> 4;
-  auto pack4 = [](float a0, float a1, float a2, float a3) {
-    return make_uint2((uint32_t)f2bf(a0) | ((uint32_t)f2bf(a1) << 16), (uint32_t)f2bf(a2) | ((uint32_t)f2bf(a3) << 16));
+  constexpr int SM = TNW >= 64 ? 15 : 7;
+  lds_barrier();   // every wave has read the last tile
+  bf16_t* const arr = wid / WPA == 0 ? as0 : wid / WPA == 1 ? bs0 : wid / WPA == 2 ? as1 : bs1;
+  float* const reg = reinterpret_cast<float*>(arr) + (wid % WPA) * RP * TNW;
+  auto at = [&](int row, int chunk) { return reinterpret_cast<f32x4*>(reg + row * TNW + 4 * (chunk ^ (row & SM))); };
+  auto row8 = [&](int row, int col, float (&v)[8]) {   // 8 consecutive columns of a row
+    const f32x4 x = *at(row, col / 4), y = *at(row, col / 4 + 1);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      v[e] = x[e];
+      v[4 + e] = y[e];
+    }
   };
-  if (o.epi == kEpiSwigluFwd) {
-    // B rows interleaved in groups of TNW (TNW / 2 rows of W_1, then the same rows of
-    // W_3; launch_cast_w13 with gemm_wave_cols): the wave's column tiles j and j + FJ / 2
-    // hold u and w of the same hidden units f
-    const int F = o.ffn;
 #pragma unroll
-    for (int i = 0; i < FI; ++i) {
-      const long long m = m0 + wm * TMW + 16 * i + r;
+  for (int i0 = 0; i0 < FI; i0 += RP / 16) {
 #pragma unroll
-      for (int j = 0; j < FJ / 2; ++j) {
-        const int f = ((int)n0 + wn * TNW) / 2 + 16 * j + 4 * jq;
-        float u[4], w[4], a[4];
+    for (int i = 0; i < RP / 16; ++i)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          u[e] = bf2f(f2bf(acc[i][j][e]));
-          w[e] = bf2f(f2bf(acc[i][j + FJ / 2][e]));
-          a[e] = u[e] / (1.0f + __expf(-u[e])) * w[e];
-        }
-        bf16_t* uw = reinterpret_cast<bf16_t*>(o.out) + m * 2 * F + f;
-        *reinterpret_cast<uint2*>(uw) = pack4(u[0], u[1], u[2], u[3]);
-        *reinterpret_cast<uint2*>(uw + F) = pack4(w[0], w[1], w[2], w[3]);
-        *reinterpret_cast<uint2*>(reinterpret_cast<bf16_t*>(o.out2) + m * F + f) = pack4(a[0], a[1], a[2], a[3]);
+      for (int j = 0; j < FJ; ++j) *at(16 * i + r, 4 * j + jq) = acc[i0 + i][j];
+    wave_sync();
+    const long long mw = m0 + wm * TMW + 16 * i0;
+    if (o.epi == kEpiF32 || o.epi == kEpiPart) {
+      constexpr int LPR = TNW / 4, RPI = 64 / LPR;
+      const int c = lane % LPR;
+      float* const dst = reinterpret_cast<float*>(o.out) + (o.epi == kEpiPart ? blockIdx.y * g.split_stride : 0) + n0 +
+                         wn * TNW + 4 * c;
+      const float* const res = o.epi == kEpiF32 && o.res ? o.res + n0 + wn * TNW + 4 * c : nullptr;
+#pragma unroll 8
+      for (int x0 = 0; x0 < RP; x0 += RPI) {
+        const int x = x0 + lane / LPR;
+        f32x4 v = *at(x, c);
+        if (res) v += *reinterpret_cast<const f32x4*>(res + (mw + x) * o.ldr);
+        *reinterpret_cast<f32x4*>(dst + (mw + x) * o.ldc) = v;
       }
-    }
-    return;
-  }
+    } else if (o.epi == kEpiSwigluFwd) {
+      // B rows interleaved in groups of TNW (TNW / 2 rows of W_1, then the same rows of
+      // W_3; launch_cast_w13 with gemm_wave_cols): columns c and c + TNW / 2 hold u and w of
+      // the same hidden unit
+      constexpr int LPR = TNW / 16, RPI = 64 / LPR;
+      const int c = 8 * (lane % LPR), F = o.ffn;
+      const long long f = (n0 + wn * TNW) / 2 + c;
+#pragma unroll 2
+      for (int x0 = 0; x0 < RP; x0 += RPI) {
+        const int x = x0 + lane / LPR;
+        float u[8], w[8], av[8];
+        row8(x, c, u);
+        row8(x, TNW / 2 + c, w);
 #pragma unroll
-  for (int i = 0; i < FI; ++i) {
-    const long long m = m0 + wm * TMW + 16 * i + r;
-#pragma unroll
-    for (int j = 0; j < FJ; ++j) {
-      const int n = (int)n0 + wn * TNW + 16 * j + 4 * jq;
-      f32x4 v = acc[i][j];
-      if (o.epi == kEpiF32 || o.epi == kEpiPart) {
-        float* dst = reinterpret_cast<float*>(o.out) + (o.epi == kEpiPart ? blockIdx.y * g.split_stride : 0) +
-                     m * o.ldc + n;
-        if (o.epi == kEpiF32 && o.res) {
-          const float4 rv = *reinterpret_cast<const float4*>(o.res + m * o.ldr + n);
-          v[0] += rv.x;
-          v[1] += rv.y;
-          v[2] += rv.z;
-          v[3] += rv.w;
+        for (int e = 0; e < 8; ++e) {
+          u[e] = bf2f(f2bf(u[e]));
+          w[e] = bf2f(f2bf(w[e]));
+          av[e] = u[e] * sigmoid(u[e]) * w[e];
         }
-        *reinterpret_cast<float4*>(dst) = make_float4(v[0], v[1], v[2], v[3]);
-      } else if (o.epi == kEpiSwigluBwd) {
-        // v = da for hidden units n .. n + 3; u, w from the forward pass (bf16 [M, 2F])
+        bf16x8* const up = reinterpret_cast<bf16x8*>(reinterpret_cast<bf16_t*>(o.out) + (mw + x) * 2 * F + f);
+        bf16x8* const wp = reinterpret_cast<bf16x8*>(reinterpret_cast<bf16_t*>(o.out) + (mw + x) * 2 * F + F + f);
+        bf16x8* const ap = reinterpret_cast<bf16x8*>(reinterpret_cast<bf16_t*>(o.out2) + (mw + x) * F + f);
+        if (g.stream_out) {
+          asm volatile("" ::: "memory");   // keeps the two branches' stores from being merged
+          __builtin_nontemporal_store(make_chunk<bf16_t>(u), up);
+          __builtin_nontemporal_store(make_chunk<bf16_t>(w), wp);
+          __builtin_nontemporal_store(make_chunk<bf16_t>(av), ap);
+          asm volatile("" ::: "memory");
+        } else {
+          *up = make_chunk<bf16_t>(u);
+          *wp = make_chunk<bf16_t>(w);
+          *ap = make_chunk<bf16_t>(av);
+        }
+      }
+    } else {
+      constexpr int LPR = TNW / 8, RPI = 64 / LPR;
+      const int c = 8 * (lane % LPR), n = (int)n0 + wn * TNW + c;
+      if (o.epi == kEpiSwigluBwd) {
+        // v = da for hidden units n .. n + 7; u, w from the forward pass (bf16 [M, 2F])
         const int F = o.ffn;
-        const bf16_t* uwp = reinterpret_cast<const bf16_t*>(o.aux) + m * 2 * F + n;
-        const uint2 ub = *reinterpret_cast<const uint2*>(uwp), wb = *reinterpret_cast<const uint2*>(uwp + F);
-        const uint32_t uu[2] = {ub.x, ub.y}, ww[2] = {wb.x, wb.y};
-        float du[4], dw[4];
+#pragma unroll 2
+        for (int x0 = 0; x0 < RP; x0 += RPI) {
+          const int x = x0 + lane / LPR;
+          const bf16_t* const uwp = reinterpret_cast<const bf16_t*>(o.aux) + (mw + x) * 2 * F + n;
+          const bf16x8 ub = load_chunk(uwp), wb = load_chunk(uwp + F);
+          float v[8], du[8], dw[8];
+          row8(x, c, v);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float uf = __uint_as_float((uu[e >> 1] >> (16 * (e & 1))) << 16);
-          const float wf = __uint_as_float((ww[e >> 1] >> (16 * (e & 1))) << 16);
-          const float sg = 1.0f / (1.0f + __expf(-uf));
-          du[e] = v[e] * wf * sg * (1.0f + uf * (1.0f - sg));
-          dw[e] = v[e] * uf * sg;
+          for (int e = 0; e < 8; ++e) {
+            const float uf = (float)ub[e], wf = (float)wb[e], sg = sigmoid(uf);
+            du[e] = v[e] * wf * sg * (1.0f + uf * (1.0f - sg));
+            dw[e] = v[e] * uf * sg;
+          }
+          bf16_t* const dst = reinterpret_cast<bf16_t*>(o.out) + (mw + x) * 2 * F + n;
+          *reinterpret_cast<bf16x8*>(dst) = make_chunk<bf16_t>(du);
+          *reinterpret_cast<bf16x8*>(dst + F) = make_chunk<bf16_t>(dw);
         }
-        bf16_t* dst = reinterpret_cast<bf16_t*>(o.out) + m * 2 * F + n;
-        *reinterpret_cast<uint2*>(dst) = pack4(du[0], du[1], du[2], du[3]);
-        *reinterpret_cast<uint2*>(dst + F) = pack4(dw[0], dw[1], dw[2], dw[3]);
       } else {
-        bf16_t* dst;
-        if (o.epi == kEpiBf16) {
-          dst = reinterpret_cast<bf16_t*>(o.out) + m * o.ldc + n;
-        } else {   // kEpiHeads
-          const int p = n / o.part_cols, c = n - p * o.part_cols;
-          const long long b = m >> o.lgn, t = m & ((1LL << o.lgn) - 1);
-          const long long h = c >> o.lgd, dd = c & ((1 << o.lgd) - 1);
-          dst = reinterpret_cast<bf16_t*>(o.parts[p]) + ((((b * o.heads + h) << o.lgn) + t) << o.lgd) + dd;
+        // token rows, or [part][b][head][token][d]: eight columns lie in one head's row
+        int hp = 0;
+        long long coff = n;
+        if (o.epi == kEpiHeads) {
+          hp = n / o.part_cols;
+          const int cc = n - hp * o.part_cols;
+          coff = ((long long)(cc >> o.lgd) << (o.lgn + o.lgd)) + (cc & ((1 << o.lgd) - 1));
         }
-        *reinterpret_cast<uint2*>(dst) = pack4(v[0], v[1], v[2], v[3]);
+#pragma unroll 4
+        for (int x0 = 0; x0 < RP; x0 += RPI) {
+          const int x = x0 + lane / LPR;
+          const long long m = mw + x;
+          float v[8];
+          row8(x, c, v);
+          bf16_t* dst;
+          if (o.epi == kEpiBf16) {
+            dst = reinterpret_cast<bf16_t*>(o.out) + m * o.ldc + coff;
+          } else {
+            const long long b = m >> o.lgn, t = m & ((1LL << o.lgn) - 1);
+            dst = reinterpret_cast<bf16_t*>(o.parts[hp]) + ((b * o.heads) << (o.lgn + o.lgd)) + coff + (t << o.lgd);
+          }
+          *reinterpret_cast<bf16x8*>(dst) = make_chunk<bf16_t>(v);
+        }
       }
     }
+    wave_sync();
   }
 }
 
@@ -581,13 +699,22 @@ unsigned blocks_for(long long n, int per) { return (unsigned)((n + per - 1) / pe
 
 }  // namespace
 
-// 256 x 256 workgroup tiles of 8 waves (4 x 2, 64 x 128 each) where the shape allows and
-// gives at least 256 tiles (or splits the contraction), else 128 x 128 tiles of 4 waves
-// (64 x 64 each); contraction tiles of 64 in two stages. (Measured on the block's shapes:
-// 256 x 256 tiles of 4 x 2 waves ran fastest, ahead of 2 x 4 waves, 256 x 128 and
-// 128 x 256 tiles, and of 32-deep tiles in four stages.)
-int gemm_tile(int M, int N, bool split) {
-  return M % 256 == 0 && N % 256 == 0 && (split || (long long)(M / 256) * (N / 256) >= 256) ? 256 : 128;
+// Workgroup tile of a product: 256 x 256 (8 waves of 64 x 128, tiles of 32 along the
+// contraction in four stages) where the shape allows and gives at least 256 tiles; else 128 x
+// 128 (4 waves of 64 x 64, two workgroups per CU) if that gives at least 256 tiles; else 64 x
+// 64 (4 waves of 32 x 32, four stages: few workgroups, each bound by the latency of its
+// tiles). At 65536 rows 256 x 128 and 128 x 256 tiles of 4 waves, two workgroups per CU, took
+// 2.32-2.34 ms for the block's products instead of 2.18; at 1024 rows, C = 512, F = 2048 the
+// forward's four products take 40 us with 64 x 64 tiles instead of 66 with 128 x 128.
+int gemm_tile(int M, int N) {
+  if (M % 256 == 0 && N % 256 == 0 && (long long)(M / 256) * (N / 256) >= 256) return 256;
+  return (long long)(M / 128) * (N / 128) >= 256 ? 128 : 64;
+}
+
+// Tile of a weight gradient with `splits` splits of the contraction: 128 x 128 where 256 x 256
+// tiles and the base number of splits leave a quarter of the CUs or more without a workgroup.
+int wgrad_tile(int M, int N, long long K) {
+  return M % 256 == 0 && N % 256 == 0 && (long long)(M / 256) * (N / 256) * gemm_splits(M, N, K) >= 192 ? 256 : 128;
 }
 
 hipError_t launch_gemm(bool trans, const GemmMat& a, const GemmMat& b, int M, int N, long long K, int splits,
@@ -595,33 +722,51 @@ hipError_t launch_gemm(bool trans, const GemmMat& a, const GemmMat& b, int M, in
   if (M <= 0 || N <= 0 || K <= 0 || M % 128 || N % 128 || K % 64 || splits < 1 || (K / 64) % splits)
     return hipErrorInvalidValue;
   if (o.epi != kEpiPart && splits != 1) return hipErrorInvalidValue;
-  const int T = gemm_tile(M, N, trans);
-  GemmArgs g{a, b, N / T, (int)((K / 64) / splits), o, (long long)M * o.ldc};
+  const int T = trans ? wgrad_tile(M, N, K) : gemm_tile(M, N);
+  GemmArgs g{a, b, N / T, (int)((K / 64) / splits), o, (long long)M * o.ldc, false};
+  if (T == 256) g.kt_per *= 2;   // tiles of 32
+  // u, w and silu(u) w together larger than the last-level cache: storing them past the caches
+  // leaves those to the operands (65536 rows, F = 2048: 413 -> 348 us); smaller ones are
+  // better found there by the next product
+  g.stream_out = o.epi == kEpiSwigluFwd && 6LL * M * o.ffn >= (256LL << 20);
   const dim3 grid((unsigned)((M / T) * (N / T)), (unsigned)splits);
   if (T == 256) {
     if (trans)
-      gemm_kernel<true, 256, 256, 4, 2, 64, 2><<<grid, 512, 0, st>>>(g);
+      gemm_kernel<true, 256, 256, 4, 2, 32, 4><<<grid, 512, 0, st>>>(g);
     else
-      gemm_kernel<false, 256, 256, 4, 2, 64, 2><<<grid, 512, 0, st>>>(g);
+      gemm_kernel<false, 256, 256, 4, 2, 32, 4><<<grid, 512, 0, st>>>(g);
+  } else if (trans) {
+    gemm_kernel<true, 128, 128, 2, 2, 64, 2><<<grid, 256, 0, st>>>(g);
+  } else if (T == 128) {
+    gemm_kernel<false, 128, 128, 2, 2, 64, 2><<<grid, 256, 0, st>>>(g);
   } else {
-    if (trans)
-      gemm_kernel<true, 128, 128, 2, 2, 64, 2><<<grid, 256, 0, st>>>(g);
-    else
-      gemm_kernel<false, 128, 128, 2, 2, 64, 2><<<grid, 256, 0, st>>>(g);
+    gemm_kernel<false, 64, 64, 2, 2, 64, 4><<<grid, 256, 0, st>>>(g);
   }
   return hipGetLastError();
 }
 
-int gemm_wave_cols(int M, int N) { return gemm_tile(M, N, false) == 256 ? 128 : 64; }
+int gemm_wave_cols(int M, int N) { return gemm_tile(M, N) / 2; }
 
 int gemm_splits(int M, int N, long long K) {
-  const int T = gemm_tile(M, N, true);
+  const int T = M % 256 == 0 && N % 256 == 0 ? 256 : 128;
   const long long tiles = (long long)(M / T) * (N / T);
   const long long nkt = K / 64;
   int s = 1;
   // about one workgroup per CU (each split adds a partial product the sum reads back), at
   // least 16 contraction tiles per split
   while (tiles * s < 256 && nkt % (2 * s) == 0 && nkt / (2 * s) >= 16) s *= 2;
+  return s;
+}
+
+int wgrad_splits(int M, int N, long long K, size_t part_bytes) {
+  int s = gemm_splits(M, N, K);
+  if (wgrad_tile(M, N, K) == 256) return s;
+  // 128 x 128 tiles: up to two workgroups per CU, at least 8 contraction tiles per split, and
+  // partial products that fit the workspace
+  const long long tiles = (long long)(M / 128) * (N / 128), nkt = K / 64;
+  while (tiles * s < 512 && nkt % (2 * s) == 0 && nkt / (2 * s) >= 8 &&
+         sizeof(float) * (size_t)(2 * s) * M * N <= part_bytes)
+    s *= 2;
   return s;
 }
 

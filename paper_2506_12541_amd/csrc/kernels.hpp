@@ -218,7 +218,10 @@ struct GemmOut {
 // B [K, N]. M, N multiples of 128, K of 64; splits > 1 only with kEpiPart.
 hipError_t launch_gemm(bool trans, const GemmMat& a, const GemmMat& b, int M, int N, long long K, int splits,
                        const GemmOut& o, hipStream_t st);
+// Splits of a weight gradient's contraction: the base number (the workspace is sized for it)
+// and the number used, within part_bytes of partial products.
 int gemm_splits(int M, int N, long long K);
+int wgrad_splits(int M, int N, long long K, size_t part_bytes);
 hipError_t launch_rmsnorm_fwd(const float* x, const float* gain, const float* wg, long long rows, int C, uint16_t* xn,
                               float* rstd, float* gate, hipStream_t st);
 hipError_t launch_rmsnorm_bwd(const float* dxn, const float* x, const float* rstd, const float* gain, const float* dres,
