@@ -18,13 +18,15 @@
 //   2. The same scores plus the bound: blocks that reach the group's threshold (about
 //      1.15 k* of them; every block of the k* best is one) go to the wave's list.
 //   3. The listed blocks are scored with f32 products and sums and ranked within their
-//      group; the selected ones are ordered by block index.
+//      group; the selected ones are ordered by block index. Groups whose k*-th and next
+//      score are closer than those sums' error (about one in a thousand) are ranked again by
+//      float64 sums over the compressed keys, so the order is that of float64 throughout.
 // Error bound of a unit-vector score: f16 rounds each of the two operands by at most 2^-11
 // of its magnitude, so by Cauchy-Schwarz the score errs by at most 2^-10 (+ 2^-22); the
 // vectors are scaled by 2^7, which keeps what f16 cannot hold (below 2^-24, or below 2^-14
 // if subnormal numbers were flushed) under 2^-17; f32 sums and norms add under 2^-17.
 // kUnitErr is 1.1 * 2^-10. A group whose list overflows (e.g. all scores equal) is scanned
-// in f32 by its wave.
+// in float64 by its wave.
 // What bounds it: VALU issue (75 instructions per 64 blocks and 16 groups in both streams,
 // about 3000 per 16 groups for the ranking), and with few waves per SIMD the latency of each
 // tile. Measured with d = 64, r = 2, k* = 16 (in brackets: one stream of all compressed keys
@@ -55,6 +57,12 @@ __device__ __forceinline__ uint32_t ordered_bits(float x) {
   x = x + 0.0f;
   uint32_t u = __float_as_uint(x);
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+}
+
+// The score of a key.
+__device__ __forceinline__ float key_score(uint64_t key) {
+  const uint32_t b = (uint32_t)(key >> 32);
+  return __uint_as_float((b & 0x80000000u) ? (b & 0x7FFFFFFFu) : ~b);
 }
 
 __device__ __forceinline__ uint64_t make_key(float score, int blk) {
@@ -104,7 +112,7 @@ __device__ __forceinline__ float unit_scale(const float* x, int n, int& e, MaxF 
 // instead of 14 us at 65536 queries x 8 heads of 64). The others: every selection block's
 // compressed keys summed (ksum, not written for r = 1: kcmp holds them), as f16 unit vectors
 // and negated norms, HD / 8 threads per block; blocks without a real token get the norm NaN,
-// which no comparison passes, and (for r > 1) a sum of NaN. A head's norms are padded with
+// which no comparison passes. A head's norms are padded with
 // NaN to a whole tile of the selection kernel.
 template <typename T, int HD>
 __global__ void __launch_bounds__(256) select_prep_kernel(const T* __restrict__ q, const uint8_t* __restrict__ valid,
@@ -143,14 +151,17 @@ __global__ void __launch_bounds__(256) select_prep_kernel(const T* __restrict__ 
   if (i >= blocks * CPR) return;   // whole rows: 256 is a multiple of CPR
   const long long blk = i / CPR;   // (b*H + h) * nblk + block, nblk = 2^lgb
   const int r = 1 << lgr;
-  float a[8];
+  double sum[8];   // rounded once: within 2^-24 of the true sum, whatever cancels
 #pragma unroll
-  for (int e = 0; e < 8; ++e) a[e] = 0.f;
+  for (int e = 0; e < 8; ++e) sum[e] = 0.0;
   for (int k = 0; k < r; ++k) {
     const f32x8 v = load_chunk(kcmp + ((blk << lgr) + k) * HD + 8 * (i % CPR));
 #pragma unroll
-    for (int e = 0; e < 8; ++e) a[e] += v[e];
+    for (int e = 0; e < 8; ++e) sum[e] += (double)v[e];
   }
+  float a[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) a[e] = (float)sum[e];
   const uint8_t* cv = cvalid + ((long long)((uint32_t)(blk >> lgb) / (uint32_t)H) << (lgb + lgr)) +
                       ((blk & ((1LL << lgb) - 1)) << lgr);
   uint32_t any = 0;
@@ -175,7 +186,7 @@ __global__ void __launch_bounds__(256) select_prep_kernel(const T* __restrict__ 
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     u[e] = (_Float16)(ldexpf(a[e], -ex) * rn);
-    o[e] = any ? a[e] : __builtin_nanf("");
+    o[e] = a[e];
   }
   *reinterpret_cast<f16x8*>(kunit + 8 * i) = u;
   if (r > 1) *reinterpret_cast<f32x8*>(ksum + 8 * i) = o;
@@ -210,6 +221,23 @@ __device__ __forceinline__ float dot8(const f32x4 (&x)[NCH], const f32x4 (&y)[NC
 #pragma unroll
     for (int e = 0; e < 4; ++e) s = fmaf(x[c][e], y[c][e], s);
   return sum8(s);
+}
+
+// r times the score of a selection block in float64 from its r compressed keys, by eight lanes.
+template <int HD>
+__device__ __forceinline__ double score64(const float* __restrict__ q, const float* __restrict__ k, int r, int sub) {
+  double s = 0.0;
+  for (int i = 0; i < r; ++i)
+#pragma unroll
+    for (int c = 0; c < HD; c += 32) {
+      const f32x4 x = *reinterpret_cast<const f32x4*>(q + c + 4 * sub);
+      const f32x4 y = *reinterpret_cast<const f32x4*>(k + i * HD + c + 4 * sub);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s = fma((double)x[e], (double)y[e], s);
+    }
+#pragma unroll
+  for (int o = 1; o < 8; o <<= 1) s += __shfl_xor(s, o);
+  return s;
 }
 
 // a[0 .. n) sorted descending from a bitonic sequence (n a power of two).
@@ -324,12 +352,12 @@ __device__ __forceinline__ void vm_wait() {
   __builtin_amdgcn_s_waitcnt((V & 15) | ((V >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
-// lgls, lgm, lgg: log2 of l', m and g; check: ksum holds keys of blocks without a real token.
+// rr: compressed keys per selection block; lgls, lgm, lgg: log2 of l', m and g.
 template <int HD, int K>
 __global__ void __launch_bounds__(kWaves * 64)
-    select_kernel(const float* __restrict__ qpool, const float* __restrict__ ksum, const uint16_t* __restrict__ kunit,
-                  const float* __restrict__ knorm, int N, int lgls, int lgm, int lgg, int mask_own, int check, int kk,
-                  int* __restrict__ sel) {
+    select_kernel(const float* __restrict__ qpool, const float* __restrict__ ksum, const float* __restrict__ kcmp,
+                  const uint16_t* __restrict__ kunit, const float* __restrict__ knorm, int N, int rr, int lgls, int lgm, int lgg,
+                  int mask_own, int kk, int* __restrict__ sel) {
   constexpr int NCH = HD / 32;
   constexpr int KT = 4096 / HD;     // blocks per staged tile (8 KB)
   constexpr int GW = 16 * kWaves;   // groups per workgroup
@@ -341,7 +369,8 @@ __global__ void __launch_bounds__(kWaves * 64)
   __shared__ __attribute__((aligned(1024))) bf16_t ring[kRing][KT * HD];
   __shared__ __attribute__((aligned(256))) float nring[kRing][KT];
   __shared__ uint32_t flat_s[kWaves][kFlat];   // block | group << 20
-  __shared__ int cnt_s[kWaves][16];
+  __shared__ int cnt_s[kWaves][16], nmax_s[kWaves][16];   // a group's keys, their largest norm (as bits)
+  __shared__ float edge_s[kWaves][2][16];                 // a group's k*-th and next score
   __shared__ __attribute__((aligned(16))) int best_s[kWaves][16 * 16];
   static_assert(sizeof(ring) >= kWaves * 16 * kPerGroup * 8, "reused tiles");
   const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -387,6 +416,7 @@ __global__ void __launch_bounds__(kWaves * 64)
   const bool live = pg < ngroups;
   f16x8 qf[NCH];
   bool over;   // the group is scanned whole instead (a zero query: all blocks tie)
+  float qnorm;
   {
     const float* qr = qb + (size_t)(live ? pg : 0) * HD;
     float a[8 * NCH];
@@ -399,6 +429,7 @@ __global__ void __launch_bounds__(kWaves * 64)
     int ex;
     const float ss = unit_scale(a, 8 * NCH, ex, [](float x) { return col_max(x); }, [](float x) { return col_sum(x); });
     over = live && ss == 0.f;
+    qnorm = ldexpf(sqrtf(ss), ex);
     const float rn = ss == 0.f ? 0.f : kUnit / sqrtf(ss);
 #pragma unroll
     for (int c = 0; c < NCH; ++c)
@@ -510,7 +541,13 @@ __global__ void __launch_bounds__(kWaves * 64)
   uint64_t* keys = reinterpret_cast<uint64_t*>(ring) + wid * 16 * kPerGroup;   // [group][kPerGroup]
   int* cnt = cnt_s[wid];
   int* best16 = best_s[wid];   // [group][16] the k* best blocks
-  if (lane < 16) cnt[lane] = 0;
+  int* nmax = nmax_s[wid];
+  if (lane < 16) {
+    cnt[lane] = 0;
+    nmax[lane] = 0;
+    edge_s[wid][0][lane] = __builtin_huge_valf();
+    edge_s[wid][1][lane] = kNegInf;
+  }
   *reinterpret_cast<int4*>(best16 + 4 * lane) = make_int4(kNoBlock, kNoBlock, kNoBlock, kNoBlock);
   wave_sync();
   if (total > kFlat) {
@@ -535,7 +572,7 @@ __global__ void __launch_bounds__(kWaves * 64)
         qv[i][c] = *reinterpret_cast<const f32x4*>(qb + (size_t)(p0 + grp) * HD + 32 * c + 4 * sub);
         kv[i][c] = *reinterpret_cast<const f32x4*>(kc + (size_t)blk * HD + 32 * c + 4 * sub);
       }
-      n[i] = check ? kn[blk] : 0.f;
+      n[i] = kn[blk];
     }
 #pragma unroll
     for (int i = 0; i < PF; ++i) {
@@ -543,6 +580,7 @@ __global__ void __launch_bounds__(kWaves * 64)
       if (sub == 0 && e0 + 8 * i + (lane >> 3) < total && s > kNegInf && n[i] <= 0.f) {
         const int grp = (int)((x[i] >> 20) & 15), blk = (int)(x[i] & 0xFFFFF);
         const int at = atomicAdd(&cnt[grp], 1);
+        atomicMax(&nmax[grp], __float_as_int(-n[i]));   // norms are stored negated
         if (at < kPerGroup) keys[grp * kPerGroup + at] = make_key(s, blk);
       }
     }
@@ -571,7 +609,40 @@ __global__ void __launch_bounds__(kWaves * 64)
     }
 #pragma unroll
     for (int i = 0; i < 8; ++i)
+      if (own8[i] != 0 && (rank[i] == kk - 1 || rank[i] == kk)) edge_s[wid][rank[i] - kk + 1][r] = key_score(own8[i]);
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
       if (own8[i] != 0 && rank[i] < kk) best16[16 * r + rank[i]] = (int)(0xFFFFFFFFu - (uint32_t)own8[i]);
+  }
+  wave_sync();
+  // A score's f32 sum errs by at most 12 * 2^-24 |q| |k| (11 roundings, one in the summed key):
+  // groups whose k*-th and next score are closer than twice that are ranked in float64, lane t
+  // holding the group's key t.
+  uint64_t near = __builtin_amdgcn_ballot_w64(
+                      live && !over &&
+                      edge_s[wid][0][r] - edge_s[wid][1][r] <= 2.0f * 12.0f / (1 << 24) * qnorm * __int_as_float(nmax[r])) &
+                  0xFFFFull;
+  const int sub8 = lane >> 3;
+  while (near) {
+    const int g16 = __builtin_ctzll(near);
+    near &= near - 1;
+    const int m16 = __shfl(n, g16);   // <= kPerGroup = 64 keys
+    const uint64_t mine = lane < m16 ? keys[g16 * kPerGroup + lane] : 0;
+    const int blk = (int)(0xFFFFFFFFu - (uint32_t)mine);
+    double s64 = 0.0;
+    for (int i = 0; 8 * i < m16; ++i) {
+      const int bi = __shfl(blk, 8 * i + sub8);   // entry 8 i + lane / 8
+      const double v = score64<HD>(qb + (size_t)(p0 + g16) * HD, kcmp + ((size_t)bh * nblk + (8 * i + sub8 < m16 ? bi : 0)) * rr * HD, rr, sub);
+      const double got = __shfl(v, 8 * sub);      // of entry 8 i + lane % 8
+      s64 = sub8 == i ? got : s64;
+    }
+    int rank = 0;
+    for (int y = 0; y < m16; ++y) {
+      const double s2 = __shfl(s64, y);
+      const int b2 = __shfl(blk, y);
+      rank += (s2 > s64) | ((s2 == s64) & (b2 < blk));
+    }
+    if (lane < m16 && rank < kk) best16[16 * g16 + rank] = blk;
   }
   wave_sync();
   // stored ascending with -1 in unused slots: lane j places the blocks of ranks 4j .. 4j + 3
@@ -595,28 +666,22 @@ __global__ void __launch_bounds__(kWaves * 64)
     }
   }
 
-  // groups left over: every block scored in f32, eight at a time; the k* best keys sit in
-  // lanes 0 .. kk - 1 in descending order
+  // groups left over: every block scored in float64, eight at a time; the k* best keys (of
+  // the scores as f32) sit in lanes 0 .. kk - 1 in descending order
   uint64_t todo = __builtin_amdgcn_ballot_w64(over) & 0xFFFFull;
   while (todo) {
-    const int rr = __builtin_ctzll(todo);
+    const int gr = __builtin_ctzll(todo);
     todo &= todo - 1;
-    const float* qr = qb + (size_t)(p0 + rr) * HD;
-    const int lo = ((p0 + rr) >> (lgm - lgg)) << lgb;
+    const float* qr = qb + (size_t)(p0 + gr) * HD;
+    const int lo = ((p0 + gr) >> (lgm - lgg)) << lgb;
     const bool zero = __builtin_amdgcn_ballot_w64(lane < HD && qr[lane < HD ? lane : 0] != 0.f) == 0;
-    f32x4 qv[NCH];
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) qv[c] = *reinterpret_cast<const f32x4*>(qr + 32 * c + 4 * sub);
     uint64_t best = 0;
     for (int b0 = 0; b0 < nblk; b0 += 64) {
       // lane's key of block b0 + lane
       uint64_t key = 0;
       for (int i = 0; i < 8; ++i) {
         const int blk = b0 + 8 * i + (lane >> 3), bc = min(blk, nblk - 1);
-        f32x4 kv[NCH];
-#pragma unroll
-        for (int c = 0; c < NCH; ++c) kv[c] = *reinterpret_cast<const f32x4*>(kc + (size_t)bc * HD + 32 * c + 4 * sub);
-        const float s = dot8<NCH>(qv, kv);
+        const float s = (float)score64<HD>(qr, kcmp + ((size_t)bh * nblk + bc) * rr * HD, rr, sub);
         const float n0 = kn[bc];
         const bool ok = blk < nblk && !(mask_own && (uint32_t)(blk - lo) < (1u << lgb)) && n0 == n0 && s > kNegInf;
         const uint64_t k8 = ok ? make_key(s, blk) : 0;
@@ -645,8 +710,8 @@ __global__ void __launch_bounds__(kWaves * 64)
       rank += o != 0 && (int)(0xFFFFFFFFu - (uint32_t)o) < blk;
       n += o != 0;
     }
-    if (has) out[rr * kk + rank] = blk;
-    if (lane >= n && lane < kk) out[rr * kk + lane] = -1;
+    if (has) out[gr * kk + rank] = blk;
+    if (lane >= n && lane < kk) out[gr * kk + lane] = -1;
   }
 }
 
@@ -669,8 +734,8 @@ hipError_t select_k(const Dims& D, const void* q, const uint8_t* valid, const fl
                      lg(nblk), lg(R), blocks, ksum, kunit, knorm);
   const dim3 grid((ngroups + 16 * kWaves - 1) / (16 * kWaves), D.B * D.H);
   hipLaunchKernelGGL((select_kernel<HD, K>), grid, dim3(kWaves * 64), 0, st, (const float*)qpool, R > 1 ? ksum : kcmp,
-                     (const uint16_t*)kunit, (const float*)knorm, D.N, lg(D.ls), lg(D.m), lg(D.g), D.mask_own,
-                     (int)(R == 1), D.k, sel);
+                     kcmp, (const uint16_t*)kunit, (const float*)knorm, D.N, R, lg(D.ls), lg(D.m), lg(D.g), D.mask_own,
+                     D.k, sel);
   return hipGetLastError();
 }
 
