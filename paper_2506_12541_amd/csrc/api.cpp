@@ -187,6 +187,7 @@ FwdWs fwd_ws_layout(const bsa::Dims& D) {
 
 struct BwdWs {
   size_t qc_lp, doc, t4c, dqc, dqpart, lse, lsec, ml;
+  size_t dpre_v, pw1_v, psm_v, w1lp_v, dplp_v;
   size_t R, terms, dplp, kc_lp, vc_lp, dkc_part, dvc_part, dkc, dvc, pk, pv, pkt, pvt, hist, seg_s, seg_e, dpre, pw1, psm, w1lp,
       total;
   int cmp_chunks, mlp_chunks, mlp_chunks_small;
@@ -224,6 +225,13 @@ BwdWs bwd_ws_layout(const bsa::Dims& D) {
   W.psm = put(sizeof(float) * (size_t)W.mlp_chunks_small * ((size_t)D.d * D.d + 2 * D.d));
   W.w1lp = put(elem_bytes(D) * (size_t)D.l * D.d * D.d);
   W.dplp = put(elem_bytes(D) * crows * D.d);
+  // the value MLP's own copies (its backward shares the key MLP's launches)
+  const bool mlp = D.pool == 0;
+  W.dpre_v = put(mlp ? sizeof(float) * crows * D.d : 0);
+  W.pw1_v = put(mlp ? sizeof(float) * (size_t)W.mlp_chunks * D.l * D.d * D.d : 0);
+  W.psm_v = put(mlp ? sizeof(float) * (size_t)W.mlp_chunks_small * ((size_t)D.d * D.d + 2 * D.d) : 0);
+  W.w1lp_v = put(mlp ? elem_bytes(D) * (size_t)D.l * D.d * D.d : 0);
+  W.dplp_v = put(mlp ? elem_bytes(D) * crows * D.d : 0);
   W.qc_lp = put(D.gcmp ? elem_bytes(D) * crows * D.d : 0);
   W.doc = put(D.gcmp ? elem_bytes(D) * crows * D.d : 0);
   W.t4c = put(D.gcmp ? 4 * sizeof(float) * crows : 0);
@@ -650,10 +658,11 @@ bsa_status_t bsa_backward(const bsa_params_t* p, const void* q, const void* k, c
     gv = {dphi_v->w1, dphi_v->b1, dphi_v->w2, dphi_v->b2};
   }
   hipError_t e;
-  BSA_PHASE("bwd.mlp", st, e = bsa::launch_compress_bwd(D, k, valid, mk, saved->hid_k, A.dkc, dk, gk, mw, st));
-  BSA_TRY(e, "compression backward K");
-  BSA_PHASE("bwd.mlp", st, e = bsa::launch_compress_bwd(D, v, valid, mv, saved->hid_v, A.dvc, dv, gv, mw, st));
-  BSA_TRY(e, "compression backward V");
+  const bsa::MlpBwdWs mwv{(float*)(w + W.dpre_v), (float*)(w + W.pw1_v), (float*)(w + W.psm_v), (void*)(w + W.w1lp_v),
+                          W.mlp_chunks, W.mlp_chunks_small, (void*)(w + W.dplp_v)};
+  const bsa::CompressBwdJob mlp_jobs[2] = {{k, mk, saved->hid_k, A.dkc, dk, gk, mw}, {v, mv, saved->hid_v, A.dvc, dv, gv, mwv}};
+  BSA_PHASE("bwd.mlp", st, e = bsa::launch_compress_bwd(D, mlp_jobs, 2, valid, st));
+  BSA_TRY(e, "compression backward");
   const bsa::Slc1Ws S1 = slc1_ws(D, w, W.pk, W.pv, W.pkt, W.pvt, W.hist, W.seg_s, W.seg_e, W.dqpart, (size_t)-1);
   if (D.g == 1) {
     BSA_TRY(bsa::launch_slc1_bwd(D, q, k, v, d_o, valid, saved->sel_idx, (const float4*)A.terms + 2 * D.rows(), S1,
@@ -680,7 +689,8 @@ bsa_status_t bsa_backward(const bsa_params_t* p, const void* q, const void* k, c
       mq = {phi_q->w1, phi_q->b1, phi_q->w2, phi_q->b2};
       gq = {dphi_q->w1, dphi_q->b1, dphi_q->w2, dphi_q->b2};
     }
-    BSA_PHASE("bwd.mlp", st, e = bsa::launch_compress_bwd(Dq, q, valid, mq, saved->hid_q, A.dqc, dq, gq, mw, st));
+    const bsa::CompressBwdJob q_job = {q, mq, saved->hid_q, A.dqc, dq, gq, mw};
+    BSA_PHASE("bwd.mlp", st, e = bsa::launch_compress_bwd(Dq, &q_job, 1, valid, st));
     BSA_TRY(e, "query coarsening backward");
   }
   return BSA_OK;

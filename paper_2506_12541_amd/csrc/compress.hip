@@ -205,13 +205,27 @@ __device__ __forceinline__ float gelu_erf_grad(float x) {
   return 0.5f * (1.0f + erff(x * 0.70710678118654752f)) + x * 0.3989422804014327f * __expf(-0.5f * x * x);
 }
 
+// One backward job as the kernels see it: the key and the value MLP (same shapes) share every
+// launch, grid.z picks the job.
+struct MlpBwdJob {
+  const void* x;
+  const float *pre, *dy, *w1f, *w2;
+  const void* w1;        // W1 in the storage type
+  void *w1_lp, *dpre_lp;
+  float *dpre, *part_w1, *part_small, *dx;
+  float *gw1, *gw2, *gb1, *gb2;
+};
+
 // One wave per 16 rows: dpre (stored), and dx = dpre W1^T added into the token gradients.
 // The dx product runs in the storage type (bf16 MFMA for bf16 layers; W1 holds
 // bf16-representable values there), the rest in f32.
 template <typename T, int HD>
-__global__ void __launch_bounds__(256) mlp_bwd_rows_kernel(const float* dy, const float* pre, const uint8_t* valid,
-                                                           int H, int N, int l, long long rows, const T* w1,
-                                                           const float* w2, float* dpre_out, float* dx_accum) {
+__global__ void __launch_bounds__(256) mlp_bwd_rows_kernel(const uint8_t* valid, int H, int N, int l, long long rows,
+                                                           MlpBwdJob j0, MlpBwdJob j1) {
+  const MlpBwdJob& job = blockIdx.z ? j1 : j0;
+  const float *dy = job.dy, *pre = job.pre, *w2 = job.w2;
+  const T* w1 = (const T*)job.w1;
+  float *dpre_out = job.dpre, *dx_accum = job.dx;
   constexpr int NCH = HD / 32, OB = HD / 16;
   __shared__ float w2s[HD * (HD + 4)];
   __shared__ __attribute__((aligned(16))) float dps_all[4][16 * (HD + 4)];
@@ -274,17 +288,87 @@ __global__ void __launch_bounds__(256) mlp_bwd_rows_kernel(const float* dy, cons
   }
 }
 
-template <typename T>
-__global__ void cast_w_kernel(const float* x, int n, T* y) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) y[i] = from_f32<T>(x[i]);
+// W1 in bf16 (layers whose l*d is not a multiple of 256), eight values per thread.
+__device__ __forceinline__ void cast_w1(const MlpBwdJob& job, int blk, int n) {
+  const int i = (blk * 256 + (int)threadIdx.x) * 8;
+  if (i >= n) return;
+  const f32x8 v = load_chunk(job.w1f + i);
+  float a[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) a[e] = v[e];
+  *reinterpret_cast<bf16x8*>((bf16_t*)job.w1_lp + i) = make_chunk<bf16_t>(a);
+}
+__global__ void __launch_bounds__(256) cast_w_kernel(int n, MlpBwdJob j0, MlpBwdJob j1) {
+  cast_w1(blockIdx.z ? j1 : j0, blockIdx.x, n);
 }
 
-// dW1 partials: workgroup = (64 flattened inputs i, row chunk); wave w owns i in [16w, 16w+16).
+// dW1 partials of f32 layers: workgroup = (16 flattened inputs i, row chunk), its four waves
+// take 32 rows each in turn, MFMA operands straight from global memory (16 consecutive inputs
+// of a row per 16 lanes), and the waves' sums are added in wave order. Bound by load latency:
+// tiles of 64 inputs staged through LDS with two barriers per 32 rows took 211 instead of
+// 55 us for both MLPs at 8192 rows of 256.
+template <int HD>
+__global__ void __launch_bounds__(256) mlp_bwd_w1_f32_kernel(const uint8_t* valid, int H, int lgb, int l, long long rows,
+                                                             long long rows_per_chunk, MlpBwdJob j0, MlpBwdJob j1) {
+  constexpr int OB = HD / 16;
+  __shared__ f32x4 red[3][OB][64];
+  const MlpBwdJob& job = blockIdx.z ? j1 : j0;
+  const float *x = (const float*)job.x, *dpre = job.dpre;
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const int r = lane & 15, j = lane >> 4;
+  const int ld = l * HD, i0 = blockIdx.x * 16, tok = i0 / HD;
+  const long long rbeg = (long long)blockIdx.y * rows_per_chunk;
+  const long long rend = rbeg + rows_per_chunk < rows ? rbeg + rows_per_chunk : rows;
+  f32x4 acc[OB];
+#pragma unroll
+  for (int ob = 0; ob < OB; ++ob) acc[ob] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+  for (long long r0 = rbeg + 32 * wid; r0 < rend; r0 += 128) {
+    f32x8 a, b[OB];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const long long row = r0 + 4 * e + j;
+      const bool in = row < rend;
+      const long long rc = in ? row : rend - 1;
+      bool ok = in;
+      if (valid)
+        ok = ok && valid[(((long long)((uint32_t)(rc >> lgb) / (uint32_t)H) << lgb) + (rc & ((1LL << lgb) - 1))) * l + tok] != 0;
+      const float xv = x[rc * ld + i0 + r];
+      a[e] = ok ? xv : 0.f;
+#pragma unroll
+      for (int ob = 0; ob < OB; ++ob) {
+        const float dv = dpre[rc * HD + 16 * ob + r];
+        b[ob][e] = in ? dv : 0.f;
+      }
+    }
+#pragma unroll
+    for (int ob = 0; ob < OB; ++ob) acc[ob] = mma(a, b[ob], acc[ob]);
+  }
+  if (wid > 0) {
+#pragma unroll
+    for (int ob = 0; ob < OB; ++ob) red[wid - 1][ob][lane] = acc[ob];
+  }
+  __syncthreads();
+  if (wid > 0) return;
+  // lane: o = 16 ob + r (column), i = i0 + 4 j + t (rows)
+  float* out = job.part_w1 + (size_t)blockIdx.y * ld * HD;
+#pragma unroll
+  for (int ob = 0; ob < OB; ++ob) {
+    const f32x4 v = ((acc[ob] + red[0][ob][lane]) + red[1][ob][lane]) + red[2][ob][lane];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) out[(size_t)(i0 + 4 * j + t) * HD + 16 * ob + r] = v[t];
+  }
+}
+
+// dW1 partials of bf16 layers whose l*d is not a multiple of 256: workgroup = (64 flattened
+// inputs i, row chunk); wave w owns i in [16w, 16w+16).
 template <typename T, int HD>
-__global__ void __launch_bounds__(256) mlp_bwd_w1_kernel(const T* x, const uint8_t* valid, const float* dpre, int H,
-                                                         int N, int l, long long rows, long long rows_per_chunk,
-                                                         float* part) {
+__global__ void __launch_bounds__(256) mlp_bwd_w1_kernel(const uint8_t* valid, int H, int N, int l, long long rows,
+                                                         long long rows_per_chunk, MlpBwdJob j0, MlpBwdJob j1) {
+  const MlpBwdJob& job = blockIdx.z ? j1 : j0;
+  const T* x = (const T*)job.x;
+  const float* dpre = job.dpre;
+  float* part = job.part_w1;
   constexpr int TSTR = 32 + 4;
   constexpr int OB = HD / 16;
   typedef typename Chunk<T>::type CT;
@@ -352,8 +436,11 @@ __global__ void __launch_bounds__(256) mlp_bwd_w1_kernel(const T* x, const uint8
 
 // dW2, db1, db2 partials over a row chunk: thread (o2, o-slice).
 template <int HD>
-__global__ void __launch_bounds__(256) mlp_bwd_small_kernel(const float* dy, const float* pre, const float* dpre,
-                                                            long long rows, long long rows_per_chunk, float* part) {
+__global__ void __launch_bounds__(256) mlp_bwd_small_kernel(long long rows, long long rows_per_chunk, MlpBwdJob j0,
+                                                            MlpBwdJob j1) {
+  const MlpBwdJob& job = blockIdx.z ? j1 : j0;
+  const float *dy = job.dy, *pre = job.pre, *dpre = job.dpre;
+  float* part = job.part_small;
   __shared__ float hs[32][HD];
   __shared__ float ys[32][HD];
   __shared__ float ps[32][HD];
@@ -399,21 +486,6 @@ __global__ void __launch_bounds__(256) mlp_bwd_small_kernel(const float* dy, con
   }
 }
 
-// out[i] = sum over chunks of part[c * stride + i]. A workgroup owns 64 outputs; its
-// 4 waves each sum every 4th chunk, then the four partial sums are added in wave order.
-__global__ void __launch_bounds__(256) sum_parts_kernel(const float* part, int chunks, long long n, long long stride,
-                                                        float* out) {
-  __shared__ float red[4][64];
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  const long long i = (long long)blockIdx.x * 64 + lane;
-  float s = 0.f;
-  if (i < n)
-    for (int c = wid; c < chunks; c += 4) s += part[(long long)c * stride + i];
-  red[wid][lane] = s;
-  __syncthreads();
-  if (wid == 0 && i < n) out[i] = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
-}
-
 // Mean pooling backward: every real token of a block receives dy / l.
 __global__ void mean_pool_bwd_kernel(const float* dy, const uint8_t* valid, int H, int N, int l, int hd, long long rows,
                                      float* dx_accum) {
@@ -440,9 +512,16 @@ __global__ void mean_pool_bwd_kernel(const float* dy, const uint8_t* valid, int 
 // owns 2 rows x 4 outputs (W2 staged transposed so its 4 outputs are one float4 read), for
 // dW2 a 4 x 4 block.
 template <int HD>
-__global__ void __launch_bounds__(256) mlp_bwd_pre_kernel(const float* dy, const float* pre, const float* w2,
-                                                          long long rows, long long rows_per_wg, float* dpre,
-                                                          bf16_t* dpre_lp, float* part) {
+__global__ void __launch_bounds__(256) mlp_bwd_pre_kernel(long long rows, long long rows_per_wg, int chunks, int nw1,
+                                                          MlpBwdJob j0, MlpBwdJob j1) {
+  const MlpBwdJob& job = blockIdx.z ? j1 : j0;
+  if ((int)blockIdx.x >= chunks) {   // the workgroups past the row chunks cast W1
+    cast_w1(job, (int)blockIdx.x - chunks, nw1);
+    return;
+  }
+  const float *dy = job.dy, *pre = job.pre, *w2 = job.w2;
+  float *dpre = job.dpre, *part = job.part_small;
+  bf16_t* dpre_lp = (bf16_t*)job.dpre_lp;
   constexpr int TR = 32;                       // rows per tile
   constexpr int OQ = HD / 4;                   // 4-wide output groups per row
   constexpr int RB = TR * OQ / 256;            // rows per thread in the dh pass (2 for HD=64, 1 for 32)
@@ -560,9 +639,11 @@ __global__ void __launch_bounds__(256) mlp_bwd_pre_kernel(const float* dy, const
 // global); a lane ends with 4 consecutive i of one row per 16-input tile. All tiles of a
 // pass are computed first, then the gradient rows are read together and written back.
 template <int HD>
-__global__ void __launch_bounds__(256) mlp_bwd_dx_kernel(const bf16_t* dpre_lp, const bf16_t* w1, const uint8_t* valid,
-                                                         int H, int N, int l, long long rows, int passes,
-                                                         float* dx_accum) {
+__global__ void __launch_bounds__(256) mlp_bwd_dx_kernel(const uint8_t* valid, int H, int N, int l, long long rows,
+                                                         int passes, MlpBwdJob j0, MlpBwdJob j1) {
+  const MlpBwdJob& job = blockIdx.z ? j1 : j0;
+  const bf16_t *dpre_lp = (const bf16_t*)job.dpre_lp, *w1 = (const bf16_t*)job.w1_lp;
+  float* dx_accum = job.dx;
   constexpr int NCH = HD / 32;
   constexpr int IT = 256 / 16;   // i tiles per workgroup
   __shared__ __attribute__((aligned(16))) bf16_t w1s[256 * HD];
@@ -621,9 +702,11 @@ __global__ void __launch_bounds__(256) mlp_bwd_dx_kernel(const bf16_t* dpre_lp, 
 // distinct objects, loop unrolled by two) by direct loads, and both operands, which run
 // along the rows, come from transpose reads. Inputs of padding tokens are zeroed in LDS.
 template <int HD>
-__global__ void __launch_bounds__(256) mlp_bwd_w1_dma_kernel(const bf16_t* x, const uint8_t* valid,
-                                                             const bf16_t* dpre_lp, int H, int N, int l,
-                                                             long long rows, long long rows_per_chunk, float* part) {
+__global__ void __launch_bounds__(256) mlp_bwd_w1_dma_kernel(const uint8_t* valid, int H, int N, int l, long long rows,
+                                                             long long rows_per_chunk, MlpBwdJob j0, MlpBwdJob j1) {
+  const MlpBwdJob& job = blockIdx.z ? j1 : j0;
+  const bf16_t *x = (const bf16_t*)job.x, *dpre_lp = (const bf16_t*)job.dpre_lp;
+  float* part = job.part_w1;
   constexpr int XW = 256;          // inputs per workgroup (tile width)
   constexpr int OB = HD / 16;
   constexpr int TR = 32;           // rows per step
@@ -704,96 +787,85 @@ __global__ void __launch_bounds__(256) mlp_bwd_w1_dma_kernel(const bf16_t* x, co
       for (int t = 0; t < 4; ++t) out[(size_t)(i0 + 64 * wid + 16 * a + 4 * j + t) * HD + 16 * ob + r] = acc[a][ob][t];
 }
 
-// (4) out[i] = sum over chunks of part[c * stride + i], chunks in order; a workgroup owns
-// 64 outputs and its 4 waves take every 4th chunk, then add their sums in wave order.
-__global__ void __launch_bounds__(256) sum_parts_wide_kernel(const float* part, int chunks, long long n,
-                                                             long long stride, float* out) {
+// (4) The chunks' partials of all four gradients summed, chunks in order: a workgroup owns 64
+// outputs and its 4 waves take every 4th chunk, then add their sums in wave order. The first
+// workgroups sum dW1 (n1 values in c1 chunks), the rest dW2, db1 and db2.
+template <int HD>
+__global__ void __launch_bounds__(256) sum_parts_kernel(int n1, int c1, int cs, MlpBwdJob j0, MlpBwdJob j1) {
   __shared__ float red[4][64];
+  const MlpBwdJob& job = blockIdx.z ? j1 : j0;
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  const long long i = (long long)blockIdx.x * 64 + lane;
+  const bool first = (int)blockIdx.x < n1 / 64;   // n1 = l d d, a multiple of 64
+  const int i = (first ? (int)blockIdx.x : (int)blockIdx.x - n1 / 64) * 64 + lane;
+  const float* part = first ? job.part_w1 : job.part_small;
+  const int n = first ? n1 : HD * HD + 2 * HD, chunks = first ? c1 : cs;
   float s = 0.f;
   if (i < n) {
 #pragma unroll 8
-    for (int c = wid; c < chunks; c += 4) s += part[(long long)c * stride + i];
+    for (int c = wid; c < chunks; c += 4) s += part[(long long)c * n + i];
   }
   red[wid][lane] = s;
   __syncthreads();
-  if (wid == 0 && i < n) out[i] = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
-}
-
-template <int HD>
-hipError_t compress_bwd_bf16(const Dims& D, const void* x, const uint8_t* valid, const Mlp& phi, const float* pre,
-                             const float* dy, float* dx_accum, const MlpGrad& grad, const MlpBwdWs& ws,
-                             hipStream_t st) {
-  const long long rows = D.cmp_rows();
-  const int ld = D.l * HD;
-  bf16_t* w1 = (bf16_t*)ws.w1_lp;
-  bf16_t* dpl = (bf16_t*)ws.dpre_lp;
-  hipLaunchKernelGGL(cast_w_kernel<bf16_t>, dim3((ld * HD + 255) / 256), dim3(256), 0, st, phi.w1, ld * HD, w1);
-  const long long rps = ((rows + ws.chunks_small - 1) / ws.chunks_small + 31) / 32 * 32;
-  hipLaunchKernelGGL((mlp_bwd_pre_kernel<HD>), dim3(ws.chunks_small), dim3(256), 0, st, dy, pre, phi.w2, rows, rps,
-                     ws.dpre, dpl, ws.part_small);
-  constexpr int kPasses = 4;   // 64-row passes per workgroup of the dx product
-  const long long ry = (rows + 64 * kPasses - 1) / (64 * kPasses);
-  hipLaunchKernelGGL((mlp_bwd_dx_kernel<HD>), dim3(ld / 256, (unsigned)ry), dim3(256), 0, st, (const bf16_t*)dpl,
-                     (const bf16_t*)w1, valid, D.H, D.N, D.l, rows, kPasses, dx_accum);
-  const long long rpc = ((rows + ws.chunks - 1) / ws.chunks + 31) / 32 * 32;
-  const int nch = (int)((rows + rpc - 1) / rpc);
-  hipLaunchKernelGGL((mlp_bwd_w1_dma_kernel<HD>), dim3(ld / 256, nch), dim3(256), 0, st, (const bf16_t*)x, valid,
-                     (const bf16_t*)dpl, D.H, D.N, D.l, rows, rpc, ws.part_w1);
-  const long long n1 = (long long)ld * HD;
-  hipLaunchKernelGGL(sum_parts_wide_kernel, dim3((unsigned)((n1 + 63) / 64)), dim3(256), 0, st, ws.part_w1, nch, n1,
-                     n1, grad.w1);
-  const long long ss = (long long)HD * HD + 2 * HD;
-  const int nsm = (int)((rows + rps - 1) / rps);
-  float* tmp = grad.w2;   // W2, b1, b2 partials are summed into their three outputs
-  hipLaunchKernelGGL(sum_parts_wide_kernel, dim3((HD * HD + 63) / 64), dim3(256), 0, st, ws.part_small, nsm,
-                     (long long)HD * HD, ss, tmp);
-  hipLaunchKernelGGL(sum_parts_wide_kernel, dim3(1), dim3(256), 0, st, ws.part_small + HD * HD, nsm, (long long)HD,
-                     ss, grad.b1);
-  hipLaunchKernelGGL(sum_parts_wide_kernel, dim3(1), dim3(256), 0, st, ws.part_small + HD * HD + HD, nsm,
-                     (long long)HD, ss, grad.b2);
-  return hipGetLastError();
+  if (wid != 0 || i >= n) return;
+  float* out = first ? job.gw1 + i
+               : i < HD * HD        ? job.gw2 + i
+               : i < HD * HD + HD   ? job.gb1 + i - HD * HD
+                                    : job.gb2 + i - HD * HD - HD;
+  *out = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
 }
 
 template <typename T, int HD>
-hipError_t compress_bwd_impl(const Dims& D, const void* x, const uint8_t* valid, const Mlp& phi, const float* pre,
-                             const float* dy, float* dx_accum, const MlpGrad& grad, const MlpBwdWs& ws,
-                             hipStream_t st) {
+hipError_t compress_bwd_impl(const Dims& D, const CompressBwdJob* jobs, int n, const uint8_t* valid, hipStream_t st) {
   const long long rows = D.cmp_rows();
   if (D.pool == 1) {
     const long long tot = rows * D.l * HD;
-    hipLaunchKernelGGL(mean_pool_bwd_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, dy, valid, D.H, D.N,
-                       D.l, HD, rows, dx_accum);
+    for (int i = 0; i < n; ++i)
+      hipLaunchKernelGGL(mean_pool_bwd_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, jobs[i].dy, valid,
+                         D.H, D.N, D.l, HD, rows, jobs[i].dx);
     return hipGetLastError();
   }
-  if constexpr (sizeof(T) == 2) {
-    if (D.l * HD % 256 == 0) return compress_bwd_bf16<HD>(D, x, valid, phi, pre, dy, dx_accum, grad, ws, st);
+  const int ld = D.l * HD, n1 = ld * HD;
+  MlpBwdJob mj[2];
+  for (int i = 0; i < n; ++i) {
+    const CompressBwdJob& c = jobs[i];
+    mj[i] = MlpBwdJob{c.x, c.pre, c.dy, c.phi.w1, c.phi.w2, sizeof(T) == 2 ? c.ws.w1_lp : (const void*)c.phi.w1,
+                      c.ws.w1_lp, c.ws.dpre_lp, c.ws.dpre, c.ws.part_w1, c.ws.part_small, c.dx,
+                      c.grad.w1, c.grad.w2, c.grad.b1, c.grad.b2};
   }
-  const int ld = D.l * HD;
-  const T* w1 = (const T*)phi.w1;
-  if (sizeof(T) == 2) {
-    hipLaunchKernelGGL(cast_w_kernel<T>, dim3((ld * HD + 255) / 256), dim3(256), 0, st, phi.w1, ld * HD, (T*)ws.w1_lp);
-    w1 = (const T*)ws.w1_lp;
-  }
-  hipLaunchKernelGGL((mlp_bwd_rows_kernel<T, HD>), dim3((unsigned)((rows + 63) / 64)), dim3(256), 0, st, dy, pre, valid,
-                     D.H, D.N, D.l, rows, w1, phi.w2, ws.dpre, dx_accum);
-  const long long rpc = ((rows + ws.chunks - 1) / ws.chunks + 31) / 32 * 32;
-  hipLaunchKernelGGL((mlp_bwd_w1_kernel<T, HD>), dim3(ld / 64, ws.chunks), dim3(256), 0, st, (const T*)x, valid, ws.dpre,
-                     D.H, D.N, D.l, rows, rpc, ws.part_w1);
+  if (n == 1) mj[1] = mj[0];
+  const unsigned nz = (unsigned)n;
+  const MlpBwdWs& ws = jobs[0].ws;   // the chunk counts are those of every job
   const long long rps = ((rows + ws.chunks_small - 1) / ws.chunks_small + 31) / 32 * 32;
-  hipLaunchKernelGGL((mlp_bwd_small_kernel<HD>), dim3(ws.chunks_small), dim3(256), 0, st, dy, pre, ws.dpre, rows, rps,
-                     ws.part_small);
-  const long long n1 = (long long)ld * HD;
-  hipLaunchKernelGGL(sum_parts_kernel, dim3((unsigned)((n1 + 63) / 64)), dim3(256), 0, st, ws.part_w1, ws.chunks, n1,
-                     n1, grad.w1);
-  const long long ss = (long long)HD * HD + 2 * HD;
-  hipLaunchKernelGGL(sum_parts_kernel, dim3((HD * HD + 63) / 64), dim3(256), 0, st, ws.part_small, ws.chunks_small,
-                     (long long)HD * HD, ss, grad.w2);
-  hipLaunchKernelGGL(sum_parts_kernel, dim3((HD + 63) / 64), dim3(256), 0, st, ws.part_small + HD * HD,
-                     ws.chunks_small, (long long)HD, ss, grad.b1);
-  hipLaunchKernelGGL(sum_parts_kernel, dim3((HD + 63) / 64), dim3(256), 0, st, ws.part_small + HD * HD + HD,
-                     ws.chunks_small, (long long)HD, ss, grad.b2);
+  const long long rpc = ((rows + ws.chunks - 1) / ws.chunks + 31) / 32 * 32;
+  const int nsm = (int)((rows + rps - 1) / rps), nch = (int)((rows + rpc - 1) / rpc);
+  const unsigned cast_wgs = (unsigned)((n1 / 8 + 255) / 256);
+  bool wide = false;
+  if constexpr (sizeof(T) == 2) wide = ld % 256 == 0;
+  if (wide) {
+    if constexpr (sizeof(T) == 2) {
+      hipLaunchKernelGGL((mlp_bwd_pre_kernel<HD>), dim3((unsigned)nsm + cast_wgs, 1, nz), dim3(256), 0, st, rows, rps,
+                         nsm, n1, mj[0], mj[1]);
+      constexpr int kPasses = 4;   // 64-row passes per workgroup of the dx product
+      const long long ry = (rows + 64 * kPasses - 1) / (64 * kPasses);
+      hipLaunchKernelGGL((mlp_bwd_dx_kernel<HD>), dim3(ld / 256, (unsigned)ry, nz), dim3(256), 0, st, valid, D.H, D.N,
+                         D.l, rows, kPasses, mj[0], mj[1]);
+      hipLaunchKernelGGL((mlp_bwd_w1_dma_kernel<HD>), dim3(ld / 256, nch, nz), dim3(256), 0, st, valid, D.H, D.N, D.l,
+                         rows, rpc, mj[0], mj[1]);
+    }
+  } else {
+    if (sizeof(T) == 2) hipLaunchKernelGGL(cast_w_kernel, dim3(cast_wgs, 1, nz), dim3(256), 0, st, n1, mj[0], mj[1]);
+    hipLaunchKernelGGL((mlp_bwd_rows_kernel<T, HD>), dim3((unsigned)((rows + 63) / 64), 1, nz), dim3(256), 0, st, valid,
+                       D.H, D.N, D.l, rows, mj[0], mj[1]);
+    if constexpr (sizeof(T) == 4)
+      hipLaunchKernelGGL((mlp_bwd_w1_f32_kernel<HD>), dim3(ld / 16, nch, nz), dim3(256), 0, st, valid, D.H,
+                         __builtin_ctz((unsigned)(D.N / D.l)), D.l, rows, rpc, mj[0], mj[1]);
+    else
+      hipLaunchKernelGGL((mlp_bwd_w1_kernel<T, HD>), dim3(ld / 64, nch, nz), dim3(256), 0, st, valid, D.H, D.N, D.l,
+                         rows, rpc, mj[0], mj[1]);
+    hipLaunchKernelGGL((mlp_bwd_small_kernel<HD>), dim3(nsm, 1, nz), dim3(256), 0, st, rows, rps, mj[0], mj[1]);
+  }
+  const unsigned sum_wgs = (unsigned)(n1 / 64 + (HD * HD + 2 * HD + 63) / 64);
+  hipLaunchKernelGGL((sum_parts_kernel<HD>), dim3(sum_wgs, 1, nz), dim3(256), 0, st, n1, nch, nsm, mj[0], mj[1]);
   return hipGetLastError();
 }
 
@@ -849,10 +921,10 @@ int mlp_bwd_chunks(const Dims& D) {
   return (int)c;
 }
 
-hipError_t launch_compress_bwd(const Dims& D, const void* x, const uint8_t* valid, const Mlp& phi, const float* pre,
-                               const float* dy, float* dx_accum, const MlpGrad& grad, const MlpBwdWs& ws,
+hipError_t launch_compress_bwd(const Dims& D, const CompressBwdJob* jobs, int n, const uint8_t* valid,
                                hipStream_t st) {
-  return BSA_DISPATCH(compress_bwd_impl, D, x, valid, phi, pre, dy, dx_accum, grad, ws, st);
+  if (n < 1 || n > 2) return hipErrorInvalidValue;
+  return BSA_DISPATCH(compress_bwd_impl, D, jobs, n, valid, st);
 }
 
 hipError_t launch_compress_fwd(const Dims& D, const CompressJob* jobs, int n, const uint8_t* valid, hipStream_t st) {

@@ -167,9 +167,16 @@ struct MlpBwdWs {
 };
 int mlp_bwd_chunks(const Dims& D);
 int mlp_bwd_chunks_small(const Dims& D);
-hipError_t launch_compress_bwd(const Dims& D, const void* x, const uint8_t* valid, const Mlp& phi, const float* pre,
-                               const float* dy, float* dx_accum, const MlpGrad& grad, const MlpBwdWs& ws,
-                               hipStream_t st);
+struct CompressBwdJob {
+  const void* x;
+  Mlp phi;
+  const float *pre, *dy;
+  float* dx;      // token gradients, added to
+  MlpGrad grad;
+  MlpBwdWs ws;    // of this job alone
+};
+// n = 1 or 2 compressions of the same shape (keys and values share the launches)
+hipError_t launch_compress_bwd(const Dims& D, const CompressBwdJob* jobs, int n, const uint8_t* valid, hipStream_t st);
 
 size_t slc1_pairs(const Dims& D);
 hipError_t launch_slc1_csr(const Dims& D, const int* sel, const uint8_t* valid, const Slc1Ws& W, uint32_t** vals_out,
