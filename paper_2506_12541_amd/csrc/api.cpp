@@ -519,13 +519,10 @@ bsa_status_t bsa_forward(const bsa_params_t* p, const void* q, const void* k, co
   const bsa::CompressJob kv_jobs[2] = {
       {k, mk, saved->kcmp, saved->hid_k, kc_lp, w + W.w1t_k, bsa::cmp_key_scale(D)},
       {v, mv, saved->vcmp, saved->hid_v, vc_lp, w + W.w1t_v, 1.0f}};
-  BSA_STEP("fwd.compress", (bsa::launch_block_valid(D, valid, saved->cvalid, st) != hipSuccess
-                                ? hipGetLastError()
-                                : bsa::launch_compress_fwd(D, kv_jobs, 2, valid, st)),
-           "compression");
+  BSA_STEP("fwd.compress", bsa::launch_compress_fwd(D, kv_jobs, 2, valid, saved->cvalid, st), "compression");
   if (D.block_coarse()) {
     const bsa::CompressJob q_job = {q, mq, saved->qcmp, saved->hid_q, qc_lp, w + W.w1t_q, 1.0f};
-    BSA_STEP("fwd.compress", bsa::launch_compress_fwd(Dq, &q_job, 1, valid, st), "query coarsening");
+    BSA_STEP("fwd.compress", bsa::launch_compress_fwd(Dq, &q_job, 1, valid, nullptr, st), "query coarsening");
   }
   // ball and compressed attention on the auxiliary stream (the caller's one with the shared
   // launch), selection on the caller's
@@ -938,10 +935,9 @@ bsa_status_t bsa_block_forward(const bsa_params_t* p, int32_t ffn_dim, const bsa
   uint16_t *wqkv = (uint16_t*)(c + L.wqkv), *wo = (uint16_t*)(c + L.wo), *w13 = (uint16_t*)(c + L.w13),
            *w2 = (uint16_t*)(c + L.w2);
   BSA_PHASE("blk.elem", st, {
-    BSA_HIP(bsa::launch_cast_bf16(w->wqkv, 3LL * C * C, wqkv, st), "cast wqkv");
-    BSA_HIP(bsa::launch_cast_bf16(w->wo, (long long)C * C, wo, st), "cast wo");
-    BSA_HIP(bsa::launch_cast_w13(w->w1, w->w3, F, C, bsa::gemm_wave_cols((int)M, 2 * F), w13, st), "cast w1, w3");
-    BSA_HIP(bsa::launch_cast_bf16(w->w2, (long long)C * F, w2, st), "cast w2");
+    BSA_HIP(bsa::launch_cast_weights(w->wqkv, w->wo, w->w1, w->w3, w->w2, C, F, bsa::gemm_wave_cols((int)M, 2 * F),
+                                     wqkv, wo, w13, w2, st),
+            "cast weights");
   });
   BSA_PHASE("blk.norm", st,
             BSA_HIP(bsa::launch_rmsnorm_fwd(x, w->g1, w->wg, M, C, (uint16_t*)sv.xn1, sv.rstd1, sv.gate, st),
@@ -1001,11 +997,8 @@ bsa_status_t bsa_block_backward(const bsa_params_t* p, int32_t ffn_dim, const bs
   float *part = f32(L.part), *dxn = f32(L.dxn), *dh = f32(L.dh), *dq = f32(L.dq), *dk = f32(L.dk),
         *dv = f32(L.dv), *dgate = f32(L.dgate), *npart = f32(L.npart);
   BSA_PHASE("blk.elem", st, {
-    BSA_HIP(bsa::launch_cast_t(w->wqkv, 3 * C, C, wqkvt, 3 * C, st), "cast wqkv^T");
-    BSA_HIP(bsa::launch_cast_t(w->wo, C, C, wot, C, st), "cast wo^T");
-    BSA_HIP(bsa::launch_cast_t(w->w1, F, C, w13t, 2 * F, st), "cast w1^T");
-    BSA_HIP(bsa::launch_cast_t(w->w3, F, C, w13t + F, 2 * F, st), "cast w3^T");
-    BSA_HIP(bsa::launch_cast_t(w->w2, C, F, w2t, C, st), "cast w2^T");
+    BSA_HIP(bsa::launch_cast_weights_t(w->wqkv, w->wo, w->w1, w->w3, w->w2, C, F, wqkvt, wot, w13t, w2t, st),
+            "cast transposed weights");
     BSA_HIP(bsa::launch_cast_bf16(dy, M * C, dy16, st), "cast dy");
   });
   // SwiGLU sublayer

@@ -365,7 +365,7 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_kernel(GemmArgs g) {
       }
     } else if (o.epi == kEpiSwigluFwd) {
       // B rows interleaved in groups of TNW (TNW / 2 rows of W_1, then the same rows of
-      // W_3; launch_cast_w13 with gemm_wave_cols): columns c and c + TNW / 2 hold u and w of
+      // W_3; launch_cast_weights with gemm_wave_cols): columns c and c + TNW / 2 hold u and w of
       // the same hidden unit
       constexpr int LPR = TNW / 16, RPI = 64 / LPR;
       const int c = 8 * (lane % LPR), F = o.ffn;
@@ -662,37 +662,74 @@ __global__ void __launch_bounds__(256) cast_bf16_kernel(const float* __restrict_
   *reinterpret_cast<bf16x8*>(dst + 8 * i) = make_chunk<bf16_t>(o);
 }
 
-// dst[c * ldd + r] = bf16(src[r * cols + c]) for a [rows, cols] f32 matrix (32 x 32 tiles
-// through LDS; rows and cols multiples of 32).
-__global__ void __launch_bounds__(256) cast_t_kernel(const float* __restrict__ src, int rows, int cols,
-                                                     bf16_t* __restrict__ dst, long long ldd) {
-  __shared__ float tile[32][33];
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  const int c0 = blockIdx.x * 32, r0 = blockIdx.y * 32;
+// The block's weights in bf16 as the forward's products read them, one launch for all (four
+// launches of a few microseconds each before): eight values per thread, the segments one after
+// the other (wqkv, wo, w2 as they are, then w13). Rows of the interleaved [W_1; W_3] operand
+// come in groups of G: row r takes row (G / 2)(r / G) + r % G of W_1 when r % G < G / 2, else
+// row (G / 2)(r / G) + r % G - G / 2 of W_3 (C a multiple of 8).
+struct CastWeights {
+  const float* src[5];   // wqkv, wo, w2, w1, w3
+  bf16_t* dst[4];        // wqkv, wo, w2, w13
+  long long n8[4];       // eight-value pieces of each
+  int C, G;
+};
+__global__ void __launch_bounds__(256) cast_weights_kernel(CastWeights a) {
+  long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+  const float* src = a.src[0];
+  bf16_t* dst = a.dst[0];
+  int seg = 0;
 #pragma unroll
-  for (int k = 0; k < 4; ++k) tile[ty + 8 * k][tx] = src[(long long)(r0 + ty + 8 * k) * cols + c0 + tx];
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < 4; ++k) dst[(long long)(c0 + ty + 8 * k) * ldd + r0 + tx] = f2bf(tile[tx][ty + 8 * k]);
-}
-
-// dst rows of the interleaved [W_1; W_3] operand in groups of G rows: row r takes row
-// (G / 2)(r / G) + r % G of W_1 when r % G < G / 2, else row (G / 2)(r / G) + r % G - G / 2
-// of W_3 (f32 -> bf16, eight elements per thread; C a multiple of 8).
-__global__ void __launch_bounds__(256) cast_w13_kernel(const float* __restrict__ w1, const float* __restrict__ w3,
-                                                       int F, int C, int G, bf16_t* __restrict__ dst) {
-  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-  const int c8 = C / 8;
-  if (i >= 2LL * F * c8) return;
-  const long long r = i / c8;
-  const int c = (int)(i - r * c8) * 8;
-  const int g = (int)(r / G), wi = (int)(r % G), h = G / 2;
-  const float* src = wi < h ? w1 + (long long)(h * g + wi) * C : w3 + (long long)(h * g + wi - h) * C;
-  const f32x8 v = load_chunk(src + c);
+  for (int k = 0; k < 3; ++k)
+    if (seg == k && i >= a.n8[k]) {
+      i -= a.n8[k];
+      seg = k + 1;
+      src = a.src[k + 1];
+      dst = a.dst[k + 1];
+    }
+  if (seg == 3) {
+    if (i >= a.n8[3]) return;
+    const int c8 = a.C / 8, r = (int)(i / c8), c = (int)(i - (long long)r * c8) * 8;
+    const int g = r / a.G, wi = r % a.G, h = a.G / 2;
+    src = (wi < h ? a.src[3] + (long long)(h * g + wi) * a.C : a.src[4] + (long long)(h * g + wi - h) * a.C) + c;
+  } else {
+    src += 8 * i;
+  }
+  const f32x8 v = load_chunk(src);
   float o[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) o[e] = v[e];
-  *reinterpret_cast<bf16x8*>(dst + r * C + c) = make_chunk<bf16_t>(o);
+  *reinterpret_cast<bf16x8*>(dst + 8 * i) = make_chunk<bf16_t>(o);
+}
+
+// Five transposed casts in one launch: dst[c * ldd + r] = bf16(src[r * cols + c]) for [rows,
+// cols] f32 matrices (32 x 32 tiles through LDS; rows and cols multiples of 32), the matrices'
+// tiles one after the other.
+struct CastWeightsT {
+  const float* src[5];
+  bf16_t* dst[5];
+  int rows[5], cols[5], ldd[5];
+};
+__global__ void __launch_bounds__(256) cast_weights_t_kernel(CastWeightsT a) {
+  __shared__ float tile[32][33];
+  int id = blockIdx.x, k = 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int nt = (a.rows[q] / 32) * (a.cols[q] / 32);
+    if (k == q && id >= nt) {
+      id -= nt;
+      k = q + 1;
+    }
+  }
+  const int cols = a.cols[k], tpr = cols / 32;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  const int r0 = id / tpr * 32, c0 = id % tpr * 32;
+  const float* src = a.src[k];
+  bf16_t* dst = a.dst[k];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) tile[ty + 8 * q][tx] = src[(long long)(r0 + ty + 8 * q) * cols + c0 + tx];
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 4; ++q) dst[(long long)(c0 + ty + 8 * q) * a.ldd[k] + r0 + tx] = f2bf(tile[tx][ty + 8 * q]);
 }
 
 unsigned blocks_for(long long n, int per) { return (unsigned)((n + per - 1) / per); }
@@ -851,15 +888,26 @@ hipError_t launch_cast_bf16(const float* src, long long n, uint16_t* dst, hipStr
   return hipGetLastError();
 }
 
-hipError_t launch_cast_w13(const float* w1, const float* w3, int F, int C, int G, uint16_t* dst, hipStream_t st) {
+hipError_t launch_cast_weights(const float* wqkv, const float* wo, const float* w1, const float* w3, const float* w2,
+                               int C, int F, int G, uint16_t* oqkv, uint16_t* oo, uint16_t* o13, uint16_t* o2,
+                               hipStream_t st) {
   if (G <= 0 || G % 2 || (2 * F) % G || C % 8) return hipErrorInvalidValue;
-  cast_w13_kernel<<<blocks_for(2LL * F * (C / 8), 256), 256, 0, st>>>(w1, w3, F, C, G, reinterpret_cast<bf16_t*>(dst));
+  const long long cc = (long long)C * C / 8, cf = (long long)C * F / 8;
+  const CastWeights a{{wqkv, wo, w2, w1, w3}, {oqkv, oo, o2, o13}, {3 * cc, cc, cf, 2 * cf}, C, G};
+  cast_weights_kernel<<<blocks_for(4 * cc + 3 * cf, 256), 256, 0, st>>>(a);
   return hipGetLastError();
 }
 
-hipError_t launch_cast_t(const float* src, int rows, int cols, uint16_t* dst, long long ldd, hipStream_t st) {
-  if (rows % 32 || cols % 32) return hipErrorInvalidValue;
-  cast_t_kernel<<<dim3(cols / 32, rows / 32), 256, 0, st>>>(src, rows, cols, reinterpret_cast<bf16_t*>(dst), ldd);
+hipError_t launch_cast_weights_t(const float* wqkv, const float* wo, const float* w1, const float* w3, const float* w2,
+                                 int C, int F, uint16_t* oqkv, uint16_t* oo, uint16_t* o13, uint16_t* o2,
+                                 hipStream_t st) {
+  if (C % 32 || F % 32) return hipErrorInvalidValue;
+  const CastWeightsT a{{wqkv, wo, w1, w3, w2},
+                       {oqkv, oo, o13, o13 + F, o2},
+                       {3 * C, C, F, F, C},
+                       {C, C, C, C, F},
+                       {3 * C, C, 2 * F, 2 * F, C}};
+  cast_weights_t_kernel<<<(unsigned)((C / 32) * (4 * (C / 32) + 3 * (F / 32))), 256, 0, st>>>(a);
   return hipGetLastError();
 }
 

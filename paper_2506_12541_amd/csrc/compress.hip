@@ -13,11 +13,7 @@
 namespace bsa {
 namespace {
 
-constexpr int kWaves = 4;
-constexpr int kRB = 2;  // 16-row blocks per wave
-
-__global__ void block_valid_kernel(const uint8_t* valid, int total_blocks, int l, uint8_t* cvalid) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
+__device__ __forceinline__ void block_valid(const uint8_t* valid, int i, int total_blocks, int l, uint8_t* cvalid) {
   if (i >= total_blocks) return;
   uint8_t any = 0;
   if (valid == nullptr) {
@@ -27,14 +23,24 @@ __global__ void block_valid_kernel(const uint8_t* valid, int total_blocks, int l
   }
   cvalid[i] = any ? 1 : 0;
 }
+__global__ void block_valid_kernel(const uint8_t* valid, int total_blocks, int l, uint8_t* cvalid) {
+  block_valid(valid, blockIdx.x * blockDim.x + threadIdx.x, total_blocks, l, cvalid);
+}
 
-// W1 [l*d, d] f32 -> W1^T [d, l*d] in the storage type.
+// Before a forward launch: the first workgroups fill cvalid (none if it is not wanted), the
+// rest write one job's (grid.y) W1 [l*d, d] f32 as W1^T [d, l*d] in the storage type.
 template <typename T>
-__global__ void transpose_w1_kernel(const float* w1, int ld, int d, T* w1t) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
+__global__ void __launch_bounds__(256) mlp_prep_kernel(const uint8_t* valid, int valid_wgs, int total_blocks, int l,
+                                                       uint8_t* cvalid, int ld, int d, const float* w1a,
+                                                       const float* w1b, T* w1ta, T* w1tb) {
+  if ((int)blockIdx.x < valid_wgs) {
+    if (blockIdx.y == 0) block_valid(valid, blockIdx.x * 256 + threadIdx.x, total_blocks, l, cvalid);
+    return;
+  }
+  const int i = ((int)blockIdx.x - valid_wgs) * 256 + threadIdx.x;
   if (i >= ld * d) return;
-  int o = i / ld, r = i % ld;
-  w1t[i] = from_f32<T>(w1[(size_t)r * d + o]);
+  const int o = i / ld, r = i - o * ld;
+  (blockIdx.y ? w1tb : w1ta)[i] = from_f32<T>((blockIdx.y ? w1b : w1a)[(size_t)r * d + o]);
 }
 
 __device__ __forceinline__ float gelu_erf(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }
@@ -51,9 +57,13 @@ struct MlpFwdJob {
 };
 
 // One wave: kRB blocks of 16 rows (coarse tokens); the workgroup stages W2 and b1/b2.
-// grid.y picks the job (the key and value compressions share one launch).
-template <typename T, int HD>
-__global__ void __launch_bounds__(kWaves * 64) mlp_fwd_kernel(const uint8_t* valid, int H, int N, int l,
+// grid.y picks the job (the key and value compressions share one launch). Bound by HBM at
+// many rows, by the latency of the wave's chain of 32-deep chunks at few: four chunks are in
+// flight, and launches that would not fill the chip take one wave of 16 rows per workgroup
+// (1024 tokens x 8 heads of 64: 17 instead of 38 us; two chunks in flight and four waves of 32
+// rows in every launch).
+template <typename T, int HD, int kRB, int kWaves>
+__global__ void __launch_bounds__(kWaves * 64) mlp_fwd_kernel(const uint8_t* valid, int H, int lgb, int l,
                                                               long long rows, MlpFwdJob j0, MlpFwdJob j1) {
   const MlpFwdJob& job = blockIdx.y ? j1 : j0;
   const T* x = (const T*)job.x;
@@ -65,14 +75,14 @@ __global__ void __launch_bounds__(kWaves * 64) mlp_fwd_kernel(const uint8_t* val
   constexpr int OB = HD / 16;  // 16-wide output blocks
   __shared__ float w2s[HD * HD];
   __shared__ float b1s[HD], b2s[HD];
-  for (int i = threadIdx.x; i < HD * HD; i += blockDim.x) w2s[i] = w2[i];
-  for (int i = threadIdx.x; i < HD; i += blockDim.x) { b1s[i] = b1[i]; b2s[i] = b2[i]; }
+#pragma unroll 16
+  for (int i = threadIdx.x; i < HD * HD; i += kWaves * 64) w2s[i] = w2[i];
+  for (int i = threadIdx.x; i < HD; i += kWaves * 64) { b1s[i] = b1[i]; b2s[i] = b2[i]; }
   __syncthreads();
 
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   const int r = lane & 15, j = lane >> 4;
   const int ld = l * HD;
-  const int nblk = N / l;
   const long long row0 = ((long long)blockIdx.x * kWaves + wid) * (16 * kRB);
 
   f32x4 acc[kRB][OB];
@@ -89,25 +99,23 @@ __global__ void __launch_bounds__(kWaves * 64) mlp_fwd_kernel(const uint8_t* val
     long long row = row0 + rb * 16 + r;
     xrow[rb] = nullptr;
     vrow[rb] = nullptr;
-    if (row < rows) {
-      xrow[rb] = x + row * ld;
-      long long bh = row / nblk;
-      int blk = (int)(row % nblk);
-      int b = (int)(bh / H);
-      if (valid) vrow[rb] = valid + (size_t)b * N + (size_t)blk * l;
-    }
+    const long long rc = row < rows ? row : rows - 1;   // rows past the end repeat the last one
+    xrow[rb] = x + rc * ld;
+    if (valid)
+      vrow[rb] = valid + (((long long)((uint32_t)(rc >> lgb) / (uint32_t)H) << lgb) + (rc & ((1LL << lgb) - 1))) * l;
   }
   // Layer 1: pre^T[o][row] = sum_i W1^T[o][i] x[row][i]; A = W1^T, B = x^T. The operands of
-  // chunk c + 1 are loaded while chunk c is multiplied.
+  // the next PF chunks are loaded while one is multiplied.
   typedef typename Chunk<T>::type CT;
-  CT bx[2][kRB], aw[2][OB];
+  constexpr int PF = sizeof(T) == 2 ? 4 : 2;
+  CT bx[PF][kRB], aw[PF][OB];
   auto fetch = [&](int c, CT (&bxs)[kRB], CT (&aws)[OB]) {
     const int i0 = 32 * c + 8 * j;
     const int tok = i0 / HD;
 #pragma unroll
     for (int rb = 0; rb < kRB; ++rb) {
-      bxs[rb] = zero_chunk(bxs[rb]);
-      if (xrow[rb] && (vrow[rb] == nullptr || vrow[rb][tok])) bxs[rb] = load_chunk(xrow[rb] + i0);
+      bxs[rb] = load_chunk(xrow[rb] + i0);
+      if (vrow[rb] && !vrow[rb][tok]) bxs[rb] = zero_chunk(bxs[rb]);
     }
 #pragma unroll
     for (int ob = 0; ob < OB; ++ob) aws[ob] = load_chunk(w1t + (size_t)(16 * ob + r) * ld + i0);
@@ -119,12 +127,17 @@ __global__ void __launch_bounds__(kWaves * 64) mlp_fwd_kernel(const uint8_t* val
       for (int rb = 0; rb < kRB; ++rb) acc[rb][ob] = mma(aws[ob], bxs[rb], acc[rb][ob]);
   };
   const int nc = ld / 32;   // even: l*d is a multiple of 64
-  fetch(0, bx[0], aw[0]);
-  for (int c = 0; c < nc; c += 2) {
-    fetch(c + 1, bx[1], aw[1]);
-    mult(bx[0], aw[0]);
-    if (c + 2 < nc) fetch(c + 2, bx[0], aw[0]);
-    mult(bx[1], aw[1]);
+#pragma unroll
+  for (int u = 0; u < PF; ++u)
+    if (u < nc) fetch(u, bx[u], aw[u]);
+  for (int c = 0; c < nc; c += PF) {
+#pragma unroll
+    for (int u = 0; u < PF; ++u) {
+      if (c + u < nc) {
+        mult(bx[u], aw[u]);
+        if (c + u + PF < nc) fetch(c + u + PF, bx[u], aw[u]);
+      }
+    }
   }
 
 #pragma unroll
@@ -871,9 +884,13 @@ hipError_t compress_bwd_impl(const Dims& D, const CompressBwdJob* jobs, int n, c
 
 // n (1 or 2) compressions of the same shape; with the MLP they share one launch (grid.y).
 template <typename T, int HD>
-hipError_t compress_impl(const Dims& D, const CompressJob* jobs, int n, const uint8_t* valid, hipStream_t st) {
+hipError_t compress_impl(const Dims& D, const CompressJob* jobs, int n, const uint8_t* valid, uint8_t* cvalid,
+                         hipStream_t st) {
   const long long rows = D.cmp_rows();
+  const int total = D.B * (D.N / D.l), valid_wgs = cvalid ? (total + 255) / 256 : 0;
   if (D.pool == 1) {
+    if (cvalid)
+      hipLaunchKernelGGL(block_valid_kernel, dim3(valid_wgs), dim3(256), 0, st, valid, total, D.l, cvalid);
     const long long tot = rows * HD;
     for (int i = 0; i < n; ++i)
       hipLaunchKernelGGL(mean_pool_kernel<T>, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st,
@@ -885,25 +902,25 @@ hipError_t compress_impl(const Dims& D, const CompressJob* jobs, int n, const ui
   MlpFwdJob mj[2];
   for (int i = 0; i < n; ++i) {
     const CompressJob& c = jobs[i];
-    hipLaunchKernelGGL(transpose_w1_kernel<T>, dim3((ld * HD + 255) / 256), dim3(256), 0, st, c.phi.w1, ld, HD,
-                       (T*)c.w1t_ws);
     mj[i] = MlpFwdJob{c.x, c.w1t_ws, c.phi.b1, c.phi.w2, c.phi.b2, c.out, c.pre, c.out_lp, c.lp_scale};
   }
   if (n == 1) mj[1] = mj[0];
-  const long long per_wg = (long long)kWaves * 16 * kRB;
-  const unsigned grid = (unsigned)((rows + per_wg - 1) / per_wg);
-  hipLaunchKernelGGL((mlp_fwd_kernel<T, HD>), dim3(grid, (unsigned)n), dim3(kWaves * 64), 0, st, valid, D.H, D.N, D.l,
-                     rows, mj[0], mj[1]);
+  const int o = n - 1;
+  hipLaunchKernelGGL(mlp_prep_kernel<T>, dim3((unsigned)(valid_wgs + (ld * HD + 255) / 256), (unsigned)n), dim3(256), 0,
+                     st, valid, valid_wgs, total, D.l, cvalid, ld, HD, jobs[0].phi.w1, jobs[o].phi.w1,
+                     (T*)jobs[0].w1t_ws, (T*)jobs[o].w1t_ws);
+  const int lgb = __builtin_ctz((unsigned)(D.N / D.l));
+  const long long wgs = (rows + 127) / 128 * n;
+  if (wgs >= 512)   // two workgroups per CU of four waves of 32 rows
+    hipLaunchKernelGGL((mlp_fwd_kernel<T, HD, 2, 4>), dim3((unsigned)((rows + 127) / 128), (unsigned)n), dim3(256), 0,
+                       st, valid, D.H, lgb, D.l, rows, mj[0], mj[1]);
+  else
+    hipLaunchKernelGGL((mlp_fwd_kernel<T, HD, 1, 1>), dim3((unsigned)((rows + 15) / 16), (unsigned)n), dim3(64), 0, st,
+                       valid, D.H, lgb, D.l, rows, mj[0], mj[1]);
   return hipGetLastError();
 }
 
 }  // namespace
-
-hipError_t launch_block_valid(const Dims& D, const uint8_t* valid, uint8_t* cvalid, hipStream_t st) {
-  const int total = D.B * (D.N / D.l);
-  hipLaunchKernelGGL(block_valid_kernel, dim3((total + 255) / 256), dim3(256), 0, st, valid, total, D.l, cvalid);
-  return hipGetLastError();
-}
 
 int mlp_bwd_chunks_small(const Dims& D) {
   const long long rows = D.cmp_rows();
@@ -927,11 +944,10 @@ hipError_t launch_compress_bwd(const Dims& D, const CompressBwdJob* jobs, int n,
   return BSA_DISPATCH(compress_bwd_impl, D, jobs, n, valid, st);
 }
 
-hipError_t launch_compress_fwd(const Dims& D, const CompressJob* jobs, int n, const uint8_t* valid, hipStream_t st) {
+hipError_t launch_compress_fwd(const Dims& D, const CompressJob* jobs, int n, const uint8_t* valid, uint8_t* cvalid,
+                               hipStream_t st) {
   if (n < 1 || n > 2) return hipErrorInvalidValue;
-  if (D.bf16)
-    return D.d == 64 ? compress_impl<bf16_t, 64>(D, jobs, n, valid, st) : compress_impl<bf16_t, 32>(D, jobs, n, valid, st);
-  return D.d == 64 ? compress_impl<float, 64>(D, jobs, n, valid, st) : compress_impl<float, 32>(D, jobs, n, valid, st);
+  return BSA_DISPATCH(compress_impl, D, jobs, n, valid, cvalid, st);
 }
 
 }  // namespace bsa

@@ -44,7 +44,6 @@ hipError_t launch_permute(const void* src, const int* perm, int64_t n_real, int6
                           hipStream_t st);
 
 // compress.hip: compression phi of Eq. 5 and its backward
-hipError_t launch_block_valid(const Dims& D, const uint8_t* valid, uint8_t* cvalid, hipStream_t st);
 // One compression: x [B, H, N, d] in the storage type; out (float32) and out_lp (the rows in
 // the storage type, multiplied by lp_scale: the compressed keys of bf16 layers carry the
 // softmax scale times log2(e) there; see launch_cmp_fwd) are [B, H, N/l, d]; pre: the MLP's
@@ -58,8 +57,10 @@ struct CompressJob {
   void* w1t_ws;
   float lp_scale;
 };
-// n = 1 or 2 compressions of the same shape (the keys and values share one launch)
-hipError_t launch_compress_fwd(const Dims& D, const CompressJob* jobs, int n, const uint8_t* valid, hipStream_t st);
+// n = 1 or 2 compressions of the same shape (the keys and values share one launch); cvalid, if
+// given, is filled with the compression blocks' validity [B, N/l].
+hipError_t launch_compress_fwd(const Dims& D, const CompressJob* jobs, int n, const uint8_t* valid, uint8_t* cvalid,
+                               hipStream_t st);
 // the bf16 layers' scale of the compressed keys' storage-type copy
 inline float cmp_key_scale(const Dims& D) { return D.bf16 ? D.scale * 1.4426950408889634f : 1.0f; }
 
@@ -204,7 +205,7 @@ struct GemmMat {
   long long ld;
   int heads, lgn, lgd;
 };
-// kEpiSwigluFwd: B rows interleave W_1 and W_3 (launch_cast_w13); writes
+// kEpiSwigluFwd: B rows interleave W_1 and W_3 (launch_cast_weights); writes
 //   u | w (bf16 [M, 2 ffn], stacked) to out and silu(u) w (bf16 [M, ffn]) to out2.
 // kEpiSwigluBwd: the product is da [M, ffn]; with u | w from aux writes du | dw (bf16
 //   [M, 2 ffn]) to out.
@@ -239,10 +240,16 @@ hipError_t launch_splitk_sum(const float* part, int S, long long stride, long lo
 hipError_t launch_pack_qkv(const float* dq, const float* dk, const float* dv, long long rows, int C, int H, int lgn,
                            int lgd, uint16_t* out, hipStream_t st);
 hipError_t launch_cast_bf16(const float* src, long long n, uint16_t* dst, hipStream_t st);
-// [W_1; W_3] interleaved in groups of G rows for kEpiSwigluFwd; G = gemm_wave_cols(M, 2F)
-hipError_t launch_cast_w13(const float* w1, const float* w3, int F, int C, int G, uint16_t* dst, hipStream_t st);
+// The block's weights in bf16, one launch each: as the forward's products read them (W_1 and
+// W_3 interleaved), and transposed for the backward's (w13t: [C, 2F], W_1's columns first).
+hipError_t launch_cast_weights(const float* wqkv, const float* wo, const float* w1, const float* w3, const float* w2,
+                               int C, int F, int G, uint16_t* oqkv, uint16_t* oo, uint16_t* o13, uint16_t* o2,
+                               hipStream_t st);
+hipError_t launch_cast_weights_t(const float* wqkv, const float* wo, const float* w1, const float* w3, const float* w2,
+                                 int C, int F, uint16_t* oqkv, uint16_t* oo, uint16_t* o13, uint16_t* o2,
+                                 hipStream_t st);
+// W_1 and W_3 rows interleave in groups of G = gemm_wave_cols(M, 2F) for kEpiSwigluFwd
 int gemm_wave_cols(int M, int N);
-hipError_t launch_cast_t(const float* src, int rows, int cols, uint16_t* dst, long long ldd, hipStream_t st);
 
 // timing.cpp: optional per-phase HIP-event timing (see bsa_timing_enable in bsa.h)
 bool timing_on();
