@@ -21,6 +21,10 @@
 //      group; the selected ones are ordered by block index. Groups whose k*-th and next
 //      score are closer than those sums' error (about one in a thousand) are ranked again by
 //      float64 sums over the compressed keys, so the order is that of float64 throughout.
+//      Float32 layers score the listed blocks as sums of six bf16 matrix products of the
+//      operands' three parts instead (f32 accuracy), the scores that have always decided their
+//      selection: their outputs are compared at 1e-5, where one group decided the other way
+//      within the operands' rounding shows.
 // Error bound of a unit-vector score: f16 rounds each of the two operands by at most 2^-11
 // of its magnitude, so by Cauchy-Schwarz the score errs by at most 2^-10 (+ 2^-22); the
 // vectors are scaled by 2^7, which keeps what f16 cannot hold (below 2^-24, or below 2^-14
@@ -223,6 +227,24 @@ __device__ __forceinline__ float dot8(const f32x4 (&x)[NCH], const f32x4 (&y)[NC
   return sum8(s);
 }
 
+// hi = bf16(x), mid = bf16(x - hi), lo = bf16(x - hi - mid) (the differences are exact in f32).
+__device__ __forceinline__ void split3(const float* x, bf16x8& hi, bf16x8& mid, bf16x8& lo) {
+  const f32x8 v = load_chunk(x);
+  float h[8], md[8], lw[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const float ah = bf2f(f2bf(v[e]));
+    const float r1 = v[e] - ah;
+    const float am = bf2f(f2bf(r1));
+    h[e] = ah;
+    md[e] = am;
+    lw[e] = r1 - am;
+  }
+  hi = make_chunk<bf16_t>(h);
+  mid = make_chunk<bf16_t>(md);
+  lo = make_chunk<bf16_t>(lw);
+}
+
 // r times the score of a selection block in float64 from its r compressed keys, by eight lanes.
 template <int HD>
 __device__ __forceinline__ double score64(const float* __restrict__ q, const float* __restrict__ k, int r, int sub) {
@@ -352,8 +374,9 @@ __device__ __forceinline__ void vm_wait() {
   __builtin_amdgcn_s_waitcnt((V & 15) | ((V >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
+// SPLIT: the listed blocks' scores from bf16 parts on the matrix cores (float32 layers).
 // rr: compressed keys per selection block; lgls, lgm, lgg: log2 of l', m and g.
-template <int HD, int K>
+template <int HD, int K, bool SPLIT>
 __global__ void __launch_bounds__(kWaves * 64)
     select_kernel(const float* __restrict__ qpool, const float* __restrict__ ksum, const float* __restrict__ kcmp,
                   const uint16_t* __restrict__ kunit, const float* __restrict__ knorm, int N, int rr, int lgls, int lgm, int lgg,
@@ -555,6 +578,47 @@ __global__ void __launch_bounds__(kWaves * 64)
     total = 0;
   }
   const int sub = lane & 7;
+  if constexpr (SPLIT) {
+    // 16 / rr entries at a time: their keys are the rows, the wave's groups the columns of a
+    // 16 x 16 product, and the lane that holds an entry's rows of its own group's column
+    // takes the score (smaller products first)
+    bf16x8 qh[NCH], qm[NCH], ql[NCH];
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) split3(qb + (size_t)(live ? pg : 0) * HD + 32 * c + 8 * j, qh[c], qm[c], ql[c]);
+    const int lgr = 31 - __builtin_clz(rr), per = 16 >> lgr;
+#pragma unroll 1
+    for (int e0 = 0; e0 < total; e0 += per) {
+      const int kblk = (int)(flat[min(e0 + (r >> lgr), total - 1)] & 0xFFFFF);
+      const float* kr = kcmp + (((size_t)bh * nblk + kblk) * rr + (r & (rr - 1))) * HD + 8 * j;
+      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int c = 0; c < NCH; ++c) {
+        bf16x8 ah, am, al;
+        split3(kr + 32 * c, ah, am, al);
+        acc = mma(al, qh[c], acc);
+        acc = mma(ah, ql[c], acc);
+        acc = mma(am, qm[c], acc);
+        acc = mma(am, qh[c], acc);
+        acc = mma(ah, qm[c], acc);
+        acc = mma(ah, qh[c], acc);
+      }
+      float s = 0.f;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        s += acc[i];
+        if (((i + 1) & (rr - 1)) != 0) continue;
+        const int e = e0 + ((4 * j + i) >> lgr);
+        const uint32_t x = flat[min(e, total - 1)];
+        const int blk = (int)(x & 0xFFFFF);
+        s *= 1.0f / (float)rr;
+        if (e < total && (int)((x >> 20) & 15) == r && s > kNegInf && kn[blk] <= 0.f) {
+          const int at = atomicAdd(&cnt[r], 1);
+          if (at < kPerGroup) keys[r * kPerGroup + at] = make_key(s, blk);
+        }
+        s = 0.f;
+      }
+    }
+  } else {
   // four rounds of eight entries at a time, all their rows in flight together
   constexpr int PF = 4;
 #pragma unroll 1
@@ -584,6 +648,7 @@ __global__ void __launch_bounds__(kWaves * 64)
         if (at < kPerGroup) keys[grp * kPerGroup + at] = make_key(s, blk);
       }
     }
+  }
   }
   wave_sync();
   // each key's rank within its group: lane j takes the group's keys j, j + 4, ..., eight at
@@ -619,7 +684,7 @@ __global__ void __launch_bounds__(kWaves * 64)
   // groups whose k*-th and next score are closer than twice that are ranked in float64, lane t
   // holding the group's key t.
   uint64_t near = __builtin_amdgcn_ballot_w64(
-                      live && !over &&
+                      !SPLIT && live && !over &&
                       edge_s[wid][0][r] - edge_s[wid][1][r] <= 2.0f * 12.0f / (1 << 24) * qnorm * __int_as_float(nmax[r])) &
                   0xFFFFull;
   const int sub8 = lane >> 3;
@@ -733,7 +798,7 @@ hipError_t select_k(const Dims& D, const void* q, const uint8_t* valid, const fl
                      (const T*)q, valid, D.H, lg(D.N), lg(D.g), pool_n8, (int)pool_blocks, qpool, kcmp, cvalid,
                      lg(nblk), lg(R), blocks, ksum, kunit, knorm);
   const dim3 grid((ngroups + 16 * kWaves - 1) / (16 * kWaves), D.B * D.H);
-  hipLaunchKernelGGL((select_kernel<HD, K>), grid, dim3(kWaves * 64), 0, st, (const float*)qpool, R > 1 ? ksum : kcmp,
+  hipLaunchKernelGGL((select_kernel<HD, K, sizeof(T) == 4>), grid, dim3(kWaves * 64), 0, st, (const float*)qpool, R > 1 ? ksum : kcmp,
                      kcmp, (const uint16_t*)kunit, (const float*)knorm, D.N, R, lg(D.ls), lg(D.m), lg(D.g), D.mask_own,
                      D.k, sel);
   return hipGetLastError();

@@ -2,7 +2,8 @@
 blocks must equal the float64 oracle's bit for bit: many tied scores, keys that differ little
 from a large common vector (candidate lists overflow and groups are scanned exactly), equal
 keys, zero queries, one key far longer than the rest; every list width, block ratio and head
-dim of the kernel, from one partly filled key tile to several."""
+dim of the kernel, from one partly filled key tile to several, for bf16 layers and (head dim
+32) the float32 layers' scores from bf16 parts."""
 import numpy as np
 import pytest
 import torch
@@ -37,10 +38,11 @@ def _keys(kind, rng, nc, d):
 
 @pytest.mark.parametrize("padded", [False, True])
 @pytest.mark.parametrize("kind", ["ties", "common", "equal", "zero_q", "outlier"])
-@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "-".join(map(str, s)))
-def test_select_whole_numbers(shape, kind, padded):
+@pytest.mark.parametrize("shape,f32", [(s, False) for s in SHAPES] + [(s, True) for s in SHAPES if s[-1] == 32],
+                         ids=lambda s: "-".join(map(str, s)) if isinstance(s, tuple) else ("f32" if s else "bf16"))
+def test_select_whole_numbers(shape, f32, kind, padded):
     n, m, l, ls, kk, g, d = shape
-    print(f"select {shape} {kind} padded={padded}", flush=True)
+    print(f"select {shape} f32={f32} {kind} padded={padded}", flush=True)
     rng = np.random.default_rng([n, d, g, len(kind)])
     B, H = 2, 2
     q = rng.integers(-3, 4, (B, H, n, d)).astype(np.float64)
@@ -53,9 +55,9 @@ def test_select_whole_numbers(shape, kind, padded):
         valid[:, n // 4:n // 4 + 4 * ls] = False
         valid[:, -max(ls, g):] = False
     p = gb.Params(batch=B, n=n, heads=H, head_dim=d, ball_size=m, cmp_block=l, slc_block=ls, topk=kk, group_size=g,
-                  kv_pool=gb.BSA_POOL_MEAN)
+                  kv_pool=gb.BSA_POOL_MEAN, dtype=gb.BSA_F32 if f32 else gb.BSA_BF16)
     dev = lambda a, t: torch.from_numpy(a).to("cuda").to(t)
-    qd, kd = dev(q, torch.bfloat16), dev(k, torch.bfloat16)
+    qd, kd = dev(q, p.torch_dtype), dev(k, p.torch_dtype)
     gate = torch.zeros((B, n, 3), device="cuda")
     _, saved = gb.forward(p, qd, kd, kd, dev(valid, torch.uint8) if padded else None, gate, None, None)
     sel = saved.sel_idx.cpu().numpy()
