@@ -12,15 +12,16 @@ constexpr float kNormEps = 1e-6f;
 
 // ---- matrix products C[M, N] = sum_k A(m, k) B(n, k) ----
 //
-// Workgroup tiles of 256 x 256 (eight waves of 64 x 128) or 128 x 128 (four waves of
-// 64 x 64) in 16 x 16 accumulator tiles, contraction tiles of 64, two LDS stages filled by
-// direct global->LDS loads while the other stage feeds the matrix cores (launch_gemm picks
+// Workgroup tiles of 256 x 256 (eight waves of 64 x 128, contraction tiles of 32 in four LDS
+// stages), 128 x 128 (four waves of 64 x 64, contraction tiles of 64 in two) or 64 x 64 (four
+// waves of 32 x 32, contraction tiles of 64 in four) in 16 x 16 accumulator tiles. Stages are
+// filled by direct global->LDS loads while another feeds the matrix cores (launch_gemm picks
 // the tile from the shape).
 //   plain form (trans = false): A [M, K] and B [N, K], contraction index fastest; tiles are
-//     staged as 128 rows x 64 (row fragments read with ds_read_b128);
+//     staged as rows x contraction (row fragments read with ds_read_b128);
 //   transposed form (trans = true): A [K, M] and B [K, N], the contraction runs over their
-//     rows (the weight gradients dW = dY^T X over tokens); tiles are staged as 64 rows x 128
-//     and read with transposing LDS reads (ds_read_b64_tr_b16).
+//     rows (the weight gradients dW = dY^T X over tokens); tiles are staged as contraction
+//     x columns and read with transposing LDS reads (ds_read_b64_tr_b16).
 // Accumulator lane L holds C[m0 + L % 16][n0 + 4 (L / 16) + e], e = 0..3 (the B fragment
 // is the first MFMA operand).
 
