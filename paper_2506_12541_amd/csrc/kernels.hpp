@@ -66,11 +66,12 @@ inline float cmp_key_scale(const Dims& D) { return D.bf16 ? D.scale * 1.44269504
 
 // select.hip: pooled-query block scores and group top-k (Eq. 6, 7, 10-12, 14)
 // qpool: B*H*(N/g)*d floats of coarse queries; written here (group mean of Eq. 11) unless
-// `given`, when it already holds them (Eq. 13); kplanes: 3 * B*H*(N/l)*d 16-bit words of
-// workspace (the compressed keys as f16 unit vectors, then their norms)
+// `given`, when it already holds them (Eq. 13); kunit: select_ws_bytes of workspace (the
+// selection blocks' summed keys as f16 unit vectors and in f32, and their norms)
 hipError_t launch_select_topk(const Dims& D, const void* q, const uint8_t* valid, const float* kcmp,
-                              const uint8_t* cvalid, int* sel, float* qpool, bool given, uint16_t* kplanes,
+                              const uint8_t* cvalid, int* sel, float* qpool, bool given, uint16_t* kunit,
                               hipStream_t st);
+size_t select_ws_bytes(const Dims& D);
 
 // attn_fwd.hip: the three attention branches (Eq. 3, 5, 8) and the gate (Eq. 9)
 hipError_t launch_ball_fwd(const Dims& D, const void* q, const void* k, const void* v, const uint8_t* valid,

@@ -6,38 +6,48 @@
 // k* best blocks (higher score first, lower block index on equal scores), stored in
 // ascending block order with -1 in unused slots.
 //
-// The mean of a block's scores is the score of its keys' sum (over r): the keys are summed
-// over each block first. The score matrix (N/g x N/l' per head) is never stored, and only
-// the few blocks that can be among the k* best are scored in f32. A workgroup owns 64
-// groups of one head, 16 per wave; the block keys are streamed twice in tiles shared
-// by its waves:
+// Scores are the f32 sums of six bf16 matrix products of the operands' three parts (x = hi +
+// mid + lo up to 2^-27 |x|; the products whose weight reaches 2^-16), key by key, and a block's
+// score is the mean of its keys': f32 accuracy, whatever the layer's storage type, so equal
+// scores (and those closer than f32 rounding) rank by block index alike in every path below.
+//
+// The score matrix (N/g x N/l' per head) is never stored, and only the few blocks that can be
+// among the k* best are scored. A workgroup owns 64 groups of one head, 16 per wave; the block
+// keys (the sum of a block's compressed keys) are streamed twice in tiles shared by its waves:
 //   1. Scores from unit vectors in f16 (one MFMA per 32 dimensions), times the key's norm,
 //      less a bound on their error: a lower bound of each block's score. Every lane keeps
 //      the largest of each of a few disjoint sets of blocks; the k*-th largest of a
 //      group's set maxima bounds its k*-th best score from below.
 //   2. The same scores plus the bound: blocks that reach the group's threshold (about
 //      1.15 k* of them; every block of the k* best is one) go to the wave's list.
-//   3. The listed blocks are scored with f32 products and sums and ranked within their
-//      group; the selected ones are ordered by block index. Groups whose k*-th and next
-//      score are closer than those sums' error (about one in a thousand) are ranked again by
-//      float64 sums over the compressed keys, so the order is that of float64 throughout.
-//      Float32 layers score the listed blocks as sums of six bf16 matrix products of the
-//      operands' three parts instead (f32 accuracy), the scores that have always decided their
-//      selection: their outputs are compared at 1e-5, where one group decided the other way
-//      within the operands' rounding shows.
-// Error bound of a unit-vector score: f16 rounds each of the two operands by at most 2^-11
-// of its magnitude, so by Cauchy-Schwarz the score errs by at most 2^-10 (+ 2^-22); the
+//   3. The listed blocks are scored by f32 dots of the pooled query and the summed keys and
+//      ranked within their group. Groups where a block of the k* best lies above one of the rest
+//      by no more than the errors of their scores (about one in thirty) are ranked again by the
+//      six products, 16 keys at a time as the rows of a product whose columns are the wave's
+//      groups; elsewhere the six products give the same k* best. The selected blocks are ordered
+//      by block index.
+// Groups whose list overflows (e.g. all scores equal) and zero queries are left over: their
+// workgroup then streams the compressed keys once, in three bf16 parts through LDS, scores
+// every block for them and keeps a running top-k per lane, merged at the end.
+// Error of a unit-vector score against the score it stands for, in units of |q| times the
+// block's norm bound w = max(|sum of its keys|, sum of its keys' norms / 16) (an upper bound of
+// the vector's length serves as its scale): f16 rounds each of the two operands by at most 2^-11
+// of its magnitude, so by Cauchy-Schwarz the product errs by at most 2^-10 (+ 2^-22); the
 // vectors are scaled by 2^7, which keeps what f16 cannot hold (below 2^-24, or below 2^-14
-// if subnormal numbers were flushed) under 2^-17; f32 sums and norms add under 2^-17.
-// kUnitErr is 1.1 * 2^-10. A group whose list overflows (e.g. all scores equal) is scanned
-// in float64 by its wave.
+// if subnormal numbers were flushed) under 2^-17; f32 sums and norms add under 2^-17. The score
+// from six products errs by at most 2^-15 |q| (sum of the keys' norms) (224 sums of at most
+// |q||k| in two 32-dimension steps, each off by an ulp at most), so by 2^-11 |q| w. kUnitErr
+// is 1.6 * 2^-10.
+// A dot errs by at most 12 * 2^-24 |q| |sum of the keys| (11 roundings, one in the summed key);
+// kDotErr adds the six products' 2^-15.
 // What bounds it: VALU issue (75 instructions per 64 blocks and 16 groups in both streams,
 // about 3000 per 16 groups for the ranking), and with few waves per SIMD the latency of each
-// tile. Measured with d = 64, r = 2, k* = 16 (in brackets: one stream of all compressed keys
-// with f32-accurate scores from six MFMAs per 32 dimensions and a 16-deep list in every lane):
-// 65536 queries x 8 heads in groups of 16 0.074 ms (0.250), one by one 0.82 ms (2.96);
-// 2^20 queries x 16 heads in groups of 32 4.0 ms (15.4). Two sets of 16 groups per wave, which
-// halve the LDS reads per group, were slower (0.109 and 0.86 ms: fewer waves).
+// tile. Measured with its preparation, k* = 16, d = 64, r = 2, N(0, 1) tensors (in brackets: one
+// stream of all compressed keys with the six products and a 16-deep list in every lane): 65536
+// queries x 8 heads in groups of 16 0.10 ms (0.27), one by one 0.94 (2.73); 2^20 queries x 16
+// heads in groups of 32 5.1 ms (15.7). Two sets of 16 groups per wave, which halve the LDS reads
+// per group, left fewer waves (the kernel alone at 65536 queries 0.109 instead of 0.074 ms, one
+// by one 0.86 instead of 0.82). With every group left over the three take 0.39, 4.5 and 28 ms.
 #include <type_traits>
 
 #include "common.hpp"
@@ -53,7 +63,9 @@ constexpr int kRing = 4, kAhead = 3;     // key tiles in LDS; of these, loads in
 constexpr int kPerGroup = 64;             // listed blocks of a group
 constexpr int kNoBlock = 0x7FFFFFFF;
 constexpr float kUnit = 128.0f;           // scale of the f16 unit vectors
-constexpr float kUnitErr = 1.1f / 1024 * kUnit * kUnit;
+constexpr float kUnitErr = 1.6f / 1024 * kUnit * kUnit;
+constexpr float kSpread = 1.0f / 16;      // least norm bound of a block, over the sum of its keys' norms
+constexpr float kDotErr = 1.0f / 32768 + 12.0f / (1 << 24);
 
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
@@ -69,26 +81,42 @@ __device__ __forceinline__ float key_score(uint64_t key) {
   return __uint_as_float((b & 0x80000000u) ? (b & 0x7FFFFFFFu) : ~b);
 }
 
-__device__ __forceinline__ uint64_t make_key(float score, int blk) {
-  return ((uint64_t)ordered_bits(score) << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)blk);
+// Keys order by score, then lower block first (blocks have 20 bits: N <= 2^24, l' >= 16); the low
+// nine bits name the block's entry in its wave's list.
+__device__ __forceinline__ uint64_t make_key(float score, int blk, int entry = 0) {
+  return ((uint64_t)ordered_bits(score) << 32) | (uint64_t)(((0xFFFFFu - (uint32_t)blk) << 9) + (uint32_t)entry);
+}
+__device__ __forceinline__ int key_block(uint64_t key) { return (int)(0xFFFFFu - ((uint32_t)key >> 9)); }
+
+// Insert x into the descending list (keys are unique, x > lst[K - 1]): every entry compares
+// with x independently, then each slot keeps its entry, takes x, or takes its upper
+// neighbour (slots are rewritten from the bottom, so the neighbour is still the old one).
+template <int K>
+__device__ __forceinline__ void topk_insert(uint64_t (&lst)[K], uint64_t x) {
+  bool gt[K];
+#pragma unroll
+  for (int t = 0; t < K; ++t) gt[t] = lst[t] > x;
+#pragma unroll
+  for (int t = K - 1; t >= 1; --t) lst[t] = gt[t] ? lst[t] : (gt[t - 1] ? x : lst[t - 1]);
+  lst[0] = gt[0] ? lst[0] : x;
 }
 
-// x of the lanes r, r + 16, r + 32, r + 48 (r = L mod 16), in that order
-__device__ __forceinline__ void group_gather(int x, int (&out)[4]) {
-  const auto p = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)x, false, false);
-  const auto e = __builtin_amdgcn_permlane32_swap(p[0], p[0], false, false);   // rows 0, 2
-  const auto o = __builtin_amdgcn_permlane32_swap(p[1], p[1], false, false);   // rows 1, 3
-  out[0] = (int)e[0];
-  out[1] = (int)o[0];
-  out[2] = (int)e[1];
-  out[3] = (int)o[1];
+// Over the group's four lanes L, L ^ 16, L ^ 32, L ^ 48.
+__device__ __forceinline__ uint64_t group_min(uint64_t x) {
+#pragma unroll
+  for (int o = 16; o < 64; o <<= 1) {
+    const uint64_t y = __shfl_xor(x, o, 64);
+    x = x < y ? x : y;
+  }
+  return x;
 }
-
-// Sum of an int over the group's four lanes.
-__device__ __forceinline__ int group_sum(int x) {
-  int v[4];
-  group_gather(x, v);
-  return (v[0] + v[1]) + (v[2] + v[3]);
+__device__ __forceinline__ uint64_t group_max(uint64_t x) {
+#pragma unroll
+  for (int o = 16; o < 64; o <<= 1) {
+    const uint64_t y = __shfl_xor(x, o, 64);
+    x = x > y ? x : y;
+  }
+  return x;
 }
 
 // Rows of HD values, one 8-value chunk per lane of HD / 8 lanes, to f16 unit vectors times
@@ -113,18 +141,19 @@ __device__ __forceinline__ float unit_scale(const float* x, int n, int& e, MaxF 
 // Preparation of the selection in one launch. Workgroups below `pool_blocks`: pooled
 // queries (Eq. 11), q_p = (1/g) * sum of the group's real queries in slot order, eight
 // channels per thread (HBM: one read of Q in 16-byte loads; a thread per channel took 33
-// instead of 14 us at 65536 queries x 8 heads of 64). The others: every selection block's
-// compressed keys summed (ksum, not written for r = 1: kcmp holds them), as f16 unit vectors
-// and negated norms, HD / 8 threads per block; blocks without a real token get the norm NaN,
-// which no comparison passes. A head's norms are padded with
-// NaN to a whole tile of the selection kernel.
+// instead of 14 us at 65536 queries x 8 heads of 64). The others: the sum of every selection
+// block's compressed keys in f32 (ksum, not written for r = 1: kcmp holds them) and, over its norm
+// bound (see above), in f16, the negated norm bound and the sum of its keys' norms (kabs), HD / 8
+// threads per block; blocks without a real token get the norms NaN, which no comparison passes.
+// A head's norm bounds are padded with NaN to a whole tile of the selection kernel.
 template <typename T, int HD>
 __global__ void __launch_bounds__(256) select_prep_kernel(const T* __restrict__ q, const uint8_t* __restrict__ valid,
                                                           int H, int lgn, int lgg, long long pool_n8, int pool_blocks,
                                                           float* __restrict__ qpool, const float* __restrict__ kcmp,
                                                           const uint8_t* __restrict__ cvalid, int lgb, int lgr,
-                                                          long long blocks, float* __restrict__ ksum,
-                                                          uint16_t* __restrict__ kunit, float* __restrict__ knorm) {
+                                                          long long blocks, uint16_t* __restrict__ kunit,
+                                                          float* __restrict__ knorm, float* __restrict__ kabs,
+                                                          float* __restrict__ ksum) {
   constexpr int CPR = HD / 8;
   if ((int)blockIdx.x < pool_blocks) {
     const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
@@ -155,14 +184,20 @@ __global__ void __launch_bounds__(256) select_prep_kernel(const T* __restrict__ 
   if (i >= blocks * CPR) return;   // whole rows: 256 is a multiple of CPR
   const long long blk = i / CPR;   // (b*H + h) * nblk + block, nblk = 2^lgb
   const int r = 1 << lgr;
-  double sum[8];   // rounded once: within 2^-24 of the true sum, whatever cancels
+  double sum[8], sq = 0.0;   // rounded once: within 2^-24 of the true sum, whatever cancels
 #pragma unroll
   for (int e = 0; e < 8; ++e) sum[e] = 0.0;
   for (int k = 0; k < r; ++k) {
     const f32x8 v = load_chunk(kcmp + ((blk << lgr) + k) * HD + 8 * (i % CPR));
 #pragma unroll
-    for (int e = 0; e < 8; ++e) sum[e] += (double)v[e];
+    for (int e = 0; e < 8; ++e) {
+      sum[e] += (double)v[e];
+      sq = fma((double)v[e], (double)v[e], sq);
+    }
   }
+#pragma unroll
+  for (int o = 1; o < CPR; o <<= 1) sq += __shfl_xor(sq, o, 64);
+  const float norms = (float)sqrt((double)r * sq), least = kSpread * norms;   // sum of r norms <= sqrt(r sum of squares)
   float a[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) a[e] = (float)sum[e];
@@ -184,7 +219,7 @@ __global__ void __launch_bounds__(256) select_prep_kernel(const T* __restrict__ 
         return x;
       });
   const float nrm = sqrtf(ss);
-  const float rn = ss == 0.f ? 0.f : kUnit / nrm;
+  const float rn = ss == 0.f ? 0.f : kUnit / fmaxf(nrm, ldexpf(least, -ex));
   f16x8 u;
   f32x8 o;
 #pragma unroll
@@ -195,9 +230,10 @@ __global__ void __launch_bounds__(256) select_prep_kernel(const T* __restrict__ 
   *reinterpret_cast<f16x8*>(kunit + 8 * i) = u;
   if (r > 1) *reinterpret_cast<f32x8*>(ksum + 8 * i) = o;
   if (i % CPR == 0) {
+    kabs[blk] = any ? norms : __builtin_nanf("");
     float* kn = knorm + (blk >> lgb) * (long long)max(1 << lgb, 4096 / HD);
     const int t = (int)(blk & ((1LL << lgb) - 1));
-    kn[t] = any ? -ldexpf(nrm, ex) : __builtin_nanf("");
+    kn[t] = any ? -fmaxf(ldexpf(nrm, ex), least) : __builtin_nanf("");
     for (int p = t + (1 << lgb); p < 4096 / HD; p += 1 << lgb) kn[p] = __builtin_nanf("");
   }
 }
@@ -228,8 +264,7 @@ __device__ __forceinline__ float dot8(const f32x4 (&x)[NCH], const f32x4 (&y)[NC
 }
 
 // hi = bf16(x), mid = bf16(x - hi), lo = bf16(x - hi - mid) (the differences are exact in f32).
-__device__ __forceinline__ void split3(const float* x, bf16x8& hi, bf16x8& mid, bf16x8& lo) {
-  const f32x8 v = load_chunk(x);
+__device__ __forceinline__ void split3(const f32x8& v, bf16x8& hi, bf16x8& mid, bf16x8& lo) {
   float h[8], md[8], lw[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
@@ -243,23 +278,6 @@ __device__ __forceinline__ void split3(const float* x, bf16x8& hi, bf16x8& mid, 
   hi = make_chunk<bf16_t>(h);
   mid = make_chunk<bf16_t>(md);
   lo = make_chunk<bf16_t>(lw);
-}
-
-// r times the score of a selection block in float64 from its r compressed keys, by eight lanes.
-template <int HD>
-__device__ __forceinline__ double score64(const float* __restrict__ q, const float* __restrict__ k, int r, int sub) {
-  double s = 0.0;
-  for (int i = 0; i < r; ++i)
-#pragma unroll
-    for (int c = 0; c < HD; c += 32) {
-      const f32x4 x = *reinterpret_cast<const f32x4*>(q + c + 4 * sub);
-      const f32x4 y = *reinterpret_cast<const f32x4*>(k + i * HD + c + 4 * sub);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) s = fma((double)x[e], (double)y[e], s);
-    }
-#pragma unroll
-  for (int o = 1; o < 8; o <<= 1) s += __shfl_xor(s, o);
-  return s;
 }
 
 // a[0 .. n) sorted descending from a bitonic sequence (n a power of two).
@@ -291,24 +309,19 @@ __device__ __forceinline__ void sort_desc(float (&a)[N]) {
         }
 }
 
-// The K-th largest of the group's 4 NB values, NB per lane (K = NB or 2 NB).
-template <int K, int NB>
-__device__ __forceinline__ float group_kth(float (&a)[NB]) {
-  static_assert(NB == K || 2 * NB == K, "values per lane");
+// The K-th largest of the group's 4 K values, K per lane.
+template <int K>
+__device__ __forceinline__ float group_kth(float (&a)[K]) {
   sort_desc(a);
   float t[K];
 #pragma unroll
-  for (int i = 0; i < NB; ++i) {
-    float lo, hi;   // the lane pair's lists: values of the even and of the odd 16-lane row
+  for (int i = 0; i < K; ++i) {   // the best K of the lane pair's lists, bitonic
+    float lo, hi, lo2, hi2;
     lo = xor16_pair(a[i], hi);
-    float lo2, hi2;
-    lo2 = xor16_pair(a[NB - 1 - i], hi2);
-    if (NB == K) {
-      t[i] = fmaxf(lo, hi2);   // the best K of both lists, bitonic
-    } else {
-      t[i] = lo;               // both lists: descending, then ascending
-      t[NB + i] = hi2;
-    }
+    lo2 = xor16_pair(a[K - 1 - i], hi2);
+    (void)hi;
+    (void)lo2;
+    t[i] = fmaxf(lo, hi2);
   }
   bitonic_merge(t);
   float best = __builtin_huge_valf();
@@ -374,26 +387,23 @@ __device__ __forceinline__ void vm_wait() {
   __builtin_amdgcn_s_waitcnt((V & 15) | ((V >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
-// SPLIT: the listed blocks' scores from bf16 parts on the matrix cores (float32 layers).
-// rr: compressed keys per selection block; lgls, lgm, lgg: log2 of l', m and g.
-template <int HD, int K, bool SPLIT>
+// lgr: log2 of the compressed keys per selection block; lgls, lgm, lgg: log2 of l', m and g.
+template <int HD, int K>
 __global__ void __launch_bounds__(kWaves * 64)
     select_kernel(const float* __restrict__ qpool, const float* __restrict__ ksum, const float* __restrict__ kcmp,
-                  const uint16_t* __restrict__ kunit, const float* __restrict__ knorm, int N, int rr, int lgls, int lgm, int lgg,
-                  int mask_own, int kk, int* __restrict__ sel) {
+                  const uint16_t* __restrict__ kunit, const float* __restrict__ knorm, const float* __restrict__ kabs, int N, int lgr, int lgls, int lgm, int lgg, int mask_own, int kk,
+                  int* __restrict__ sel) {
   constexpr int NCH = HD / 32;
   constexpr int KT = 4096 / HD;     // blocks per staged tile (8 KB)
   constexpr int GW = 16 * kWaves;   // groups per workgroup
   constexpr int NST = KT / 16;      // 16-block sub-tiles of a tile
   constexpr int NC = 4 * NST;       // blocks per lane and tile
-  constexpr int NB = K;             // sets per lane: a block's set is its place in the tile
-  static_assert(NC % NB == 0, "sets");
+  static_assert(NC % K == 0, "sets");   // K sets per lane: a block's set is its place in the tile
   // a ring of key tiles (8 KB each) and their norms, kAhead of them in flight
   __shared__ __attribute__((aligned(1024))) bf16_t ring[kRing][KT * HD];
   __shared__ __attribute__((aligned(256))) float nring[kRing][KT];
   __shared__ uint32_t flat_s[kWaves][kFlat];   // block | group << 20
-  __shared__ int cnt_s[kWaves][16], nmax_s[kWaves][16];   // a group's keys, their largest norm (as bits)
-  __shared__ float edge_s[kWaves][2][16];                 // a group's k*-th and next score
+  __shared__ int cnt_s[kWaves][16];            // a group's keys
   __shared__ __attribute__((aligned(16))) int best_s[kWaves][16 * 16];
   static_assert(sizeof(ring) >= kWaves * 16 * kPerGroup * 8, "reused tiles");
   const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -404,7 +414,9 @@ __global__ void __launch_bounds__(kWaves * 64)
   const int nblk = N >> lgls;
   const bf16_t* ku = kunit + (size_t)bh * nblk * HD;
   const float* kn = knorm + (size_t)bh * max(nblk, KT);   // negated; padded with NaN to a tile
-  const float* kc = ksum + (size_t)bh * nblk * HD;
+  const float* ka = kabs + (size_t)bh * nblk;
+  const float* ks = ksum + (size_t)bh * nblk * HD;
+  const float* kc = kcmp + ((size_t)bh * nblk << lgr) * HD;
   const float* qb = qpool + (size_t)bh * ngroups * HD;
 
   // tiles u = 0 .. 2 nt - 1: the keys once per pass. Every wave loads its share of a tile
@@ -438,7 +450,7 @@ __global__ void __launch_bounds__(kWaves * 64)
   const int pg = p0 + r;
   const bool live = pg < ngroups;
   f16x8 qf[NCH];
-  bool over;   // the group is scanned whole instead (a zero query: all blocks tie)
+  bool zero, over;   // over: the group's scores are all formed instead (a zero query: all blocks tie)
   float qnorm;
   {
     const float* qr = qb + (size_t)(live ? pg : 0) * HD;
@@ -451,8 +463,9 @@ __global__ void __launch_bounds__(kWaves * 64)
     }
     int ex;
     const float ss = unit_scale(a, 8 * NCH, ex, [](float x) { return col_max(x); }, [](float x) { return col_sum(x); });
-    over = live && ss == 0.f;
     qnorm = ldexpf(sqrtf(ss), ex);
+    zero = ss == 0.f;
+    over = live && zero;
     const float rn = ss == 0.f ? 0.f : kUnit / sqrtf(ss);
 #pragma unroll
     for (int c = 0; c < NCH; ++c)
@@ -493,29 +506,29 @@ __global__ void __launch_bounds__(kWaves * 64)
   // the block of index t in a tile that starts at block t0
   auto block_of = [&](int t0, int t) { return t0 + 16 * (t / 4) + 4 * j + t % 4; };
 
-  float top[NB];   // minus each set's largest lower bound
+  float top[K];   // minus each set's largest lower bound
 #pragma unroll
-  for (int t = 0; t < NB; ++t) top[t] = __builtin_huge_valf();
+  for (int t = 0; t < K; ++t) top[t] = __builtin_huge_valf();
 #pragma unroll 1
   for (int u = 0; u < nt; ++u) {
     advance(u);
     const int t0 = u * KT;
     if (t0 < wave_hi && t0 + KT > wave_lo)
       scores(u, -kUnitErr, [&](int t, float n, float sc) {
-        float& x = top[t % NB];
+        float& x = top[t % K];
         x = fminf(x, own(block_of(t0, t)) ? __builtin_huge_valf() : n * sc);
       });
     else
       scores(u, -kUnitErr, [&](int t, float n, float sc) {
-        float& x = top[t % NB];
+        float& x = top[t % K];
         x = fminf(x, n * sc);
       });
   }
   // just below the k*-th largest lower bound (-inf: fewer than K sets hold a block), so that
   // blocks that reach it lie above; NaN passes no block
 #pragma unroll
-  for (int t = 0; t < NB; ++t) top[t] = -top[t];
-  float thr = group_kth<K, NB>(top);
+  for (int t = 0; t < K; ++t) top[t] = -top[t];
+  float thr = group_kth<K>(top);
   thr = thr == 0.f ? __int_as_float((int)0x80000001)
                    : thr > kNegInf ? __int_as_float(__float_as_int(thr) + (thr > 0.f ? -1 : 1)) : thr;
   thr = live && !over ? thr : __builtin_nanf("");
@@ -560,17 +573,11 @@ __global__ void __launch_bounds__(kWaves * 64)
   }
   __syncthreads();   // the tiles are free: they hold the groups' lists from here
 
-  // f32 scores, each to its group's list as a key (in no particular order)
+  // the listed blocks' dots, each to its group's list as a key (in no particular order)
   uint64_t* keys = reinterpret_cast<uint64_t*>(ring) + wid * 16 * kPerGroup;   // [group][kPerGroup]
   int* cnt = cnt_s[wid];
   int* best16 = best_s[wid];   // [group][16] the k* best blocks
-  int* nmax = nmax_s[wid];
-  if (lane < 16) {
-    cnt[lane] = 0;
-    nmax[lane] = 0;
-    edge_s[wid][0][lane] = __builtin_huge_valf();
-    edge_s[wid][1][lane] = kNegInf;
-  }
+  if (lane < 16) cnt[lane] = 0;
   *reinterpret_cast<int4*>(best16 + 4 * lane) = make_int4(kNoBlock, kNoBlock, kNoBlock, kNoBlock);
   wave_sync();
   if (total > kFlat) {
@@ -578,77 +585,38 @@ __global__ void __launch_bounds__(kWaves * 64)
     total = 0;
   }
   const int sub = lane & 7;
-  if constexpr (SPLIT) {
-    // 16 / rr entries at a time: their keys are the rows, the wave's groups the columns of a
-    // 16 x 16 product, and the lane that holds an entry's rows of its own group's column
-    // takes the score (smaller products first)
-    bf16x8 qh[NCH], qm[NCH], ql[NCH];
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) split3(qb + (size_t)(live ? pg : 0) * HD + 32 * c + 8 * j, qh[c], qm[c], ql[c]);
-    const int lgr = 31 - __builtin_clz(rr), per = 16 >> lgr;
-#pragma unroll 1
-    for (int e0 = 0; e0 < total; e0 += per) {
-      const int kblk = (int)(flat[min(e0 + (r >> lgr), total - 1)] & 0xFFFFF);
-      const float* kr = kcmp + (((size_t)bh * nblk + kblk) * rr + (r & (rr - 1))) * HD + 8 * j;
-      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int c = 0; c < NCH; ++c) {
-        bf16x8 ah, am, al;
-        split3(kr + 32 * c, ah, am, al);
-        acc = mma(al, qh[c], acc);
-        acc = mma(ah, ql[c], acc);
-        acc = mma(am, qm[c], acc);
-        acc = mma(am, qh[c], acc);
-        acc = mma(ah, qm[c], acc);
-        acc = mma(ah, qh[c], acc);
-      }
-      float s = 0.f;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        s += acc[i];
-        if (((i + 1) & (rr - 1)) != 0) continue;
-        const int e = e0 + ((4 * j + i) >> lgr);
-        const uint32_t x = flat[min(e, total - 1)];
-        const int blk = (int)(x & 0xFFFFF);
-        s *= 1.0f / (float)rr;
-        if (e < total && (int)((x >> 20) & 15) == r && s > kNegInf && kn[blk] <= 0.f) {
-          const int at = atomicAdd(&cnt[r], 1);
-          if (at < kPerGroup) keys[r * kPerGroup + at] = make_key(s, blk);
-        }
-        s = 0.f;
-      }
-    }
-  } else {
   // four rounds of eight entries at a time, all their rows in flight together
   constexpr int PF = 4;
 #pragma unroll 1
   for (int e0 = 0; e0 < total; e0 += 8 * PF) {
     uint32_t x[PF];
     f32x4 qv[PF][NCH], kv[PF][NCH];
-    float n[PF];
+    float a[PF];
 #pragma unroll
     for (int i = 0; i < PF; ++i) x[i] = flat[min(e0 + 8 * i + (lane >> 3), total - 1)];
 #pragma unroll
     for (int i = 0; i < PF; ++i) {
-      const int grp = (int)((x[i] >> 20) & 15), blk = (int)(x[i] & 0xFFFFF);
+      const int grp = (int)((x[i] >> 20) & 15), blk = min((int)(x[i] & 0xFFFFF), nblk - 1);
 #pragma unroll
       for (int c = 0; c < NCH; ++c) {
         qv[i][c] = *reinterpret_cast<const f32x4*>(qb + (size_t)(p0 + grp) * HD + 32 * c + 4 * sub);
-        kv[i][c] = *reinterpret_cast<const f32x4*>(kc + (size_t)blk * HD + 32 * c + 4 * sub);
+        kv[i][c] = *reinterpret_cast<const f32x4*>(ks + (size_t)blk * HD + 32 * c + 4 * sub);
       }
-      n[i] = kn[blk];
+      a[i] = ka[blk];
     }
 #pragma unroll
     for (int i = 0; i < PF; ++i) {
       const float s = dot8<NCH>(qv[i], kv[i]);
-      if (sub == 0 && e0 + 8 * i + (lane >> 3) < total && s > kNegInf && n[i] <= 0.f) {
-        const int grp = (int)((x[i] >> 20) & 15), blk = (int)(x[i] & 0xFFFFF);
-        const int at = atomicAdd(&cnt[grp], 1);
-        atomicMax(&nmax[grp], __float_as_int(-n[i]));   // norms are stored negated
-        if (at < kPerGroup) keys[grp * kPerGroup + at] = make_key(s, blk);
+      const int grp = (int)((x[i] >> 20) & 15), blk = (int)(x[i] & 0xFFFFF);
+      if (sub == 0 && e0 + 8 * i + (lane >> 3) < total && a[i] >= 0.f && blk < nblk) {
+        // a score beyond f32's range may tie with blocks that the list need not hold
+        const bool finite = fabsf(s) < __builtin_huge_valf();
+        const int at = atomicAdd(&cnt[grp], finite ? 1 : kPerGroup + 1);
+        const int e = e0 + 8 * i + (lane >> 3);
+        flat[e] = __float_as_uint(a[i]);   // the entry has been read
+        if (at < kPerGroup) keys[grp * kPerGroup + at] = make_key(s, blk, e);
       }
     }
-  }
   }
   wave_sync();
   // each key's rank within its group: lane j takes the group's keys j, j + 4, ..., eight at
@@ -657,6 +625,7 @@ __global__ void __launch_bounds__(kWaves * 64)
   over = over || (live && n > kPerGroup);
   const int nr = over ? 0 : n;
   const uint64_t* list = keys + r * kPerGroup;
+  float lo = __builtin_huge_valf(), hi = kNegInf;   // least score of the k* best, largest of the rest
   for (int b0 = 0; __builtin_amdgcn_ballot_w64(b0 < nr); b0 += 32) {
     uint64_t own8[8];
     int rank[8];
@@ -673,46 +642,104 @@ __global__ void __launch_bounds__(kWaves * 64)
       for (int i = 0; i < 8; ++i) rank[i] += k2 > own8[i];
     }
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-      if (own8[i] != 0 && (rank[i] == kk - 1 || rank[i] == kk)) edge_s[wid][rank[i] - kk + 1][r] = key_score(own8[i]);
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-      if (own8[i] != 0 && rank[i] < kk) best16[16 * r + rank[i]] = (int)(0xFFFFFFFFu - (uint32_t)own8[i]);
+    for (int i = 0; i < 8; ++i) {
+      if (own8[i] == 0) continue;
+      const float sc = key_score(own8[i]);
+      const float err = kDotErr * qnorm * __uint_as_float(flat[(uint32_t)own8[i] & 511u]);
+      if (rank[i] < kk) {
+        best16[16 * r + rank[i]] = key_block(own8[i]);
+        lo = fminf(lo, sc - err);
+      } else {
+        hi = fmaxf(hi, sc + err);
+      }
+    }
   }
+  lo = -col_max(-lo);
+  hi = col_max(hi);
+
+  // the group's pooled query and a row of 8 j .. of a compressed key in three bf16 parts
+  bf16x8 qh[NCH], qm[NCH], ql[NCH];
+  auto load_query = [&]() {
+#pragma unroll
+    for (int c = 0; c < NCH; ++c)
+      split3(load_chunk(qb + (size_t)(live ? pg : 0) * HD + 32 * c + 8 * j), qh[c], qm[c], ql[c]);
+  };
+  auto load_key = [&](int key, f32x8 (&v)[NCH]) {
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) v[c] = load_chunk(kc + (size_t)key * HD + 32 * c + 8 * j);
+  };
+  // scores of 16 keys (rows) for the wave's groups (columns), smaller products first
+  auto six = [&](int c, const bf16x8& ah, const bf16x8& am, const bf16x8& al, f32x4 acc) {
+    acc = mma(al, qh[c], acc);
+    acc = mma(ah, ql[c], acc);
+    acc = mma(am, qm[c], acc);
+    acc = mma(am, qh[c], acc);
+    acc = mma(ah, qm[c], acc);
+    return mma(ah, qh[c], acc);
+  };
+  const int rr = 1 << lgr;
+  const float rcp_r = 1.0f / (float)rr;
+
+  // groups whose cut the dots do not decide: their list's blocks scored by the six products
   wave_sync();
-  // A score's f32 sum errs by at most 12 * 2^-24 |q| |k| (11 roundings, one in the summed key):
-  // groups whose k*-th and next score are closer than twice that are ranked in float64, lane t
-  // holding the group's key t.
-  uint64_t near = __builtin_amdgcn_ballot_w64(
-                      !SPLIT && live && !over &&
-                      edge_s[wid][0][r] - edge_s[wid][1][r] <= 2.0f * 12.0f / (1 << 24) * qnorm * __int_as_float(nmax[r])) &
-                  0xFFFFull;
-  const int sub8 = lane >> 3;
+  uint64_t near = __builtin_amdgcn_ballot_w64(live && !over && !(lo > hi)) & 0xFFFFull;
+  if (near) load_query();
   while (near) {
     const int g16 = __builtin_ctzll(near);
     near &= near - 1;
-    const int m16 = __shfl(n, g16);   // <= kPerGroup = 64 keys
-    const uint64_t mine = lane < m16 ? keys[g16 * kPerGroup + lane] : 0;
-    const int blk = (int)(0xFFFFFFFFu - (uint32_t)mine);
-    double s64 = 0.0;
-    for (int i = 0; 8 * i < m16; ++i) {
-      const int bi = __shfl(blk, 8 * i + sub8);   // entry 8 i + lane / 8
-      const double v = score64<HD>(qb + (size_t)(p0 + g16) * HD, kcmp + ((size_t)bh * nblk + (8 * i + sub8 < m16 ? bi : 0)) * rr * HD, rr, sub);
-      const double got = __shfl(v, 8 * sub);      // of entry 8 i + lane % 8
-      s64 = sub8 == i ? got : s64;
+    const int m16 = __builtin_amdgcn_readlane(n, g16);   // <= kPerGroup = 64 keys
+    uint64_t* gl = keys + g16 * kPerGroup;
+    bool bad = false;
+    const int per = 16 >> lgr;   // blocks per product; four products' keys in flight together
+#pragma unroll 1
+    for (int b0 = 0; b0 < m16; b0 += 4 * per) {
+      f32x8 kv[4][NCH];
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        const int blk = key_block(gl[min(b0 + b * per + (r >> lgr), m16 - 1)]);
+        load_key((blk << lgr) + (r & (rr - 1)), kv[b]);
+      }
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        const int e0 = b0 + b * per;
+        if (e0 >= m16) break;
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+          bf16x8 ah, am, al;
+          split3(kv[b][c], ah, am, al);
+          acc = six(c, ah, am, al, acc);
+        }
+        float s = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          s += acc[i];
+          if (((i + 1) & (rr - 1)) != 0) continue;
+          const int e = e0 + ((4 * j + i) >> lgr);
+          s *= rcp_r;
+          if (r == g16 && e < m16) {
+            bad = bad || !(fabsf(s) < __builtin_huge_valf());
+            gl[e] = make_key(s, key_block(gl[e]));
+          }
+          s = 0.f;
+        }
+      }
     }
+    wave_sync();
+    if (__builtin_amdgcn_ballot_w64(bad)) {
+      over = over || r == g16;
+      continue;
+    }
+    const uint64_t mine = lane < m16 ? gl[lane] : 0;
     int rank = 0;
-    for (int y = 0; y < m16; ++y) {
-      const double s2 = __shfl(s64, y);
-      const int b2 = __shfl(blk, y);
-      rank += (s2 > s64) | ((s2 == s64) & (b2 < blk));
-    }
-    if (lane < m16 && rank < kk) best16[16 * g16 + rank] = blk;
+#pragma unroll 4
+    for (int y = 0; y < m16; ++y) rank += gl[y] > mine;
+    if (lane < m16 && rank < kk) best16[16 * g16 + rank] = key_block(mine);
   }
   wave_sync();
   // stored ascending with -1 in unused slots: lane j places the blocks of ranks 4j .. 4j + 3
   int* out = sel + ((size_t)bh * ngroups + p0) * kk;
-  {
+  auto store = [&](bool mine_too) {
     int4 v[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) v[i] = reinterpret_cast<const int4*>(best16 + 16 * r)[i];
@@ -727,101 +754,168 @@ __global__ void __launch_bounds__(kWaves * 64)
       for (int t = 0; t < 16; ++t) pos += all[t] < mine[i];
       const bool used = mine[i] != kNoBlock;
       if (!used) pos = 4 * j + i;   // ranks are filled from 0: the slots past them stay unused
-      if (live && !over && pos < kk) out[r * kk + pos] = used ? mine[i] : -1;
+      if (mine_too && pos < kk) out[r * kk + pos] = used ? mine[i] : -1;
     }
-  }
+  };
+  store(live && !over);
 
-  // groups left over: every block scored in float64, eight at a time; the k* best keys (of
-  // the scores as f32) sit in lanes 0 .. kk - 1 in descending order
-  uint64_t todo = __builtin_amdgcn_ballot_w64(over) & 0xFFFFull;
-  while (todo) {
-    const int gr = __builtin_ctzll(todo);
-    todo &= todo - 1;
-    const float* qr = qb + (size_t)(p0 + gr) * HD;
-    const int lo = ((p0 + gr) >> (lgm - lgg)) << lgb;
-    const bool zero = __builtin_amdgcn_ballot_w64(lane < HD && qr[lane < HD ? lane : 0] != 0.f) == 0;
-    uint64_t best = 0;
-    for (int b0 = 0; b0 < nblk; b0 += 64) {
-      // lane's key of block b0 + lane
-      uint64_t key = 0;
-      for (int i = 0; i < 8; ++i) {
-        const int blk = b0 + 8 * i + (lane >> 3), bc = min(blk, nblk - 1);
-        const float s = (float)score64<HD>(qr, kcmp + ((size_t)bh * nblk + bc) * rr * HD, rr, sub);
-        const float n0 = kn[bc];
-        const bool ok = blk < nblk && !(mask_own && (uint32_t)(blk - lo) < (1u << lgb)) && n0 == n0 && s > kNegInf;
-        const uint64_t k8 = ok ? make_key(s, blk) : 0;
-        const uint64_t got = __shfl(k8, 8 * sub);   // of block b0 + 8 i + sub
-        key = (lane >> 3) == i ? got : key;
+  // Groups left over: the workgroup streams the compressed keys, 64 at a time, wave w splits
+  // rows 16 w .. of a tile into the fragments of its three parts, and every wave with such a
+  // group scores the tile for it. A lane keeps the K best of its rows' blocks; each lane's K / 4
+  // best are all at least the smallest of the four lanes' (K / 4)-th, so the group already holds
+  // K >= k* at or above that value and nothing below it can enter.
+  if (!__syncthreads_or(over)) return;
+  constexpr int TS = 4;   // 16-key sub-tiles of a tile, one per wave
+  static_assert(kWaves == TS && sizeof(ring) >= TS * 3 * NCH * 64 * 16, "parts of a tile");
+  bf16x8* const frag = reinterpret_cast<bf16x8*>(ring);   // [sub-tile][part][chunk][lane]
+  const int ntok = nblk << lgr;
+  const bool wave_over = __builtin_amdgcn_ballot_w64(over) != 0;
+  uint64_t lst[K];
+#pragma unroll
+  for (int t = 0; t < K; ++t) lst[t] = 0;
+  if (wave_over) load_query();
+  f32x8 kv[NCH];
+  float norm;   // NaN where the row's block holds no real token: no score passes
+  auto fetch = [&](int t0) {
+    const int row = t0 + 16 * wid + r, rc = min(row, ntok - 1);
+    norm = row < ntok ? ka[rc >> lgr] : __builtin_nanf("");
+    load_key(rc, kv);
+  };
+  fetch(0);
+#pragma unroll 1
+  for (int t0 = 0; t0 < ntok; t0 += 16 * TS) {
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+      bf16x8 ah, am, al;
+      split3(norm >= 0.f ? kv[c] : kv[c] + __builtin_nanf(""), ah, am, al);
+      frag[((3 * wid + 0) * NCH + c) * 64 + lane] = ah;
+      frag[((3 * wid + 1) * NCH + c) * 64 + lane] = am;
+      frag[((3 * wid + 2) * NCH + c) * 64 + lane] = al;
+    }
+    const uint64_t least = group_min(lst[K / 4 - 1]);
+    // a zero query scores every block 0: the first k* eligible blocks are the result
+    if (__syncthreads_and(!over || (zero && least != 0))) break;
+    if (t0 + 16 * TS < ntok) fetch(t0 + 16 * TS);
+    if (wave_over) {
+      f32x4 acc[TS];
+#pragma unroll
+      for (int st = 0; st < TS; ++st) {
+        acc[st] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+          const bf16x8* f = frag + (3 * st * NCH + c) * 64 + lane;
+          acc[st] = six(c, f[0], f[NCH * 64], f[2 * NCH * 64], acc[st]);
+        }
       }
+      // the tile's candidates of this lane, in ascending block order; -inf: none
+      float cand[4 * TS];
+#pragma unroll
+      for (int st = 0; st < TS; ++st) {
+        float s = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const bool last = ((i + 1) & (rr - 1)) == 0;
+          s += acc[st][i];
+          const int blk = (t0 + 16 * st + 4 * j + i) >> lgr;
+          const bool ok = last && over && !(mask_own && own(blk));
+          cand[4 * st + i] = ok ? s * rcp_r : kNegInf;
+          s = last ? 0.f : s;
+        }
+      }
+      // best first; the wave repeats as often as its busiest lane needs
       for (;;) {
-        const uint64_t kth = __shfl(best, kk - 1);
-        const uint64_t hits = __builtin_amdgcn_ballot_w64(key > kth);
-        if (!hits) break;
-        const int src = __builtin_ctzll(hits);
-        const uint64_t x = __shfl(key, src);
-        const int pos = __popcll(__builtin_amdgcn_ballot_w64(lane < kk && best > x));
-        const uint64_t up = __shfl_up(best, 1);
-        best = lane < pos ? best : lane == pos ? x : up;
-        if (lane == src) key = 0;
+        float bs = kNegInf;
+        int bi = 0;
+#pragma unroll
+        for (int t = 0; t < 4 * TS; ++t) {   // first maximum: the lowest block among equal scores
+          const bool better = cand[t] > bs;
+          bs = better ? cand[t] : bs;
+          bi = better ? t : bi;
+        }
+        const uint64_t key = bs > kNegInf ? make_key(bs, (t0 + 16 * (bi / 4) + 4 * j + bi % 4) >> lgr) : 0;
+        const bool take = key > (least > lst[K - 1] ? least : lst[K - 1]);
+        if (!__builtin_amdgcn_ballot_w64(take)) break;
+        if (take) topk_insert<K>(lst, key);
+#pragma unroll
+        for (int t = 0; t < 4 * TS; ++t) cand[t] = take && t != bi ? cand[t] : kNegInf;
       }
-      // a zero query scores every block 0: the first k* eligible blocks are the result
-      if (zero && __shfl(best, kk - 1) != 0) break;
     }
-    const bool has = lane < kk && best != 0;
-    const int blk = (int)(0xFFFFFFFFu - (uint32_t)best);
-    int rank = 0, n = 0;
-    for (int t = 0; t < kk; ++t) {
-      const uint64_t o = __shfl(best, t);
-      rank += o != 0 && (int)(0xFFFFFFFFu - (uint32_t)o) < blk;
-      n += o != 0;
-    }
-    if (has) out[gr * kk + rank] = blk;
-    if (lane >= n && lane < kk) out[gr * kk + lane] = -1;
+    __syncthreads();
   }
+  if (over) *reinterpret_cast<int4*>(best16 + 16 * r + 4 * j) = make_int4(kNoBlock, kNoBlock, kNoBlock, kNoBlock);
+  wave_sync();
+  // k* rounds of a 4-way merge of a group's sorted lists: the best head is chosen and its owner
+  // drops it (keys are unique)
+#pragma unroll 1
+  for (int t = 0; t < kk; ++t) {
+    const uint64_t w = group_max(lst[0]);
+    const bool pop = w != 0 && lst[0] == w;
+#pragma unroll
+    for (int i = 0; i < K - 1; ++i) lst[i] = pop ? lst[i + 1] : lst[i];
+    lst[K - 1] = pop ? 0 : lst[K - 1];
+    if (over && j == 0 && w != 0) best16[16 * r + t] = key_block(w);
+  }
+  wave_sync();
+  store(over);
+}
+
+// Workspace: unit vectors, norm bounds (a head's padded to a whole tile), sums of norms and, for
+// several keys per block, their sums, each 256-byte aligned.
+struct SelectWs {
+  size_t norm, abs, sum, total;
+};
+SelectWs select_ws(const Dims& D) {
+  auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
+  const size_t heads = (size_t)D.B * D.H, nblk = D.N / D.ls, tile = 4096 / D.d;
+  SelectWs W;
+  W.norm = up(2 * heads * nblk * D.d);
+  W.abs = W.norm + up(4 * heads * (nblk > tile ? nblk : tile));
+  W.sum = W.abs + up(4 * heads * nblk);
+  W.total = W.sum + (D.ls > D.l ? up(4 * heads * nblk * D.d) : 0);
+  return W;
 }
 
 template <typename T, int HD, int K>
 hipError_t select_k(const Dims& D, const void* q, const uint8_t* valid, const float* kcmp, const uint8_t* cvalid,
-                    int* sel, float* qpool, bool given, uint16_t* kplanes, hipStream_t st) {
+                    int* sel, float* qpool, bool given, uint16_t* kunit, hipStream_t st) {
   auto lg = [](int x) { return __builtin_ctz((unsigned)x); };
   const int ngroups = D.N / D.g, nblk = D.N / D.ls, R = D.ls / D.l;
   const long long blocks = (long long)D.B * D.H * nblk;
   const long long pool_n8 = given ? 0 : (long long)D.B * D.H * ngroups * (HD / 8);
   const long long pool_blocks = (pool_n8 + 255) / 256, key_blocks = (blocks * (HD / 8) + 255) / 256;
-  // workspace of 6 bytes per compressed key and channel: unit vectors (2), norms, and for
-  // R > 1 the summed keys (4, 256-byte aligned)
-  uint16_t* kunit = kplanes;
-  float* knorm = reinterpret_cast<float*>(kplanes + blocks * HD);
-  const size_t norm_end = (2 * (size_t)blocks * HD + 4 * (size_t)D.B * D.H * (nblk > 4096 / HD ? nblk : 4096 / HD) + 255) & ~(size_t)255;
-  float* ksum = R > 1 ? reinterpret_cast<float*>(reinterpret_cast<char*>(kplanes) + norm_end) : nullptr;
+  const SelectWs W = select_ws(D);
+  char* const w = reinterpret_cast<char*>(kunit);
+  float *knorm = (float*)(w + W.norm), *kabs = (float*)(w + W.abs), *ksum = (float*)(w + W.sum);
   hipLaunchKernelGGL((select_prep_kernel<T, HD>), dim3((unsigned)(pool_blocks + key_blocks)), dim3(256), 0, st,
                      (const T*)q, valid, D.H, lg(D.N), lg(D.g), pool_n8, (int)pool_blocks, qpool, kcmp, cvalid,
-                     lg(nblk), lg(R), blocks, ksum, kunit, knorm);
+                     lg(nblk), lg(R), blocks, kunit, knorm, kabs, ksum);
   const dim3 grid((ngroups + 16 * kWaves - 1) / (16 * kWaves), D.B * D.H);
-  hipLaunchKernelGGL((select_kernel<HD, K, sizeof(T) == 4>), grid, dim3(kWaves * 64), 0, st, (const float*)qpool, R > 1 ? ksum : kcmp,
-                     kcmp, (const uint16_t*)kunit, (const float*)knorm, D.N, R, lg(D.ls), lg(D.m), lg(D.g), D.mask_own,
+  hipLaunchKernelGGL((select_kernel<HD, K>), grid, dim3(kWaves * 64), 0, st, (const float*)qpool,
+                     R > 1 ? (const float*)ksum : kcmp, kcmp, (const uint16_t*)kunit, (const float*)knorm,
+                     (const float*)kabs, D.N, lg(R), lg(D.ls), lg(D.m), lg(D.g), D.mask_own,
                      D.k, sel);
   return hipGetLastError();
 }
 
 template <typename T, int HD>
 hipError_t select_hd(const Dims& D, const void* q, const uint8_t* valid, const float* kcmp, const uint8_t* cvalid,
-                     int* sel, float* qpool, bool given, uint16_t* kplanes, hipStream_t st) {
-  if (D.k <= 4) return select_k<T, HD, 4>(D, q, valid, kcmp, cvalid, sel, qpool, given, kplanes, st);
-  if (D.k <= 8) return select_k<T, HD, 8>(D, q, valid, kcmp, cvalid, sel, qpool, given, kplanes, st);
-  return select_k<T, HD, 16>(D, q, valid, kcmp, cvalid, sel, qpool, given, kplanes, st);
+                     int* sel, float* qpool, bool given, uint16_t* kunit, hipStream_t st) {
+  if (D.k <= 4) return select_k<T, HD, 4>(D, q, valid, kcmp, cvalid, sel, qpool, given, kunit, st);
+  if (D.k <= 8) return select_k<T, HD, 8>(D, q, valid, kcmp, cvalid, sel, qpool, given, kunit, st);
+  return select_k<T, HD, 16>(D, q, valid, kcmp, cvalid, sel, qpool, given, kunit, st);
 }
 
 }  // namespace
 
 hipError_t launch_select_topk(const Dims& D, const void* q, const uint8_t* valid, const float* kcmp,
-                              const uint8_t* cvalid, int* sel, float* qpool, bool given, uint16_t* kplanes,
+                              const uint8_t* cvalid, int* sel, float* qpool, bool given, uint16_t* kunit,
                               hipStream_t st) {
   if (D.bf16)
-    return D.d == 64 ? select_hd<bf16_t, 64>(D, q, valid, kcmp, cvalid, sel, qpool, given, kplanes, st)
-                     : select_hd<bf16_t, 32>(D, q, valid, kcmp, cvalid, sel, qpool, given, kplanes, st);
-  return D.d == 64 ? select_hd<float, 64>(D, q, valid, kcmp, cvalid, sel, qpool, given, kplanes, st)
-                   : select_hd<float, 32>(D, q, valid, kcmp, cvalid, sel, qpool, given, kplanes, st);
+    return D.d == 64 ? select_hd<bf16_t, 64>(D, q, valid, kcmp, cvalid, sel, qpool, given, kunit, st)
+                     : select_hd<bf16_t, 32>(D, q, valid, kcmp, cvalid, sel, qpool, given, kunit, st);
+  return select_hd<float, 32>(D, q, valid, kcmp, cvalid, sel, qpool, given, kunit, st);   // float32: head_dim 32
 }
+
+size_t select_ws_bytes(const Dims& D) { return select_ws(D).total; }
 
 }  // namespace bsa

@@ -67,3 +67,88 @@ def test_select_whole_numbers(shape, f32, kind, padded):
             kc, _ = ob.compress(k[b, h], valid[b], None, P)
             scores = ob.group_block_scores(q[b, h], kc, valid[b], P)
             assert np.array_equal(sel[b, h], ob.topk_blocks(scores, kk)), (b, h)
+
+
+@pytest.mark.parametrize("many", [False, True], ids=["listed", "overflow"])
+@pytest.mark.parametrize("f32,d,g", [(False, 64, 16), (False, 32, 8), (False, 64, 1), (True, 32, 8)])
+def test_equal_float32_scores_rank_by_block(f32, d, g, many):
+    """Scores that differ by less than float32 holds rank by block index. Keys score 1 or
+    1 + 2^-30, the larger ones in the higher blocks: every float32 sum of the products 1 and
+    2^-30 is 1. `many`: all blocks tie so (candidate lists overflow), else k* + 4 of them."""
+    n, m, l, ls, kk, B, H = 4096, 256, 16, 32, 8, 1, 2
+    print(f"equal float32 scores f32={f32} d={d} g={g} many={many}", flush=True)
+    nblk = n // ls
+    tied = np.arange(nblk) if many else np.arange(nblk - 5 * (kk + 4), nblk, 5)
+    k = np.zeros((nblk, d))
+    k[:, 0] = 0.25
+    k[tied, 0] = 1.0
+    k[tied[len(tied) // 2:], 1] = 2.0 ** -30
+    k = np.broadcast_to(np.repeat(k, ls, axis=0), (B, H, n, d))
+    q = np.zeros((B, H, n, d))
+    q[..., :2] = 1.0
+    p = gb.Params(batch=B, n=n, heads=H, head_dim=d, ball_size=m, cmp_block=l, slc_block=ls, topk=kk, group_size=g,
+                  kv_pool=gb.BSA_POOL_MEAN, dtype=gb.BSA_F32 if f32 else gb.BSA_BF16)
+    qd, kd = (torch.from_numpy(np.ascontiguousarray(a)).to("cuda").to(p.torch_dtype) for a in (q, k))
+    _, saved = gb.forward(p, qd, kd, kd, None, torch.zeros((B, n, 3), device="cuda"), None, None)
+    score = np.full(nblk, 0.25)
+    score[tied] = 1.0
+    scores = np.broadcast_to(score, (n // g, nblk)).copy()
+    scores[np.arange(n // g)[:, None] * g // m == np.arange(nblk)[None] * ls // m] = -np.inf
+    want = ob.topk_blocks(scores, kk)
+    for h in range(H):
+        assert np.array_equal(saved.sel_idx[0, h].cpu().numpy(), want), h
+
+
+# n, ball, l, l', k*, g, d
+REAL = [
+    (4096, 256, 8, 16, 8, 8, 32),
+    (8192, 256, 16, 32, 16, 16, 64),
+    (8192, 512, 16, 64, 16, 32, 64),
+    (65536, 256, 16, 32, 16, 1, 64),
+]
+
+
+@pytest.mark.parametrize("kind", ["normal", "common", "far common", "binades", "cancel"])
+@pytest.mark.parametrize("shape,f32", [(s, False) for s in REAL] + [(REAL[0], True)],
+                         ids=lambda s: "-".join(map(str, s)) if isinstance(s, tuple) else ("f32" if s else "bf16"))
+def test_select_real_values(shape, f32, kind):
+    """Real-valued scores against float64 scores of the saved compressed keys and coarse queries:
+    no block left out may score above a selected one by more than the two scores' float32 error.
+    A score of six bf16 products errs by at most 2^-15 |q| times the sum of its keys' norms (224
+    sums of at most |q||k|, each off by an ulp at most), over r for a block's mean. Keys: normal,
+    with a common vector 20 and 1000 times their spread, of lengths over 40 binades, and with the
+    keys of a block nearly cancelling."""
+    n, m, l, ls, kk, g, d = shape
+    print(f"select real {shape} f32={f32} {kind}", flush=True)
+    gen = torch.Generator("cuda").manual_seed(n + d + len(kind))
+    rn = lambda *s: torch.randn(s, generator=gen, device="cuda")
+    B, H, r, nblk = 1, 2, ls // l, n // ls
+    key = rn(B, H, n // l, d)
+    if "common" in kind:
+        key = key * (0.05 if kind == "common" else 0.001) + rn(B, H, 1, d)
+    elif kind == "binades":
+        key = key * torch.exp2(40 * torch.rand((B, H, n // l, 1), generator=gen, device="cuda") - 20)
+    elif kind == "cancel":
+        key = key * 0.01
+        key[:, :, ::2] += 1.0
+        key[:, :, 1::2] -= 1.0
+    p = gb.Params(batch=B, n=n, heads=H, head_dim=d, ball_size=m, cmp_block=l, slc_block=ls, topk=kk, group_size=g,
+                  kv_pool=gb.BSA_POOL_MEAN, dtype=gb.BSA_F32 if f32 else gb.BSA_BF16)
+    k = key.repeat_interleave(l, 2).to(p.torch_dtype).contiguous()
+    q = rn(B, H, n, d).to(p.torch_dtype)
+    _, saved = gb.forward(p, q, k, k, None, torch.zeros((B, n, 3), device="cuda"), None, None)
+    for h in range(H):
+        kc, qc = saved.kcmp[0, h].double(), saved.qcmp[0, h].double()
+        norms = kc.norm(dim=1).view(nblk, r).sum(1)
+        for s in range(0, n // g, 8192):
+            qs, sel = qc[s:s + 8192], saved.sel_idx[0, h, s:s + 8192].long()
+            assert bool((sel >= 0).all()) and bool((sel[:, 1:] > sel[:, :-1]).all())
+            sc = (qs @ kc.view(nblk, r, d).sum(1).t()) / r
+            err = 2.0 ** -15 / r * qs.norm(dim=1, keepdim=True) * norms
+            own = (torch.arange(s, s + qs.shape[0], device="cuda") * g // m)[:, None] == \
+                (torch.arange(nblk, device="cuda") * ls // m)[None]
+            taken = torch.zeros_like(own).scatter(1, sel, True)
+            assert not bool((taken & own).any())
+            worst = torch.where(taken, sc + err, torch.inf).amin(1)
+            best_left = torch.where(taken | own, -torch.inf, sc - err).amax(1)
+            assert bool((best_left <= worst).all()), (h, s, float((best_left - worst).max()))
