@@ -13,7 +13,8 @@
 //
 // The score matrix (N/g x N/l' per head) is never stored, and only the few blocks that can be
 // among the k* best are scored. A workgroup owns 64 groups of one head, 16 per wave; the block
-// keys (the sum of a block's compressed keys) are streamed twice in tiles shared by its waves:
+// keys (the sum of a block's compressed keys, less a vector common to the head's blocks, which
+// shifts every score of a group alike) are streamed twice in tiles shared by its waves:
 //   1. Scores from unit vectors in f16 (one MFMA per 32 dimensions), times the key's norm,
 //      less a bound on their error: a lower bound of each block's score. Every lane keeps
 //      the largest of each of a few disjoint sets of blocks; the k*-th largest of a
@@ -28,9 +29,14 @@
 //      by block index.
 // Groups whose list overflows (e.g. all scores equal) and zero queries are left over: their
 // workgroup then streams the compressed keys once, in three bf16 parts through LDS, scores
-// every block for them and keeps a running top-k per lane, merged at the end.
+// every block for them and keeps a running top-k per lane, merged at the end. Heads whose keys
+// are nearly equal, so that every list would overflow, skip the two streams.
+// The common vector is a trimmed mean of blocks sampled over the head: without it, a component
+// that all keys share (a bias, slowly varying features) widens the bound below, though it cannot
+// change a ranking, until the lists overflow (65536 queries in groups of 16, keys N(0, 1) plus a
+// common vector 20 times as long: 0.39 ms, with it 0.12). Any vector would do, so a few blocks serve.
 // Error of a unit-vector score against the score it stands for, in units of |q| times the
-// block's norm bound w = max(|sum of its keys|, sum of its keys' norms / 16) (an upper bound of
+// block's norm bound w = max(|its vector|, sum of its keys' norms / 16) (an upper bound of
 // the vector's length serves as its scale): f16 rounds each of the two operands by at most 2^-11
 // of its magnitude, so by Cauchy-Schwarz the product errs by at most 2^-10 (+ 2^-22); the
 // vectors are scaled by 2^7, which keeps what f16 cannot hold (below 2^-24, or below 2^-14
@@ -44,10 +50,11 @@
 // about 3000 per 16 groups for the ranking), and with few waves per SIMD the latency of each
 // tile. Measured with its preparation, k* = 16, d = 64, r = 2, N(0, 1) tensors (in brackets: one
 // stream of all compressed keys with the six products and a 16-deep list in every lane): 65536
-// queries x 8 heads in groups of 16 0.10 ms (0.27), one by one 0.94 (2.73); 2^20 queries x 16
-// heads in groups of 32 5.1 ms (15.7). Two sets of 16 groups per wave, which halve the LDS reads
+// queries x 8 heads in groups of 16 0.10 ms (0.27), one by one 0.91 (2.73); 2^20 queries x 16
+// heads in groups of 32 4.8 ms (15.7). Two sets of 16 groups per wave, which halve the LDS reads
 // per group, left fewer waves (the kernel alone at 65536 queries 0.109 instead of 0.074 ms, one
-// by one 0.86 instead of 0.82). With every group left over the three take 0.39, 4.5 and 28 ms.
+// by one 0.86 instead of 0.82). With every group left over (keys N(0, 1) plus a common
+// vector 1000 times as long) the three take 0.27, 3.0 and 18 ms.
 #include <type_traits>
 
 #include "common.hpp"
@@ -65,6 +72,10 @@ constexpr int kNoBlock = 0x7FFFFFFF;
 constexpr float kUnit = 128.0f;           // scale of the f16 unit vectors
 constexpr float kUnitErr = 1.6f / 1024 * kUnit * kUnit;
 constexpr float kSpread = 1.0f / 16;      // least norm bound of a block, over the sum of its keys' norms
+// Heads whose blocks' vectors are shorter than this share of their keys' norms skip the filter: its
+// error bound, held up by kSpread, is then 7 times that of spread keys and lists overflow (a common
+// vector 100 times as long as the keys at 65536 queries: 0.28 ms, 0.40 with the filter first).
+constexpr float kEqual = 1.0f / 112;
 constexpr float kDotErr = 1.0f / 32768 + 12.0f / (1 << 24);
 
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
@@ -142,10 +153,14 @@ __device__ __forceinline__ float unit_scale(const float* x, int n, int& e, MaxF 
 // queries (Eq. 11), q_p = (1/g) * sum of the group's real queries in slot order, eight
 // channels per thread (HBM: one read of Q in 16-byte loads; a thread per channel took 33
 // instead of 14 us at 65536 queries x 8 heads of 64). The others: the sum of every selection
-// block's compressed keys in f32 (ksum, not written for r = 1: kcmp holds them) and, over its norm
-// bound (see above), in f16, the negated norm bound and the sum of its keys' norms (kabs), HD / 8
-// threads per block; blocks without a real token get the norms NaN, which no comparison passes.
-// A head's norm bounds are padded with NaN to a whole tile of the selection kernel.
+// block's compressed keys in f32 (ksum, not written for r = 1: kcmp holds them), less the head's
+// common vector and over its norm bound (see above) in f16, the negated norm bound and the sum of
+// its keys' norms (kabs), HD / 8 threads per block; blocks without a real token get the norms NaN,
+// which no comparison passes. A head's norm bounds are padded with NaN to a whole tile of the
+// selection kernel. Every workgroup forms its head's common vector from the same 16 blocks (a
+// launch of its own for it would cost more than the loads): per channel the mean without the
+// smallest and the largest. Heads smaller than a workgroup's share of blocks do without. The
+// head's first workgroup notes whether most sampled blocks are as good as equal (flags).
 template <typename T, int HD>
 __global__ void __launch_bounds__(256) select_prep_kernel(const T* __restrict__ q, const uint8_t* __restrict__ valid,
                                                           int H, int lgn, int lgg, long long pool_n8, int pool_blocks,
@@ -153,8 +168,9 @@ __global__ void __launch_bounds__(256) select_prep_kernel(const T* __restrict__ 
                                                           const uint8_t* __restrict__ cvalid, int lgb, int lgr,
                                                           long long blocks, uint16_t* __restrict__ kunit,
                                                           float* __restrict__ knorm, float* __restrict__ kabs,
-                                                          float* __restrict__ ksum) {
-  constexpr int CPR = HD / 8;
+                                                          float* __restrict__ ksum, int* __restrict__ flags) {
+  constexpr int CPR = HD / 8, NS = 16;   // sampled blocks
+  __shared__ float sample[NS][HD], common[HD];
   if ((int)blockIdx.x < pool_blocks) {
     const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
     if (i >= pool_n8) return;
@@ -183,28 +199,88 @@ __global__ void __launch_bounds__(256) select_prep_kernel(const T* __restrict__ 
   const long long i = (long long)(blockIdx.x - pool_blocks) * 256 + threadIdx.x;
   if (i >= blocks * CPR) return;   // whole rows: 256 is a multiple of CPR
   const long long blk = i / CPR;   // (b*H + h) * nblk + block, nblk = 2^lgb
-  const int r = 1 << lgr;
-  double sum[8], sq = 0.0;   // rounded once: within 2^-24 of the true sum, whatever cancels
+  const int r = 1 << lgr, c = 8 * (int)(i % CPR);
+  const int nblk = 1 << lgb;
+  const bool centred = nblk >= 256 / CPR;   // the workgroup's blocks are of one head
+  const int row = (int)threadIdx.x / CPR, srow = row % NS;
+  // eight channels of the thread's block and of the block it samples: the keys' sum (rounded once
+  // when used: within 2^-24 of the true sum, whatever cancels), an upper bound of the sum of their
+  // norms, and whether the block holds a real token
+  const long long bk[2] = {blk, centred ? (blk >> lgb << lgb) + ((2 * srow + 1) * nblk) / (2 * NS) : blk};
+  double sum[2][8], sq[2] = {0.0, 0.0};
+  uint32_t any[2] = {0, 0};
+  float norms[2];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) sum[e] = 0.0;
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) sum[t][e] = 0.0;
+  const uint8_t* cv = cvalid + ((long long)((uint32_t)(blk >> lgb) / (uint32_t)H) << (lgb + lgr));
   for (int k = 0; k < r; ++k) {
-    const f32x8 v = load_chunk(kcmp + ((blk << lgr) + k) * HD + 8 * (i % CPR));
+    f32x8 v[2];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      sum[e] += (double)v[e];
-      sq = fma((double)v[e], (double)v[e], sq);
+    for (int t = 0; t < 2; ++t) {
+      v[t] = load_chunk(kcmp + ((bk[t] << lgr) + k) * HD + c);
+      any[t] |= cv[((bk[t] & (nblk - 1)) << lgr) + k];
     }
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        sum[t][e] += (double)v[t][e];
+        sq[t] = fma((double)v[t][e], (double)v[t][e], sq[t]);
+      }
   }
 #pragma unroll
-  for (int o = 1; o < CPR; o <<= 1) sq += __shfl_xor(sq, o, 64);
-  const float norms = (float)sqrt((double)r * sq), least = kSpread * norms;   // sum of r norms <= sqrt(r sum of squares)
+  for (int t = 0; t < 2; ++t) {
+#pragma unroll
+    for (int o = 1; o < CPR; o <<= 1) sq[t] += __shfl_xor(sq[t], o, 64);
+    norms[t] = (float)sqrt((double)r * sq[t]);   // sum of r norms <= sqrt(r sum of squares)
+  }
+  const float least = kSpread * norms[0];
+  float mean[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) mean[e] = 0.f;
+  bool equal = false;
+  if (centred) {
+    if (row < NS) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) sample[row][c + e] = any[1] ? (float)sum[1][e] : __builtin_nanf("");
+    }
+    __syncthreads();
+    if (threadIdx.x < HD) {
+      float s = 0.f, lo = __builtin_huge_valf(), hi = kNegInf;
+      int n = 0;
+#pragma unroll
+      for (int t = 0; t < NS; ++t) {
+        const float x = sample[t][threadIdx.x];
+        const bool ok = fabsf(x) < 1e30f;   // not NaN, and the sum stays in range
+        s += ok ? x : 0.f;
+        lo = ok ? fminf(lo, x) : lo;
+        hi = ok ? fmaxf(hi, x) : hi;
+        n += ok;
+      }
+      common[threadIdx.x] = n > 2 ? (s - lo - hi) / (float)(n - 2) : 0.f;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 8; ++e) mean[e] = common[c + e];
+    if (((blk - row) & (nblk - 1)) == 0) {   // the head's first workgroup
+      float d2 = 0.f;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float d = (float)(sum[1][e] - (double)mean[e]);
+        d2 = fmaf(d, d, d2);
+      }
+#pragma unroll
+      for (int o = 1; o < CPR; o <<= 1) d2 += __shfl_xor(d2, o, 64);
+      const float lim = kEqual * norms[1];
+      equal = 2 * __syncthreads_count(any[1] && d2 < lim * lim) > __syncthreads_count(any[1]);
+    }
+  }
+  if (c == 0 && (blk & (nblk - 1)) == 0) flags[blk >> lgb] = equal;
   float a[8];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) a[e] = (float)sum[e];
-  const uint8_t* cv = cvalid + ((long long)((uint32_t)(blk >> lgb) / (uint32_t)H) << (lgb + lgr)) +
-                      ((blk & ((1LL << lgb) - 1)) << lgr);
-  uint32_t any = 0;
-  for (int k = 0; k < r; ++k) any |= cv[k];
+  for (int e = 0; e < 8; ++e) a[e] = (float)(sum[0][e] - (double)mean[e]);
   int ex;
   const float ss = unit_scale(
       a, 8, ex,
@@ -225,15 +301,15 @@ __global__ void __launch_bounds__(256) select_prep_kernel(const T* __restrict__ 
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     u[e] = (_Float16)(ldexpf(a[e], -ex) * rn);
-    o[e] = a[e];
+    o[e] = (float)sum[0][e];
   }
   *reinterpret_cast<f16x8*>(kunit + 8 * i) = u;
   if (r > 1) *reinterpret_cast<f32x8*>(ksum + 8 * i) = o;
-  if (i % CPR == 0) {
-    kabs[blk] = any ? norms : __builtin_nanf("");
+  if (c == 0) {
+    kabs[blk] = any[0] ? norms[0] : __builtin_nanf("");
     float* kn = knorm + (blk >> lgb) * (long long)max(1 << lgb, 4096 / HD);
     const int t = (int)(blk & ((1LL << lgb) - 1));
-    kn[t] = any ? -fmaxf(ldexpf(nrm, ex), least) : __builtin_nanf("");
+    kn[t] = any[0] ? -fmaxf(ldexpf(nrm, ex), least) : __builtin_nanf("");
     for (int p = t + (1 << lgb); p < 4096 / HD; p += 1 << lgb) kn[p] = __builtin_nanf("");
   }
 }
@@ -391,7 +467,8 @@ __device__ __forceinline__ void vm_wait() {
 template <int HD, int K>
 __global__ void __launch_bounds__(kWaves * 64)
     select_kernel(const float* __restrict__ qpool, const float* __restrict__ ksum, const float* __restrict__ kcmp,
-                  const uint16_t* __restrict__ kunit, const float* __restrict__ knorm, const float* __restrict__ kabs, int N, int lgr, int lgls, int lgm, int lgg, int mask_own, int kk,
+                  const uint16_t* __restrict__ kunit, const float* __restrict__ knorm, const float* __restrict__ kabs,
+                  const int* __restrict__ flags, int N, int lgr, int lgls, int lgm, int lgg, int mask_own, int kk,
                   int* __restrict__ sel) {
   constexpr int NCH = HD / 32;
   constexpr int KT = 4096 / HD;     // blocks per staged tile (8 KB)
@@ -445,6 +522,7 @@ __global__ void __launch_bounds__(kWaves * 64)
 
 #pragma unroll
   for (int u = 0; u < kAhead; ++u) issue(u);
+  const int ntu = flags[bh] ? 0 : nt;   // tiles used
 
   // this lane's group: unit query (B operand)
   const int pg = p0 + r;
@@ -510,7 +588,7 @@ __global__ void __launch_bounds__(kWaves * 64)
 #pragma unroll
   for (int t = 0; t < K; ++t) top[t] = __builtin_huge_valf();
 #pragma unroll 1
-  for (int u = 0; u < nt; ++u) {
+  for (int u = 0; u < ntu; ++u) {
     advance(u);
     const int t0 = u * KT;
     if (t0 < wave_hi && t0 + KT > wave_lo)
@@ -556,7 +634,7 @@ __global__ void __launch_bounds__(kWaves * 64)
     }
   };
 #pragma unroll 1
-  for (int u = nt; u < 2 * nt; ++u) {
+  for (int u = nt; u < nt + ntu; ++u) {
     advance(u);
     const int t0 = (u - nt) * KT;
     if (t0 < wave_hi && t0 + KT > wave_lo)
@@ -571,6 +649,7 @@ __global__ void __launch_bounds__(kWaves * 64)
     const int done = (u - nt) % TF + 1;
     if (done == TF || u == 2 * nt - 1) move(u - nt - done + 1, done * NC);
   }
+  if (ntu == 0) vm_drain();   // the first tiles have landed
   __syncthreads();   // the tiles are free: they hold the groups' lists from here
 
   // the listed blocks' dots, each to its group's list as a key (in no particular order)
@@ -580,7 +659,7 @@ __global__ void __launch_bounds__(kWaves * 64)
   if (lane < 16) cnt[lane] = 0;
   *reinterpret_cast<int4*>(best16 + 4 * lane) = make_int4(kNoBlock, kNoBlock, kNoBlock, kNoBlock);
   wave_sync();
-  if (total > kFlat) {
+  if (total > kFlat || ntu == 0) {
     over = live;
     total = 0;
   }
@@ -619,41 +698,43 @@ __global__ void __launch_bounds__(kWaves * 64)
     }
   }
   wave_sync();
-  // each key's rank within its group: lane j takes the group's keys j, j + 4, ..., eight at
-  // a time, and compares them with all of the group's keys
   const int n = cnt[r];
   over = over || (live && n > kPerGroup);
-  const int nr = over ? 0 : n;
   const uint64_t* list = keys + r * kPerGroup;
-  float lo = __builtin_huge_valf(), hi = kNegInf;   // least score of the k* best, largest of the rest
-  for (int b0 = 0; __builtin_amdgcn_ballot_w64(b0 < nr); b0 += 32) {
-    uint64_t own8[8];
-    int rank[8];
+  // each key's rank within its group (nr keys): lane j takes the group's keys j, j + 4, ..., eight
+  // at a time, and compares them with all of the group's keys
+  auto rank_keys = [&](int nr, auto&& each) {
+    for (int b0 = 0; __builtin_amdgcn_ballot_w64(b0 < nr); b0 += 32) {
+      uint64_t own8[8];
+      int rank[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int y = b0 + 4 * i + j;
-      own8[i] = y < nr ? list[y] : 0;
-      rank[i] = 0;
-    }
+      for (int i = 0; i < 8; ++i) {
+        const int y = b0 + 4 * i + j;
+        own8[i] = y < nr ? list[y] : 0;
+        rank[i] = 0;
+      }
 #pragma unroll 4
-    for (int y = 0; y < nr; ++y) {
-      const uint64_t k2 = list[y];
+      for (int y = 0; y < nr; ++y) {
+        const uint64_t k2 = list[y];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) rank[i] += k2 > own8[i];
-    }
+        for (int i = 0; i < 8; ++i) rank[i] += k2 > own8[i];
+      }
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      if (own8[i] == 0) continue;
-      const float sc = key_score(own8[i]);
-      const float err = kDotErr * qnorm * __uint_as_float(flat[(uint32_t)own8[i] & 511u]);
-      if (rank[i] < kk) {
-        best16[16 * r + rank[i]] = key_block(own8[i]);
-        lo = fminf(lo, sc - err);
-      } else {
-        hi = fmaxf(hi, sc + err);
+      for (int i = 0; i < 8; ++i) {
+        if (own8[i] == 0) continue;
+        if (rank[i] < kk) best16[16 * r + rank[i]] = key_block(own8[i]);
+        each(own8[i], rank[i]);
       }
     }
-  }
+  };
+  float lo = __builtin_huge_valf(), hi = kNegInf;   // least score of the k* best, largest of the rest
+  rank_keys(over ? 0 : n, [&](uint64_t key, int rank) {
+    const float sc = key_score(key), err = kDotErr * qnorm * __uint_as_float(flat[(uint32_t)key & 511u]);
+    if (rank < kk)
+      lo = fminf(lo, sc - err);
+    else
+      hi = fmaxf(hi, sc + err);
+  });
   lo = -col_max(-lo);
   hi = col_max(hi);
 
@@ -680,29 +761,36 @@ __global__ void __launch_bounds__(kWaves * 64)
   const int rr = 1 << lgr;
   const float rcp_r = 1.0f / (float)rr;
 
-  // groups whose cut the dots do not decide: their list's blocks scored by the six products
+  // groups whose cut the dots do not decide: the blocks of their lists, gathered in `flat` as
+  // (group, place in its list), are scored by the six products
   wave_sync();
-  uint64_t near = __builtin_amdgcn_ballot_w64(live && !over && !(lo > hi)) & 0xFFFFull;
-  if (near) load_query();
-  while (near) {
-    const int g16 = __builtin_ctzll(near);
-    near &= near - 1;
-    const int m16 = __builtin_amdgcn_readlane(n, g16);   // <= kPerGroup = 64 keys
-    uint64_t* gl = keys + g16 * kPerGroup;
+  const bool near = live && !over && !(lo > hi);
+  if (__builtin_amdgcn_ballot_w64(near)) {
+    const int nn = near ? n : 0;
+    int end = nn;   // of the group's entries
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) {
+      const int y = __shfl_up(end, o, 16);
+      end += r >= o ? y : 0;
+    }
+    for (int i = j; i < nn; i += 4) flat[end - nn + i] = (uint32_t)(r * kPerGroup + i);
+    const int tot = __builtin_amdgcn_readlane(end, 15);   // at most the kFlat entries there were
+    load_query();
+    wave_sync();
     bool bad = false;
     const int per = 16 >> lgr;   // blocks per product; four products' keys in flight together
 #pragma unroll 1
-    for (int b0 = 0; b0 < m16; b0 += 4 * per) {
+    for (int b0 = 0; b0 < tot; b0 += 4 * per) {
       f32x8 kv[4][NCH];
 #pragma unroll
       for (int b = 0; b < 4; ++b) {
-        const int blk = key_block(gl[min(b0 + b * per + (r >> lgr), m16 - 1)]);
+        const int blk = key_block(keys[flat[min(b0 + b * per + (r >> lgr), tot - 1)]]);
         load_key((blk << lgr) + (r & (rr - 1)), kv[b]);
       }
 #pragma unroll
       for (int b = 0; b < 4; ++b) {
         const int e0 = b0 + b * per;
-        if (e0 >= m16) break;
+        if (e0 >= tot) break;
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
@@ -716,25 +804,19 @@ __global__ void __launch_bounds__(kWaves * 64)
           s += acc[i];
           if (((i + 1) & (rr - 1)) != 0) continue;
           const int e = e0 + ((4 * j + i) >> lgr);
+          const int at = (int)flat[min(e, tot - 1)];
           s *= rcp_r;
-          if (r == g16 && e < m16) {
+          if (e < tot && at / kPerGroup == r) {   // the entry's own group's column
             bad = bad || !(fabsf(s) < __builtin_huge_valf());
-            gl[e] = make_key(s, key_block(gl[e]));
+            keys[at] = make_key(s, key_block(keys[at]));
           }
           s = 0.f;
         }
       }
     }
     wave_sync();
-    if (__builtin_amdgcn_ballot_w64(bad)) {
-      over = over || r == g16;
-      continue;
-    }
-    const uint64_t mine = lane < m16 ? gl[lane] : 0;
-    int rank = 0;
-#pragma unroll 4
-    for (int y = 0; y < m16; ++y) rank += gl[y] > mine;
-    if (lane < m16 && rank < kk) best16[16 * g16 + rank] = key_block(mine);
+    over = over || col_max(bad ? 1.f : 0.f) > 0.f;
+    rank_keys(near && !over ? n : 0, [](uint64_t, int) {});
   }
   wave_sync();
   // stored ascending with -1 in unused slots: lane j places the blocks of ranks 4j .. 4j + 3
@@ -765,6 +847,7 @@ __global__ void __launch_bounds__(kWaves * 64)
   // best are all at least the smallest of the four lanes' (K / 4)-th, so the group already holds
   // K >= k* at or above that value and nothing below it can enter.
   if (!__syncthreads_or(over)) return;
+  const bool some_zero = __syncthreads_or(over && zero);
   constexpr int TS = 4;   // 16-key sub-tiles of a tile, one per wave
   static_assert(kWaves == TS && sizeof(ring) >= TS * 3 * NCH * 64 * 16, "parts of a tile");
   bf16x8* const frag = reinterpret_cast<bf16x8*>(ring);   // [sub-tile][part][chunk][lane]
@@ -774,6 +857,39 @@ __global__ void __launch_bounds__(kWaves * 64)
 #pragma unroll
   for (int t = 0; t < K; ++t) lst[t] = 0;
   if (wave_over) load_query();
+  // a tile's blocks into the lane's list: rows t0 + 16 st + 4 j + i, R keys per block
+  auto take_tile = [&](auto rc, int t0, const f32x4 (&acc)[TS], uint64_t least) {
+    constexpr int R = decltype(rc)::value, NPS = 4 / R;
+    float cand[NPS * TS];   // in ascending block order; -inf: none
+    const int blk0 = (t0 + 4 * j) / R;
+#pragma unroll
+    for (int st = 0; st < TS; ++st)
+#pragma unroll
+      for (int u = 0; u < NPS; ++u) {
+        float s = 0.f;
+#pragma unroll
+        for (int i = 0; i < R; ++i) s += acc[st][u * R + i];
+        const int blk = blk0 + st * (16 / R) + u;
+        cand[st * NPS + u] = over && !(mask_own && own(blk)) ? s * (1.0f / R) : kNegInf;
+      }
+    // best first; the wave repeats as often as its busiest lane needs
+    for (;;) {
+      float bs = kNegInf;
+      int bi = 0;
+#pragma unroll
+      for (int t = 0; t < NPS * TS; ++t) {   // first maximum: the lowest block among equal scores
+        const bool better = cand[t] > bs;
+        bs = better ? cand[t] : bs;
+        bi = better ? t : bi;
+      }
+      const uint64_t key = bs > kNegInf ? make_key(bs, blk0 + bi / NPS * (16 / R) + bi % NPS) : 0;
+      const bool take = key > (least > lst[K - 1] ? least : lst[K - 1]);
+      if (!__builtin_amdgcn_ballot_w64(take)) break;
+      if (take) topk_insert<K>(lst, key);
+#pragma unroll
+      for (int t = 0; t < NPS * TS; ++t) cand[t] = take && t != bi ? cand[t] : kNegInf;
+    }
+  };
   f32x8 kv[NCH];
   float norm;   // NaN where the row's block holds no real token: no score passes
   auto fetch = [&](int t0) {
@@ -794,7 +910,10 @@ __global__ void __launch_bounds__(kWaves * 64)
     }
     const uint64_t least = group_min(lst[K / 4 - 1]);
     // a zero query scores every block 0: the first k* eligible blocks are the result
-    if (__syncthreads_and(!over || (zero && least != 0))) break;
+    if (!some_zero)
+      __syncthreads();
+    else if (__syncthreads_and(!over || (zero && least != 0)))
+      break;
     if (t0 + 16 * TS < ntok) fetch(t0 + 16 * TS);
     if (wave_over) {
       f32x4 acc[TS];
@@ -807,38 +926,12 @@ __global__ void __launch_bounds__(kWaves * 64)
           acc[st] = six(c, f[0], f[NCH * 64], f[2 * NCH * 64], acc[st]);
         }
       }
-      // the tile's candidates of this lane, in ascending block order; -inf: none
-      float cand[4 * TS];
-#pragma unroll
-      for (int st = 0; st < TS; ++st) {
-        float s = 0.f;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const bool last = ((i + 1) & (rr - 1)) == 0;
-          s += acc[st][i];
-          const int blk = (t0 + 16 * st + 4 * j + i) >> lgr;
-          const bool ok = last && over && !(mask_own && own(blk));
-          cand[4 * st + i] = ok ? s * rcp_r : kNegInf;
-          s = last ? 0.f : s;
-        }
-      }
-      // best first; the wave repeats as often as its busiest lane needs
-      for (;;) {
-        float bs = kNegInf;
-        int bi = 0;
-#pragma unroll
-        for (int t = 0; t < 4 * TS; ++t) {   // first maximum: the lowest block among equal scores
-          const bool better = cand[t] > bs;
-          bs = better ? cand[t] : bs;
-          bi = better ? t : bi;
-        }
-        const uint64_t key = bs > kNegInf ? make_key(bs, (t0 + 16 * (bi / 4) + 4 * j + bi % 4) >> lgr) : 0;
-        const bool take = key > (least > lst[K - 1] ? least : lst[K - 1]);
-        if (!__builtin_amdgcn_ballot_w64(take)) break;
-        if (take) topk_insert<K>(lst, key);
-#pragma unroll
-        for (int t = 0; t < 4 * TS; ++t) cand[t] = take && t != bi ? cand[t] : kNegInf;
-      }
+      if (lgr == 0)
+        take_tile(std::integral_constant<int, 1>{}, t0, acc, least);
+      else if (lgr == 1)
+        take_tile(std::integral_constant<int, 2>{}, t0, acc, least);
+      else
+        take_tile(std::integral_constant<int, 4>{}, t0, acc, least);
     }
     __syncthreads();
   }
@@ -859,10 +952,10 @@ __global__ void __launch_bounds__(kWaves * 64)
   store(over);
 }
 
-// Workspace: unit vectors, norm bounds (a head's padded to a whole tile), sums of norms and, for
-// several keys per block, their sums, each 256-byte aligned.
+// Workspace: unit vectors, norm bounds (a head's padded to a whole tile), sums of norms, a flag per
+// head and, for several keys per block, their sums, each 256-byte aligned.
 struct SelectWs {
-  size_t norm, abs, sum, total;
+  size_t norm, abs, flags, sum, total;
 };
 SelectWs select_ws(const Dims& D) {
   auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
@@ -870,7 +963,8 @@ SelectWs select_ws(const Dims& D) {
   SelectWs W;
   W.norm = up(2 * heads * nblk * D.d);
   W.abs = W.norm + up(4 * heads * (nblk > tile ? nblk : tile));
-  W.sum = W.abs + up(4 * heads * nblk);
+  W.flags = W.abs + up(4 * heads * nblk);
+  W.sum = W.flags + up(4 * heads);
   W.total = W.sum + (D.ls > D.l ? up(4 * heads * nblk * D.d) : 0);
   return W;
 }
@@ -886,13 +980,14 @@ hipError_t select_k(const Dims& D, const void* q, const uint8_t* valid, const fl
   const SelectWs W = select_ws(D);
   char* const w = reinterpret_cast<char*>(kunit);
   float *knorm = (float*)(w + W.norm), *kabs = (float*)(w + W.abs), *ksum = (float*)(w + W.sum);
+  int* flags = (int*)(w + W.flags);
   hipLaunchKernelGGL((select_prep_kernel<T, HD>), dim3((unsigned)(pool_blocks + key_blocks)), dim3(256), 0, st,
                      (const T*)q, valid, D.H, lg(D.N), lg(D.g), pool_n8, (int)pool_blocks, qpool, kcmp, cvalid,
-                     lg(nblk), lg(R), blocks, kunit, knorm, kabs, ksum);
+                     lg(nblk), lg(R), blocks, kunit, knorm, kabs, ksum, flags);
   const dim3 grid((ngroups + 16 * kWaves - 1) / (16 * kWaves), D.B * D.H);
   hipLaunchKernelGGL((select_kernel<HD, K>), grid, dim3(kWaves * 64), 0, st, (const float*)qpool,
                      R > 1 ? (const float*)ksum : kcmp, kcmp, (const uint16_t*)kunit, (const float*)knorm,
-                     (const float*)kabs, D.N, lg(R), lg(D.ls), lg(D.m), lg(D.g), D.mask_own,
+                     (const float*)kabs, (const int*)flags, D.N, lg(R), lg(D.ls), lg(D.m), lg(D.g), D.mask_own,
                      D.k, sel);
   return hipGetLastError();
 }

@@ -9,7 +9,7 @@ import pytest
 import torch
 
 from oracle import bsa as ob
-from paper_2506_12541_amd import bsa as gb
+from paper_2506_12541_amd import _lib, bsa as gb
 
 pytestmark = pytest.mark.gpu
 
@@ -152,3 +152,31 @@ def test_select_real_values(shape, f32, kind):
             worst = torch.where(taken, sc + err, torch.inf).amin(1)
             best_left = torch.where(taken | own, -torch.inf, sc - err).amax(1)
             assert bool((best_left <= worst).all()), (h, s, float((best_left - worst).max()))
+
+
+def test_select_time_does_not_depend_on_a_common_key():
+    """A component that all keys share shifts every score of a group alike: the selection takes
+    the time it takes without it (bound: twice; it was over forty times when the filter's error
+    bound followed the whole keys and every candidate list overflowed)."""
+    p = gb.Params(batch=1, n=65536, heads=8, head_dim=64, ball_size=256, cmp_block=16, slc_block=32, topk=16,
+                  group_size=16, kv_pool=gb.BSA_POOL_MEAN)
+    gen = torch.Generator("cuda").manual_seed(3)
+    rn = lambda *s: torch.randn(s, generator=gen, device="cuda")
+    q, key, common = rn(1, 8, 65536, 64).bfloat16(), rn(1, 8, 4096, 64), rn(1, 8, 1, 64)
+    gate = torch.zeros((1, 65536, 3), device="cuda")
+    lib = _lib.load()
+    ms, count = {}, _lib.C.c_int32()
+    for scale in (0.0, 20.0):
+        k = (key + scale * common).repeat_interleave(16, 2).bfloat16().contiguous()
+        gb.forward(p, q, k, k, None, gate, None, None)
+        times = []
+        for _ in range(5):
+            lib.bsa_timing_enable(1)
+            gb.forward(p, q, k, k, None, gate, None, None)
+            t = _lib.C.c_double()
+            _lib.check(lib.bsa_timing_query(b"fwd.select", _lib.C.byref(t), _lib.C.byref(count)), "timing")
+            times.append(t.value)
+            lib.bsa_timing_enable(0)
+        ms[scale] = min(times)
+    print(f"select with and without a common key: {ms}", flush=True)
+    assert ms[20.0] < 2 * ms[0.0], ms
