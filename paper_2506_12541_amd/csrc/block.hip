@@ -154,12 +154,14 @@ __device__ __forceinline__ void tr_frags4(const bf16_t* t, int k0, int m0, int l
     f[i] = __builtin_bit_cast(bf16x8, make_uint4(r[2 * i].x, r[2 * i].y, r[2 * i + 1].x, r[2 * i + 1].y));
 }
 
-// 1 / (1 + exp(-x)): the hardware reciprocal and one Newton step (within an ulp of the divided
-// value, at a third of the division's instructions); exp is kept finite.
+// 1 / (1 + exp(-x)) from t = exp(-|x|), which never overflows: 1 / (1 + t), or t / (1 + t) for
+// negative x. The hardware reciprocal and one Newton step (within an ulp of the divided value, at a
+// third of the division's instructions; 1 + t is at most 2).
 __device__ __forceinline__ float sigmoid(float x) {
-  const float y = 1.0f + __expf(fminf(-x, 80.0f));
-  const float r = __builtin_amdgcn_rcpf(y);
-  return fmaf(fmaf(-y, r, 1.0f), r, r);
+  const float t = __expf(-fabsf(x)), y = 1.0f + t;
+  float r = __builtin_amdgcn_rcpf(y);
+  r = fmaf(fmaf(-y, r, 1.0f), r, r);
+  return x < 0.f ? t * r : r;
 }
 
 struct GemmArgs {

@@ -73,3 +73,26 @@ def test_block_products(case):
         assert bool((err <= (2.0 ** -16 + 2.0 ** -8) * mag).all()), name
         assert float(err.norm() / ref.norm()) < 1e-3, name
     assert np.isfinite(float(g["dx"].double().norm()))
+
+
+def test_swiglu_far_negative():
+    """silu(u) w for u down to about -200, where exp(-u) leaves float32's range: within one
+    bfloat16 rounding and float32's relative error, except where sigmoid(u) is below float32's
+    smallest normal number 2^-126 (that times |u w|, below 2^15 here)."""
+    B, n, H, d, F = 1, 256, 4, 32, 128
+    C, l = H * d, 8
+    print("swiglu far negative", flush=True)
+    gen = torch.Generator("cuda").manual_seed(11)
+    rn = lambda *s: torch.randn(s, generator=gen, device="cuda")
+    p = gb.Params(batch=B, n=n, heads=H, head_dim=d, ball_size=256, cmp_block=l, slc_block=2 * l, topk=4, group_size=l,
+                  kv_pool=gb.BSA_POOL_MEAN)
+    W = {"g1": 1 + 0.1 * rn(C), "wqkv": rn(3 * C, C) / C ** 0.5, "wg": rn(3, C) / C ** 0.5, "wo": rn(C, C) / C ** 0.5,
+         "g2": 1 + 0.1 * rn(C), "w1": 50 * rn(F, C) / C ** 0.5, "w3": rn(F, C) / C ** 0.5, "w2": rn(C, F) / F ** 0.5}
+    phi = {"w1": rn(l * d, d), "b1": rn(d), "w2": rn(d, d), "b2": rn(d)}
+    _, sv = gb.block_forward(p, F, W, phi, phi, rn(B, n, C))
+    uw = sv.uw.view(B * n, 2 * F).double()
+    u, w = uw[:, :F], uw[:, F:]
+    assert float(u.min()) < -100 and float((u * w).abs().max()) < 2.0 ** 15
+    ref = torch.nn.functional.silu(u) * w
+    err = (sv.a.view(B * n, F).double() - ref).abs()
+    assert bool((err <= (2.0 ** -8 + 2.0 ** -16) * ref.abs() + 2.0 ** -111).all()), float(err[u < -80].max())
