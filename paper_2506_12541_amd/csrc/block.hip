@@ -116,7 +116,7 @@ __device__ __forceinline__ void lgkm_drain() { asm volatile("s_waitcnt lgkmcnt(0
 
 // LDS byte addresses of the two transposing reads that give lane (p = L % 16, j = L / 16)
 // the operand X[k0 + 4j + i][m0 + p] (i = 0..3) and X[k0 + 16 + 4j + i][m0 + p] of a
-// [64][COLS] tile X: within each 16-lane group, ds_read_b64_tr_b16 hands lane l element
+// [BK][COLS] tile X (BK = 32 or 64): within each 16-lane group, ds_read_b64_tr_b16 hands lane l element
 // l % 4 of the 4-element runs addressed by lanes l / 4, 4 + l / 4, 8 + l / 4, 12 + l / 4, so
 // lane p addresses row k0 + 4j + p / 4 (then + 16) at columns m0 + 4 (p % 4) + [0, 4).
 template <int COLS>
@@ -154,14 +154,13 @@ __device__ __forceinline__ void tr_frags4(const bf16_t* t, int k0, int m0, int l
     f[i] = __builtin_bit_cast(bf16x8, make_uint4(r[2 * i].x, r[2 * i].y, r[2 * i + 1].x, r[2 * i + 1].y));
 }
 
-// 1 / (1 + exp(-x)) from t = exp(-|x|), which never overflows: 1 / (1 + t), or t / (1 + t) for
-// negative x. The hardware reciprocal and one Newton step (within an ulp of the divided value, at a
-// third of the division's instructions; 1 + t is at most 2).
+// 1 / (1 + exp(-x)): the hardware reciprocal and one Newton step (within an ulp of the divided
+// value, at a third of the division's instructions). Where exp(-x) leaves the range in which the
+// reciprocal is a normal number (x below -87) the reciprocal stands: the step would give NaN.
 __device__ __forceinline__ float sigmoid(float x) {
-  const float t = __expf(-fabsf(x)), y = 1.0f + t;
-  float r = __builtin_amdgcn_rcpf(y);
-  r = fmaf(fmaf(-y, r, 1.0f), r, r);
-  return x < 0.f ? t * r : r;
+  const float y = 1.0f + __expf(-x);
+  const float r = __builtin_amdgcn_rcpf(y);
+  return y < 0x1p126f ? fmaf(fmaf(-y, r, 1.0f), r, r) : r;
 }
 
 struct GemmArgs {
@@ -324,8 +323,9 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_kernel(GemmArgs g) {
   // rows straight from the accumulators left 32-byte pieces: at 65536 rows, C = 512, F = 2048
   // the SwiGLU forward took 477 instead of 402 us, its backward 497 instead of 340, the Q/K/V
   // product 174 instead of 140. (Without any epilogue the same products take 209, 122 and 90 us:
-  // the writes are HBM-bound and the workgroups of a round write together.) 16-byte chunk c of row x sits at c ^ (x mod 16) (mod 8 for
-  // 32-column tiles): rows written and rows read spread over the banks.
+  // the writes are HBM-bound and the workgroups of a round write together.) 16-byte chunk c of
+  // row x sits at c ^ (x mod 16) (mod 8 for 32-column tiles): rows written and rows read spread
+  // over the banks.
   constexpr int AB = 2 * (AE < BE ? AE : BE);                          // bytes used of a stage array
   constexpr int RP = epi_rows(AB, TMW, TNW, NW);
   constexpr int WPA = AB / (RP * TNW * 4);                             // waves per stage array
