@@ -159,7 +159,7 @@ __device__ __forceinline__ float unit_scale(const float* x, int n, int& e, MaxF 
 // which no comparison passes. A head's norm bounds are padded with NaN to a whole tile of the
 // selection kernel. Every workgroup forms its head's common vector from the same 16 blocks (a
 // launch of its own for it would cost more than the loads): per channel the mean without the
-// smallest and the largest. Heads smaller than a workgroup's share of blocks do without. The
+// smallest and the largest. Heads whose blocks all fit the candidate lists do without. The
 // head's first workgroup notes whether most sampled blocks are as good as equal (flags).
 template <typename T, int HD>
 __global__ void __launch_bounds__(256) select_prep_kernel(const T* __restrict__ q, const uint8_t* __restrict__ valid,
@@ -170,6 +170,7 @@ __global__ void __launch_bounds__(256) select_prep_kernel(const T* __restrict__ 
                                                           float* __restrict__ knorm, float* __restrict__ kabs,
                                                           float* __restrict__ ksum, int* __restrict__ flags) {
   constexpr int CPR = HD / 8, NS = 16;   // sampled blocks
+  static_assert(2 * kFlat / 16 >= 256 / CPR, "heads with a common vector hold whole workgroups");
   __shared__ float sample[NS][HD], common[HD];
   if ((int)blockIdx.x < pool_blocks) {
     const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
@@ -201,7 +202,7 @@ __global__ void __launch_bounds__(256) select_prep_kernel(const T* __restrict__ 
   const long long blk = i / CPR;   // (b*H + h) * nblk + block, nblk = 2^lgb
   const int r = 1 << lgr, c = 8 * (int)(i % CPR);
   const int nblk = 1 << lgb;
-  const bool centred = nblk >= 256 / CPR;   // the workgroup's blocks are of one head
+  const bool centred = nblk > kFlat / 16;   // (then the workgroup's blocks are of one head)
   const int row = (int)threadIdx.x / CPR, srow = row % NS;
   // eight channels of the thread's block and of the block it samples: the keys' sum (rounded once
   // when used: within 2^-24 of the true sum, whatever cancels), an upper bound of the sum of their

@@ -1,9 +1,9 @@
 """Group top-k on inputs whose scores are whole numbers (exact in float32), so the selected
 blocks must equal the float64 oracle's bit for bit: many tied scores, keys that differ little
-from a large common vector (candidate lists overflow and groups are scanned exactly), equal
-keys, zero queries, one key far longer than the rest; every list width, block ratio and head
-dim of the kernel, from one partly filled key tile to several, for bf16 layers and (head dim
-32) the float32 layers' scores from bf16 parts."""
+from a large common vector, equal keys (the filter is skipped and every block scored), zero
+queries, one key far longer than the rest; every list width, block ratio and head dim of the
+kernel, from one partly filled key tile to several, for bf16 layers and (head dim 32) float32
+ones. Then scores that are equal in float32 only, and real values against float64 scores."""
 import numpy as np
 import pytest
 import torch
