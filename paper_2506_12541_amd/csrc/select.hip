@@ -46,9 +46,10 @@
 // is 1.6 * 2^-10.
 // A dot errs by at most 12 * 2^-24 |q| |sum of the keys| (11 roundings, one in the summed key);
 // kDotErr adds the six products' 2^-15.
-// What bounds it: VALU issue (75 instructions per 64 blocks and 16 groups in both streams,
-// about 3000 per 16 groups for the ranking), and with few waves per SIMD the latency of each
-// tile. Measured with its preparation, k* = 16, d = 64, r = 2, N(0, 1) tensors (in brackets: one
+// What bounds it: at 65536 queries in groups of 16 (two waves per SIMD) the latency of each tile
+// and of the ranking, issue taking 26% of the time; with more waves VALU issue (75 instructions per
+// 64 blocks and 16 groups in both streams, about 3000 per 16 groups for the ranking).
+// Measured with its preparation, k* = 16, d = 64, r = 2, N(0, 1) tensors (in brackets: one
 // stream of all compressed keys with the six products and a 16-deep list in every lane): 65536
 // queries x 8 heads in groups of 16 0.10 ms (0.27), one by one 0.91 (2.73); 2^20 queries x 16
 // heads in groups of 32 4.8 ms (15.7). Two sets of 16 groups per wave, which halve the LDS reads
