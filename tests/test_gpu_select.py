@@ -99,6 +99,40 @@ def test_equal_float32_scores_rank_by_block(f32, d, g, many):
         assert np.array_equal(saved.sel_idx[0, h].cpu().numpy(), want), h
 
 
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), -float("inf")])
+@pytest.mark.parametrize("shape,f32", [(SHAPES[1], False), (SHAPES[2], False), (SHAPES[4], False), (SHAPES[6], False),
+                                       (SHAPES[3], True)],
+                         ids=lambda s: "-".join(map(str, s)) if isinstance(s, tuple) else ("f32" if s else "bf16"))
+def test_select_non_finite(shape, f32, bad):
+    """A block with a value that is not finite in one of its keys is never selected, whatever the
+    query, and a group whose pooled query is not finite selects nothing (products of three parts
+    turn an infinity into NaN); every other group selects as the oracle does without that block."""
+    n, m, l, ls, kk, g, d = shape
+    print(f"select non-finite {shape} f32={f32} {bad}", flush=True)
+    rng = np.random.default_rng([n, d, g])
+    H, r = 2, ls // l
+    q = rng.integers(-3, 4, (1, H, n, d)).astype(np.float64)
+    kc = rng.integers(-1, 2, (H, n // l, d)).astype(np.float64)
+    P = ob.Params(ball=m, cmp_block=l, slc_block=ls, topk=kk, group=g, kv_pool="mean")
+    want, valid = [], np.ones(n, bool)
+    blk, grp = [3, n // ls - 2], n // g // 2
+    for h in range(H):
+        scores = ob.group_block_scores(q[0, h], kc[h], valid, P)
+        scores[:, blk] = -np.inf
+        scores[grp] = -np.inf
+        want.append(ob.topk_blocks(scores, kk))
+    k = np.repeat(kc, l, axis=1)[None]
+    k[:, :, blk[0] * ls, 5] = bad
+    k[:, :, blk[1] * ls + (r - 1) * l, d - 1] = bad
+    q[:, :, grp * g, 7] = bad
+    p = gb.Params(batch=1, n=n, heads=H, head_dim=d, ball_size=m, cmp_block=l, slc_block=ls, topk=kk, group_size=g,
+                  kv_pool=gb.BSA_POOL_MEAN, dtype=gb.BSA_F32 if f32 else gb.BSA_BF16)
+    qd, kd = (torch.from_numpy(np.ascontiguousarray(a)).to("cuda").to(p.torch_dtype) for a in (q, k))
+    _, saved = gb.forward(p, qd, kd, kd, None, torch.zeros((1, n, 3), device="cuda"), None, None)
+    for h in range(H):
+        assert np.array_equal(saved.sel_idx[0, h].cpu().numpy(), want[h]), h
+
+
 # n, ball, l, l', k*, g, d
 REAL = [
     (4096, 256, 8, 16, 8, 8, 32),
