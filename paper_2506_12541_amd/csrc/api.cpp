@@ -225,7 +225,7 @@ BwdWs bwd_ws_layout(const bsa::Dims& D) {
   W.psm = put(sizeof(float) * (size_t)W.mlp_chunks_small * ((size_t)D.d * D.d + 2 * D.d));
   W.w1lp = put(elem_bytes(D) * (size_t)D.l * D.d * D.d);
   W.dplp = put(elem_bytes(D) * crows * D.d);
-  // the value MLP's own copies (its backward shares the key MLP's launches: 0.30 -> 0.22 ms for
+  // the value MLP's own copies (its backward shares the key MLP's launches: 0.30 -> 0.21 ms for
   // both at 65536 points x 8 heads of 64, where the copies take 34 MB)
   const bool mlp = D.pool == 0;
   W.dpre_v = put(mlp ? sizeof(float) * crows * D.d : 0);
